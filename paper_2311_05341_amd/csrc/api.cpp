@@ -38,7 +38,9 @@ int copy_tables(const dd_plan &p, void *dst, void *stream) {
   uint8_t *base = (uint8_t *)dst;
   const TableLayout L = table_layout(p);
   hipError_t e = hipSuccess;
-  if (p.desc.dtype != DD_F32 && is_direct(p.fwd)) {  // the direct kernel reads the plain shift table
+  if (p.gtab.use) {
+    e = hipMemcpyAsync(base, p.gtab.data.data(), p.gtab.data.size() * 4, hipMemcpyHostToDevice, st);
+  } else if (p.desc.dtype != DD_F32 && is_direct(p.fwd)) {  // the direct kernel reads the plain shift table
     e = hipMemcpyAsync(base + L.int_offs, p.shift.data(), p.shift.size() * sizeof(int32_t), hipMemcpyHostToDevice, st);
   } else if (p.desc.dtype != DD_F32) {
     e = hipMemcpyAsync(base + L.int_offs, p.itab.offs.data(), p.itab.offs.size() * 4, hipMemcpyHostToDevice, st);
@@ -172,7 +174,7 @@ dd_status dd_execute(const dd_plan *p, const void *d_in, float *d_out, int64_t o
   if (out_pitch < p->n_out) return fail(DD_ERR_ARG, "out_pitch < n_out");
   if (out_pitch % 4) return fail(DD_ERR_ALIGN, "out_pitch must be a multiple of 4 elements");
   int e = p->desc.dtype == DD_F32 ? launch_forward_f32(*p, p->d_tables, d_in, d_out, out_pitch, stream)
-                                  : launch_forward_int(*p, p->d_tables, d_in, d_out, out_pitch, stream);
+                                  : launch_forward(*p, p->d_tables, d_in, d_out, out_pitch, stream);
   if (e) return hip_fail(e, "forward launch");
   return DD_OK;
 }

@@ -7,6 +7,7 @@
 #include <vector>
 
 #include "../../include/dd.h"
+#include "group_tables.h"
 
 namespace dd {
 
@@ -53,6 +54,7 @@ inline int int_entry_words(int dm_per_wave, int segs) {
 struct IntTables {
   std::vector<uint32_t> offs;  // [n_dblk][waves][n_chan rounded up to chan_block][int_entry_words]
   std::vector<int32_t> sbase;  // [n_dblk][n_chan]
+  size_t offs_words = 0, sbase_words = 0;  // their sizes, also where they are not filled in
   int row_bytes = 0, chan_block = 0, segs = 0, lds_bytes = 0;
 };
 // Tables of the float kernel (forward or adjoint) for one tile shape.  The
@@ -80,7 +82,8 @@ struct dd_plan {
   int64_t in_pitch_bytes = 0;
   dd::TileCfg fwd;             // forward tile shape
   int32_t span_fwd = 0;        // largest delay spread inside a forward DM block
-  dd::IntTables itab;          // integer plans: forward kernel tables
+  dd::IntTables itab;          // integer plans: staged forward kernel's tables (sizes only while gtab is in use)
+  dd::GroupTables gtab;        // integer plans: group-sum tables; in use until tiles are chosen explicitly
   dd::FloatTables ftab_fwd;    // float plans: forward kernel tables
   dd::FloatTables ftab_adj;    // float plans: adjoint kernel tables
   // binding
@@ -98,7 +101,9 @@ dd_status choose_forward_tiles(dd_plan &p);
 // Rebuild the tables of one direction (0 forward, 1 adjoint) for compiled
 // shape `shape` and TileOrder `order`.  DD_ERR_RANGE if the shape cannot hold
 // the plan's delay spread; the plan is unchanged then.
-dd_status set_tiles(dd_plan &p, int direction, int shape, int order);
+// An integer plan's forward then runs that shape's kernel (gtab.use is cleared).
+// With fill false an integer plan's staged tables are only sized.
+dd_status set_tiles(dd_plan &p, int direction, int shape, int order, bool fill = true);
 int num_shapes(const dd_plan &p);
 size_t table_bytes(const dd_plan &p);
 // Byte offsets of the plan's current tables inside a table workspace of
@@ -153,6 +158,15 @@ enum OutMode { kOutFloat = 0, kOutRawTotals = 1, kOutCombineHigh = 2 };
 // for DD_U16 plans only.
 int launch_forward_int(const dd_plan &p, const void *tables, const void *d_in, float *d_out, int64_t out_pitch,
                        void *stream, int64_t out_limit = 0, int out_mode = kOutFloat);
+// The kernel of the plan's shape (p.fwd) and, where the plan uses them, the
+// group-sum kernel (fwd_group.hip); launch_forward picks between the two.
+int launch_forward_group(const dd_plan &p, const void *tables, const void *d_in, float *d_out, int64_t out_pitch,
+                         void *stream, int64_t out_limit = 0, int out_mode = kOutFloat);
+inline int launch_forward(const dd_plan &p, const void *tables, const void *d_in, float *d_out, int64_t out_pitch,
+                          void *stream, int64_t out_limit = 0, int out_mode = kOutFloat) {
+  return (p.gtab.use ? launch_forward_group : launch_forward_int)(p, tables, d_in, d_out, out_pitch, stream, out_limit,
+                                                                  out_mode);
+}
 int launch_forward_f32(const dd_plan &p, const void *tables, const void *d_in, float *d_out, int64_t out_pitch,
                        void *stream, int64_t out_limit = 0);
 // Float tile shapes compiled into the library: (ns, per_wave, waves, row_block).

@@ -1,0 +1,470 @@
+// Host tables of the group-sum kernel: see group_tables.h.
+#include "group_tables.h"
+
+#include <string.h>
+
+#include <algorithm>
+#include <climits>
+#include <new>
+#include <thread>
+
+namespace dd {
+namespace {
+
+constexpr int kMaxGroup = 12;   // channels per group
+constexpr int kGroupStep = 4;   // group sizes are multiples of this (the last group of the band aside)
+constexpr int kSizes = kMaxGroup / kGroupStep;
+constexpr uint32_t kZeroRow = 2 * kGrpSetBytes;  // LDS offset of the row of zeros
+
+struct Group {
+  int c0 = 0, g = 0;
+  int words = 0;                   // words of a pattern row (a multiple of 4)
+  int n_pat = 0;
+  uint8_t slot_of[kGrpMaxRows];       // pattern of each DM row, in path order
+  std::vector<int32_t> r;          // [n_pat][g] relative delays, in path order
+  int base = 0;
+  int lds() const { return n_pat * words * 4; }
+};
+
+struct Block {
+  std::vector<uint32_t> rec[kGrpWaves];  // operation blocks numbered from 1 (0: the idle one)
+  std::vector<uint32_t> ops;
+  std::vector<uint32_t> sum;
+  int n_steps = 0;
+  int64_t lo = INT64_MAX, hi = INT64_MIN;
+  double cost = 0;
+  int lds = 0;
+  bool ok = true;
+};
+
+// Instructions that one chunk of a group's partial sums costs a wave.
+constexpr double kCostAdd = 13, kCostMove = 23, kCostFold = 12, kCostWrite = 4, kCostRecord = 40;
+// Weight of all waves' work against the busiest wave's where a step's work is split.
+constexpr double kCostShared = 1.0, kCostCrowd = 3.0;
+
+// Modelled clocks of a group with n_pat patterns over rows of `words` words: its
+// LDS time (4 bytes per word written once and per window word read) and its
+// instructions on 4 SIMDs, the larger in full.  A group that takes more than a
+// fifth of an LDS set leaves a step too few parts for all waves.
+double group_cost(int rows, int g, int n_pat, int words, double steps) {
+  const int chunks = (words + kGrpChunk - 1) / kGrpChunk;
+  const double bytes = 4.0 * n_pat * words;
+  const double lds = (bytes + 4.0 * rows * kGrpWin) / 110.0;
+  double build = chunks * (kCostAdd * g + 3 * kCostFold + kCostMove * steps + kCostWrite * n_pat +
+                           kCostRecord * (g + steps + 4) / kGrpOps);
+  build *= 1.0 + kCostCrowd * std::max(0.0, bytes / (0.2 * kGrpSetBytes) - 1.0);
+  const double sum = rows * 18.0;
+  return std::max(lds, build + sum) + 0.2 * std::min(lds, build + sum) + 40.0;
+}
+
+double guess_steps(int n_pat) { return n_pat - 1 + 0.04 * n_pat * n_pat; }
+
+int distinct(const uint64_t *h, int rows) {
+  uint64_t tab[2 * kGrpMaxRows];
+  bool used[2 * kGrpMaxRows] = {};
+  int n = 0;
+  for (int d = 0; d < rows; ++d) {
+    int i = (int)((h[d] * 0x9E3779B97F4A7C15ull) >> 57);
+    while (used[i] && tab[i] != h[d]) i = (i + 1) & (2 * kGrpMaxRows - 1);
+    if (!used[i]) {
+      used[i] = true;
+      tab[i] = h[d];
+      ++n;
+    }
+  }
+  return n;
+}
+
+// Fill in a group's patterns and the path over them.
+void fill_group(const int32_t *sh, int rows, Group *G) {
+  const int g = G->g;
+  const int32_t *s0 = sh + (size_t)G->c0 * rows;
+  int first[kGrpMaxRows], cls[kGrpMaxRows], n = 0;
+  for (int d = 0; d < rows; ++d) {
+    int k = 0;
+    for (; k < n; ++k) {
+      bool same = true;
+      for (int c = 1; c < g && same; ++c) {
+        const int32_t *s = s0 + (size_t)c * rows;
+        same = s[d] - s0[d] == s[first[k]] - s0[first[k]];
+      }
+      if (same) break;
+    }
+    if (k == n) first[n++] = d;
+    cls[d] = k;
+  }
+  std::vector<int32_t> pat((size_t)n * g);
+  int start = 0;
+  int64_t best = INT64_MAX;
+  for (int k = 0; k < n; ++k) {
+    int64_t sum = 0;
+    for (int c = 0; c < g; ++c) {
+      pat[(size_t)k * g + c] = s0[(size_t)c * rows + first[k]] - s0[first[k]];
+      sum += pat[(size_t)k * g + c];
+    }
+    if (sum < best) best = sum, start = k;
+  }
+  // nearest-neighbour path in the number of one-sample moves
+  bool used[kGrpMaxRows] = {};
+  int place[kGrpMaxRows];
+  G->r.resize((size_t)n * g);
+  int cur = start;
+  for (int i = 0; i < n; ++i) {
+    used[cur] = true;
+    place[cur] = i;
+    std::copy_n(&pat[(size_t)cur * g], g, &G->r[(size_t)i * g]);
+    int next = -1;
+    int64_t bd = INT64_MAX;
+    for (int k = 0; k < n; ++k) {
+      if (used[k]) continue;
+      int64_t dist = 0;
+      for (int c = 0; c < g; ++c) dist += std::abs((int64_t)pat[(size_t)k * g + c] - pat[(size_t)cur * g + c]);
+      if (dist < bd) bd = dist, next = k;
+    }
+    cur = next;
+  }
+  G->n_pat = n;
+  for (int d = 0; d < rows; ++d) G->slot_of[d] = (uint8_t)place[cls[d]];
+}
+
+struct Input {
+  const int32_t *shift;
+  int n_dm, n_chan, bits;
+  int64_t pitch;
+  uint32_t sample_max() const { return bits == 16 ? 0 : (1u << bits) - 1; }
+};
+
+struct Op {
+  int32_t s, c;
+  uint32_t flags;
+};
+
+// The operations that build some of a group's patterns, as operation blocks.
+struct Part {
+  int words, chunks;
+  uint32_t slot;     // LDS address of its first pattern's row
+  uint32_t block0;   // first operation block
+  std::vector<int> rows;  // rows written by each block
+  double cost;       // of one chunk
+};
+
+// Append `ops` as operation blocks.  Spare operations of the last one repeat its
+// first window and do nothing.
+void emit_ops(const Input &in, const std::vector<Op> &ops, Block *b, Part *part) {
+  const int per_load = in.bits == 16 ? 2 : 4;  // samples
+  for (size_t i = 0; i < ops.size(); i += kGrpOps) {
+    int64_t off[kGrpOps], base = INT64_MAX;
+    for (int q = 0; q < kGrpOps; ++q) {
+      const Op &op = ops[i + q < ops.size() ? i + q : i];
+      off[q] = op.c * in.pitch + ((int64_t)op.s & ~(int64_t)(per_load - 1)) * in.bits / 8;
+      base = std::min(base, off[q]);
+      b->lo = std::min<int64_t>(b->lo, op.s - 3);
+      b->hi = std::max<int64_t>(b->hi, (int64_t)op.s + part->chunks * kGrpChunk + 12);
+    }
+    part->rows.push_back(0);
+    part->cost += kCostRecord;
+    uint32_t words[kGrpBlockWords] = {(uint32_t)base, (uint32_t)(base >> 32)};
+    for (int q = 0; q < kGrpOps; ++q) {
+      if (off[q] - base > kGrpMaxOffset) b->ok = false;
+      words[4 + q] = (uint32_t)(off[q] - base);
+      if (i + q >= ops.size()) continue;
+      const uint32_t kind = ops[i + q].flags | (uint32_t)(ops[i + q].s & (per_load - 1));
+      words[2 + q / 4] |= kind << (8 * (q % 4));
+      part->cost += kind & kOpMove ? kCostMove : kCostAdd;
+      if (kind & kOpFold) part->cost += kCostFold;
+      if (kind & kOpWrite) ++part->rows.back(), part->cost += kCostWrite;
+    }
+    b->ops.insert(b->ops.end(), words, words + kGrpBlockWords);
+  }
+}
+
+// Patterns [p0, p1) of a group: the first one's adds, phase by phase, then moves.
+Part make_part(const Input &in, const Group &G, int p0, int p1, uint32_t slot0, Block *b) {
+  const int g = G.g, per_load = in.bits == 16 ? 2 : 4;
+  Part part = {};
+  part.words = G.words;
+  part.chunks = (G.words + kGrpChunk - 1) / kGrpChunk;
+  part.slot = slot0 + (uint32_t)(p0 * G.words * 4);
+  part.block0 = (uint32_t)(b->ops.size() / kGrpBlockWords) + 1;
+  std::vector<Op> ops;
+  for (int m = 0; m < per_load; ++m) {
+    const size_t n = ops.size();
+    for (int c = 0; c < g; ++c) {
+      const int32_t s = G.base + G.r[(size_t)p0 * g + c];
+      if ((s & (per_load - 1)) == m) ops.push_back({s, G.c0 + c, kOpAdd});
+    }
+    if (ops.size() > n) ops.back().flags |= kOpFold;
+  }
+  ops.back().flags |= kOpWrite;
+  for (int p = p0 + 1; p < p1; ++p) {
+    const int32_t *from = &G.r[(size_t)(p - 1) * g], *to = &G.r[(size_t)p * g];
+    for (int c = 0; c < g; ++c) {
+      for (int32_t v = from[c]; v < to[c]; ++v) ops.push_back({G.base + v, G.c0 + c, kOpMove});
+      for (int32_t v = from[c]; v > to[c]; --v) ops.push_back({G.base + v - 1, G.c0 + c, kOpMove | kOpDown});
+    }
+    ops.back().flags |= kOpWrite;
+  }
+  emit_ops(in, ops, b, &part);
+  return part;
+}
+
+// Records of one chunk of a part for wave stream `rec`.
+void emit_chunk(const Part &part, int chunk, std::vector<uint32_t> *rec) {
+  const int k0 = chunk * kGrpChunk, lanes = std::min(63, (part.words - k0 + 3) / 4);
+  uint32_t slot = part.slot + 4u * (uint32_t)k0;
+  for (size_t i = 0; i < part.rows.size(); ++i) {
+    rec->push_back(part.block0 + (uint32_t)i);
+    rec->push_back((i == 0 ? kRecStart : 0) | (uint32_t)lanes << 8 | (uint32_t)k0 << 16);
+    rec->push_back(slot);
+    rec->push_back((uint32_t)part.words * 4);
+    slot += (uint32_t)(part.rows[i] * part.words * 4);
+  }
+}
+
+void end_step(std::vector<uint32_t> *rec, size_t mark) {
+  if (rec->size() == mark) rec->resize(mark + kGrpRecWords, 0);  // nothing to do in the step: an idle record
+  (*rec)[rec->size() - kGrpRecWords + 1] |= kRecLast;
+}
+
+void build_block(const Input &in, int blk, bool cost_only, Block *b) {
+  const int n_chan = in.n_chan, rows = group_rows(in.bits), per_wave = group_rows_per_wave(in.bits);
+  const size_t sum_words = group_sum_words(in.bits);
+  const uint32_t sample_max = in.sample_max();
+  // delays of the block's rows, channel by channel; rows past the last repeat it
+  std::vector<int32_t> sh((size_t)n_chan * rows);
+  for (int d = 0; d < rows; ++d) {
+    const int32_t *row = in.shift + (size_t)std::min(blk * rows + d, in.n_dm - 1) * n_chan;
+    for (int c = 0; c < n_chan; ++c) sh[(size_t)c * rows + d] = row[c];
+  }
+  auto words_of = [&](int c) {
+    const int32_t *s = &sh[(size_t)c * rows];
+    return (int)std::min<int64_t>(((int64_t)kGrpWin + s[rows - 1] - s[0] + 3) / 4 * 4, INT_MAX);
+  };
+  // Split the band into groups of least modelled time (dynamic programming over
+  // the multiples of kGroupStep).
+  const int np = (n_chan + kGroupStep - 1) / kGroupStep;
+  std::vector<double> cost(np + 1, 1e300);
+  std::vector<int> len(np + 1, 0);
+  cost[0] = 0;
+  for (int p = 0; p < np; ++p) {
+    if (cost[p] >= 1e300) continue;
+    const int c0 = p * kGroupStep;
+    const int words = words_of(c0);
+    if (words > kGrpMaxWords) continue;
+    const int32_t *s0 = &sh[(size_t)c0 * rows];
+    uint64_t h[kGrpMaxRows] = {};
+    for (int k = 1; k <= kSizes && p + k <= np; ++k) {
+      const int lo = std::max(c0 + 1, c0 + (k - 1) * kGroupStep), hi = std::min(n_chan, c0 + k * kGroupStep);
+      for (int c = lo; c < hi; ++c) {
+        const int32_t *s = &sh[(size_t)c * rows];
+        for (int d = 0; d < rows; ++d)
+          h[d] = h[d] * 0xD1342543DE82EF95ull + (uint64_t)(uint32_t)(s[d] - s0[d]) + 1;
+      }
+      const int n = distinct(h, rows);
+      if ((int64_t)n * words * 4 > kGrpSetBytes) break;
+      const double v = cost[p] + group_cost(rows, hi - c0, n, words, guess_steps(n));
+      if (v < cost[p + k]) cost[p + k] = v, len[p + k] = k;
+      if (n > rows * 7 / 8) break;
+    }
+  }
+  if (cost[np] >= 1e300) {
+    b->ok = false;
+    return;
+  }
+  b->cost = cost[np];
+  if (cost_only) return;
+  std::vector<Group> groups;
+  for (int p = np; p > 0; p -= len[p]) {
+    Group G;
+    G.c0 = (p - len[p]) * kGroupStep;
+    G.g = std::min(n_chan, p * kGroupStep) - G.c0;
+    G.words = words_of(G.c0);
+    G.base = sh[(size_t)G.c0 * rows];
+    groups.push_back(std::move(G));
+  }
+  std::reverse(groups.begin(), groups.end());
+  for (Group &G : groups) {
+    fill_group(sh.data(), rows, &G);
+    if (G.lds() > kGrpSetBytes) {
+      b->ok = false;
+      return;
+    }
+  }
+  // Steps: as many groups as fit in one LDS set, at most
+  // 2 * kGrpStepPairs.  A group is
+  // built in one or more parts (runs of its patterns), each chunk of a part by one
+  // wave: the longest first to the wave with the least work, with as many parts
+  // as make the busiest wave's work least.
+  int64_t acc = 0;  // channels since the last flush of the 16-bit sums
+  for (size_t i = 0; i < groups.size(); ++b->n_steps) {
+    const uint32_t set = (uint32_t)(b->n_steps & 1) * kGrpSetBytes;
+    size_t j = i;
+    int bytes = 0;
+    while (j < groups.size() && j < i + 2 * kGrpStepPairs && bytes + groups[j].lds() <= kGrpSetBytes) bytes += groups[j++].lds();
+    b->lds = std::max(b->lds, (int)set + bytes);
+    struct Task {
+      int part, chunk;
+    };
+    double best = 1e300;
+    std::vector<uint32_t> best_ops;
+    std::vector<Part> best_parts;
+    std::vector<int> best_wave;
+    std::vector<Task> best_tasks;
+    const size_t ops_mark = b->ops.size();
+    for (int split = 1; split <= 4 && (split == 1 || 4 * best_tasks.size() < 3 * kGrpWaves); ++split) {
+      std::vector<Part> parts;
+      uint32_t slot = set;
+      for (size_t q = i; q < j; ++q) {
+        const Group &G = groups[q];
+        const int n = std::min(split, G.n_pat);
+        for (int k = 0; k < n; ++k) parts.push_back(make_part(in, G, G.n_pat * k / n, G.n_pat * (k + 1) / n, slot, b));
+        slot += (uint32_t)G.lds();
+      }
+      std::vector<Task> tasks;
+      for (size_t k = 0; k < parts.size(); ++k)
+        for (int c = 0; c < parts[k].chunks; ++c) tasks.push_back({(int)k, c});
+      std::stable_sort(tasks.begin(), tasks.end(),
+                       [&](const Task &x, const Task &y) { return parts[x.part].cost > parts[y.part].cost; });
+      double load[kGrpWaves] = {}, simd[4] = {}, total = 0;
+      std::vector<int> wave;
+      for (const Task &t : tasks) {  // (waves w, w + 4, ... share a SIMD)
+        int w = 0;
+        for (int k = 1; k < kGrpWaves; ++k)
+          if (load[k] < load[w] || (load[k] == load[w] && simd[k & 3] < simd[w & 3])) w = k;
+        load[w] += parts[t.part].cost;
+        simd[w & 3] += parts[t.part].cost;
+        total += parts[t.part].cost;
+        wave.push_back(w);
+      }
+      const double cost = *std::max_element(load, load + kGrpWaves) + kCostShared * total / kGrpWaves;
+      if (cost < best) {
+        best = cost;
+        best_ops.assign(b->ops.begin() + ops_mark, b->ops.end());
+        best_parts = std::move(parts);
+        best_tasks = std::move(tasks);
+        best_wave = std::move(wave);
+      }
+      b->ops.resize(ops_mark);
+    }
+    b->ops.insert(b->ops.end(), best_ops.begin(), best_ops.end());
+    size_t mark[kGrpWaves];
+    for (int w = 0; w < kGrpWaves; ++w) mark[w] = b->rec[w].size();
+    for (size_t k = 0; k < best_tasks.size(); ++k)
+      emit_chunk(best_parts[best_tasks[k].part], best_tasks[k].chunk, &b->rec[best_wave[k]]);
+    for (int w = 0; w < kGrpWaves; ++w) end_step(&b->rec[w], mark[w]);
+    const size_t sm = b->sum.size();
+    b->sum.resize(sm + kGrpWaves * sum_words, kZeroRow);
+    uint32_t slot = set;
+    for (size_t q = i; q < j; ++q) {
+      const Group &G = groups[q];
+      const size_t pair = (q - i) / 2, half = (q - i) % 2;
+      uint32_t marks = 0;
+      acc += G.g;
+      if (half == 1 || q + 1 == j) {
+        int64_t next = 0;
+        for (size_t k = q + 1; k < std::min(groups.size(), q + 3); ++k) next += groups[k].g;
+        if (sample_max && (!next || (acc + next) * sample_max > 65535)) marks |= kSumFlush, acc = 0;
+        if (q + 1 == j) marks |= kSumLast;
+      }
+      for (int d = 0; d < rows; ++d) {
+        uint32_t *e = &b->sum[sm + (size_t)(d / per_wave) * sum_words + pair * 2 * per_wave];
+        const int32_t u = sh[(size_t)G.c0 * rows + d] - G.base;
+        uint32_t &dst = e[half * per_wave + d % per_wave];
+        dst = (dst & ~kSumOffset) | (slot + 4u * (uint32_t)(G.slot_of[d] * G.words + u));
+        if (d % per_wave == 0) e[0] |= marks;
+      }
+      slot += (uint32_t)G.lds();
+    }
+    i = j;
+  }
+  for (auto &r : b->rec) end_step(&r, r.size());  // nothing is built during the last step
+}
+
+}  // namespace
+
+bool build_group_tables(const int32_t *shift, int n_dm, int n_chan, int bits, int64_t pitch_bytes, GroupTables *t,
+                        double max_cost) {
+  static_assert(sizeof(GroupBlock) == 72, "device layout");
+  static_assert(kMaxGroup * 255 <= 65535, "a group's packed sums fit 16 bits");
+  *t = GroupTables();
+  const int n_blk = (n_dm + group_rows(bits) - 1) / group_rows(bits);
+  const Input in = {shift, n_dm, n_chan, bits, pitch_bytes};
+  try {
+    std::vector<Block> blocks(n_blk);
+    const int64_t work = (int64_t)n_blk * n_chan;
+    if (max_cost > 0 && n_blk > 3) {  // plans that are far from it: the costs of two blocks tell
+      Block mid, last;
+      build_block(in, n_blk / 2, true, &mid);
+      if (mid.ok) build_block(in, n_blk - 1, true, &last);
+      if (!mid.ok || !last.ok || 0.5 * n_blk * (mid.cost + last.cost) > 1.2 * max_cost) return false;
+    }
+    const int nthr = (int)std::min<int64_t>({16, n_blk, std::max<int64_t>(1, work / 512),
+                                             std::max(1u, std::thread::hardware_concurrency())});
+    bool bad = false;
+    auto run = [&](int k, bool *failed) {
+      try {
+        for (int b = k; b < n_blk; b += nthr) build_block(in, b, false, &blocks[b]);
+      } catch (const std::bad_alloc &) {
+        *failed = true;
+      }
+    };
+    if (nthr == 1) {
+      run(0, &bad);
+    } else {
+      std::vector<std::thread> th;
+      std::vector<uint8_t> failed(nthr, 0);
+      for (int k = 0; k < nthr; ++k) th.emplace_back(run, k, (bool *)&failed[k]);
+      for (auto &x : th) x.join();
+      for (uint8_t f : failed) bad |= f != 0;
+    }
+    if (bad) return false;
+    size_t recs = 0, ops = kGrpBlockWords, sums = 0;
+    t->lo = 0;  // the idle operation block loads the tile's own samples of channel 0
+    t->hi = kGrpChunk + 12;
+    for (const Block &b : blocks) {
+      if (!b.ok) return false;
+      for (const auto &r : b.rec) recs += r.size();
+      sums += b.sum.size();
+      ops += b.ops.size();
+      t->lo = std::min(t->lo, b.lo);
+      t->hi = std::max(t->hi, b.hi);
+      t->cost += b.cost;
+      t->lds_bytes = std::max(t->lds_bytes, b.lds);
+    }
+    if (max_cost > 0 && t->cost > max_cost) return false;
+    t->n_blk = n_blk;
+    t->rec_off = ((int64_t)n_blk * (int64_t)(sizeof(GroupBlock) / 4) + 63) / 64 * 64;
+    t->op_off = (t->rec_off + (int64_t)recs + 4 * kGrpRecWords + 63) / 64 * 64;  // records are loaded ahead
+    t->sum_off = (t->op_off + (int64_t)ops + 63) / 64 * 64;
+    const int64_t total = t->sum_off + (int64_t)sums + 64;  // a wave loads 64 entries
+    if (total >= ((int64_t)1 << 31)) return false;
+    t->data.assign((size_t)total, 0);
+    size_t ro = 0, oo = kGrpBlockWords, so = 0;
+    for (int b = 0; b < n_blk; ++b) {
+      GroupBlock g = {};
+      const uint32_t op0 = (uint32_t)(oo / kGrpBlockWords) - 1;  // the block's operation blocks count from 1
+      for (int k = 0; k < kGrpWaves; ++k) {
+        std::vector<uint32_t> &r = blocks[b].rec[k];
+        for (size_t i = 0; i < r.size(); i += kGrpRecWords)
+          if (r[i]) r[i] += op0;
+        g.rec_first[k] = (uint32_t)(ro / kGrpRecWords);
+        std::copy(r.begin(), r.end(), t->data.begin() + t->rec_off + ro);
+        ro += r.size();
+      }
+      std::copy(blocks[b].ops.begin(), blocks[b].ops.end(), t->data.begin() + t->op_off + oo);
+      oo += blocks[b].ops.size();
+      g.sum_first = (uint32_t)so;
+      g.n_steps = (uint32_t)blocks[b].n_steps;
+      g.n_steps = (uint32_t)blocks[b].n_steps;
+      std::copy(blocks[b].sum.begin(), blocks[b].sum.end(), t->data.begin() + t->sum_off + so);
+      so += blocks[b].sum.size();
+      memcpy(&t->data[(size_t)b * (sizeof g / 4)], &g, sizeof g);
+      blocks[b] = Block();
+    }
+  } catch (const std::bad_alloc &) {
+    return false;
+  }
+  return true;
+}
+
+}  // namespace dd

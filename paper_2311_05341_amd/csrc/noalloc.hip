@@ -69,7 +69,7 @@ extern "C" dd_status dd_execute_noalloc(const dd_plan *p, const void *d_in, floa
   e = copy_tables(*p, tables, stream);
   if (e) return hip_error(e, "table upload");
   e = p->desc.dtype == DD_F32 ? launch_forward_f32(*p, tables, d_in, d_out, out_pitch, stream)
-                              : launch_forward_int(*p, tables, d_in, d_out, out_pitch, stream);
+                              : launch_forward(*p, tables, d_in, d_out, out_pitch, stream);
   if (e) return hip_error(e, "forward launch");
   return DD_OK;
 }

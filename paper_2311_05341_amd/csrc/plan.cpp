@@ -162,13 +162,15 @@ dd_status build_int_tables(const dd_plan &p, int ns, int dm_per_wave, int waves,
   t->chan_block = chan_block;
   t->segs = segs;
   t->lds_bytes = (int)lds;
-  if (!fill) return DD_OK;
   const int n_dblk = (nd + dblk - 1) / dblk;
   const int ew = int_entry_words(dm_per_wave, segs);  // 32-bit words per channel
   const int ncp = (nc + chan_block - 1) / chan_block * chan_block;  // channels rounded up to whole blocks
+  t->offs_words = (size_t)n_dblk * waves * ncp * ew;
+  t->sbase_words = (size_t)n_dblk * nc;
+  if (!fill) return DD_OK;
   try {
-    t->offs.assign((size_t)n_dblk * waves * ncp * ew, 0);
-    t->sbase.assign((size_t)n_dblk * nc, 0);
+    t->offs.assign(t->offs_words, 0);
+    t->sbase.assign(t->sbase_words, 0);
   } catch (const std::bad_alloc &) {
     return fail(DD_ERR_NOMEM, "table allocation failed");
   }
@@ -267,7 +269,7 @@ int num_shapes(const dd_plan &p) {
   return p.desc.dtype == DD_F32 ? kNumF32Shapes : kNumIntShapes + kNumDirectShapes;
 }
 
-dd_status set_tiles(dd_plan &p, int direction, int shape, int order) {
+dd_status set_tiles(dd_plan &p, int direction, int shape, int order, bool fill) {
   if (direction != 0 && !(direction == 1 && p.desc.dtype == DD_F32))
     return fail(DD_ERR_ARG, "direction must be 0 (forward) or 1 (adjoint, float plans)");
   if (shape < 0 || shape >= num_shapes(p)) return fail(DD_ERR_ARG, "no such tile shape");
@@ -306,9 +308,10 @@ dd_status set_tiles(dd_plan &p, int direction, int shape, int order) {
     p.fwd = t;
     p.span_fwd = max_dm_block_span(p, t.waves * t.dm_per_wave);
     p.itab = IntTables();
+    p.gtab.use = false;
     return DD_OK;
   }
-  const dd_status st = build_int_tables(p, k[0], k[1], k[2], k[3], int_shape_segs(shape), kLdsLimit, &tab);
+  const dd_status st = build_int_tables(p, k[0], k[1], k[2], k[3], int_shape_segs(shape), kLdsLimit, &tab, fill);
   if (st != DD_OK) return st;
   t.ns = k[0];
   t.dm_per_wave = k[1];
@@ -320,6 +323,7 @@ dd_status set_tiles(dd_plan &p, int direction, int shape, int order) {
   p.fwd = t;
   p.span_fwd = max_dm_block_span(p, t.waves * t.dm_per_wave);
   p.itab = std::move(tab);
+  p.gtab.use = false;
   return DD_OK;
 }
 
@@ -337,8 +341,8 @@ dd_status set_tiles(dd_plan &p, int direction, int shape, int order) {
 // MHz: 50.1 against 44.1 Tadds/s for the best staged shape, the phase-load
 // form; 4096 ch x 2^19 x 2048 DMs at 120-190 MHz: 50.0 against 25.3 for the
 // best staged shape; grid order 1 there against 46.2 for the grouped order).
-dd_status choose_forward_tiles(dd_plan &p) {
-  if (p.desc.dtype == DD_U4) return set_tiles(p, 0, kNumIntShapes + 1, kOrderXcdTiles);
+static dd_status choose_shapes(dd_plan &p) {
+  if (p.desc.dtype == DD_U4) return set_tiles(p, 0, kNumIntShapes + 1, kOrderXcdTiles, false);
   const int dirs = p.desc.dtype == DD_F32 ? 2 : 1;
   for (int dir = 0; dir < dirs; ++dir) {
     dd_status last = DD_ERR_RANGE;
@@ -346,7 +350,7 @@ dd_status choose_forward_tiles(dd_plan &p) {
       for (int i = 0; i < num_shapes(p); ++i) {
         const bool phase = p.desc.dtype == DD_U8 && int_shape_segs(i) > 0;
         if (phase != (pass == 0)) continue;
-        last = set_tiles(p, dir, i, kOrderDmGroups);
+        last = set_tiles(p, dir, i, kOrderDmGroups, false);
         // an 8-wave phase-load shape pays only when two of its workgroups share a CU
         if (last == DD_OK && phase && p.fwd.waves == 8 && 2 * p.fwd.lds_bytes > kLdsLimit) last = DD_ERR_RANGE;
         if (last == DD_OK || last == DD_ERR_NOMEM) break;
@@ -364,7 +368,7 @@ dd_status choose_forward_tiles(dd_plan &p) {
   // those four plans (staged shapes 16, 17, 18 and 5) 33.0-34.3 against 15.0-24.4 Tadds/s.
   const int direct = kNumIntShapes;
   if (p.desc.dtype == DD_U8 && !is_direct(p.fwd) && p.fwd.chan_block <= 4)
-    return set_tiles(p, 0, direct, p.fwd.chan_block <= 2 ? kOrderDmGroups : kOrderXcdTiles);
+    return set_tiles(p, 0, direct, p.fwd.chan_block <= 2 ? kOrderDmGroups : kOrderXcdTiles, false);
   // 16-bit plans: the 8-wave shape with 4 rows per wave and 4 channels per stage,
   // where two of its workgroups fit in a CU's LDS, so that one's barrier waits
   // overlap the other's adds: first in its phase-load form (the two copies loaded
@@ -376,27 +380,65 @@ dd_status choose_forward_tiles(dd_plan &p) {
   // staged shape was the 1-row, 16-wave raw ring: 17.0-17.8 against 14.6-15.1
   // Tadds/s), as does one with at most 2.
   if (p.desc.dtype == DD_U16 && !is_direct(p.fwd)) {
-    if (p.fwd.chan_block <= 2) return set_tiles(p, 0, direct, kOrderXcdTiles);
+    if (p.fwd.chan_block <= 2) return set_tiles(p, 0, direct, kOrderXcdTiles, false);
     const int keep_shape = p.fwd.shape, keep_order = p.fwd.order;
     bool moved = false;
     for (int want_phase = 1; want_phase >= 0; --want_phase)
       for (int i = 0; i < kNumIntShapes; ++i) {
         const int *k = kIntShapes[i];
         if (k[0] != 16 || k[1] != 4 || k[2] != 8 || k[3] != 4 || (k[4] > 0) != (want_phase == 1)) continue;
-        if (i == keep_shape) return moved ? set_tiles(p, 0, keep_shape, keep_order) : DD_OK;
-        const dd_status st = set_tiles(p, 0, i, kOrderDmGroups);
+        if (i == keep_shape) return moved ? set_tiles(p, 0, keep_shape, keep_order, false) : DD_OK;
+        const dd_status st = set_tiles(p, 0, i, kOrderDmGroups, false);
         if (st == DD_ERR_NOMEM) return st;
         if (st == DD_OK && 2 * p.fwd.lds_bytes <= kLdsLimit) return DD_OK;
         moved = moved || st == DD_OK;
         break;
       }
     if (moved) {
-      const dd_status st = set_tiles(p, 0, keep_shape, keep_order);
+      const dd_status st = set_tiles(p, 0, keep_shape, keep_order, false);
       if (st != DD_OK) return st;
     }
-    if (p.fwd.chan_block <= 4) return set_tiles(p, 0, direct, kOrderXcdTiles);
+    if (p.fwd.chan_block <= 4) return set_tiles(p, 0, direct, kOrderXcdTiles, false);
   }
   return DD_OK;
+}
+
+// Whether an integer plan's forward runs by group sums (fwd_group.hip) instead of
+// its shape's kernel: where the modelled time is smaller by a tenth (the model is
+// good to that; plans near the line run equally fast either way: 210 against 206 us
+// on one).  Both run in rounds of resident workgroups (256 CUs): group sums one per
+// CU, the other kernels two of 32 rows x 512 samples.  kModel: the group kernel's
+// measured time against its model (8192 ch x 2^20 x 4000 DMs 8-bit: 353 ms against 513;
+// 1024 ch x 101773 x 700: 1.09 against 1.48); rate: additions per CU clock of the other
+// kernels (8-bit 40.8 Tadds/s, 4-bit 50, 16-bit 28).  On the two plans above, 4-bit 8192
+// ch x 2^18 x 500 and 16-bit the same, group sums against the other kernels: 353 / 820,
+// 1.09 / 1.78, 13.1 / 22.4 and 21.7 / 37.7 ms; 128 ch x 32768 x 256 DMs of step 1 (28
+// patterns per 8 channels) stays: 42 against 36 us.
+static void choose_group_sums(dd_plan &p) {
+  if (p.desc.dtype == DD_F32) return;
+  const double kModel = 0.74, kCus = 256;
+  const int bits = p.desc.dtype == DD_U4 ? 4 : p.desc.dtype == DD_U16 ? 16 : 8;
+  const double rate = bits == 16 ? 46.0 : bits == 4 ? 80.0 : 64.0;
+  const int64_t tile = bits == 16 ? kGrpWin : 2 * kGrpWin;
+  const int64_t n_blk = (p.desc.n_dm + group_rows(bits) - 1) / group_rows(bits);
+  const double groups = ceil((double)n_blk * (double)((p.n_out + tile - 1) / tile) / kCus);
+  const double others = ceil((double)((p.desc.n_dm + 31) / 32) * (double)((p.n_out + 511) / 512) / (2 * kCus));
+  // the group kernel's rounds at its mean cost per block against the others' rounds
+  const double limit = 0.9 * others * (2.0 * 32 * 512) * p.desc.n_chan / rate / (groups * kModel) * (double)n_blk;
+  if (!build_group_tables(p.shift.data(), p.desc.n_dm, p.desc.n_chan, bits, p.in_pitch_bytes, &p.gtab, limit) ||
+      p.gtab.data.size() * 4 > table_bytes(p)) {
+    p.gtab = GroupTables();
+    return;
+  }
+  p.gtab.use = true;
+}
+
+dd_status choose_forward_tiles(dd_plan &p) {
+  dd_status st = choose_shapes(p);
+  if (st != DD_OK) return st;
+  choose_group_sums(p);
+  if (p.desc.dtype != DD_F32 && !p.gtab.use) st = set_tiles(p, 0, p.fwd.shape, p.fwd.order);  // fill its tables
+  return st;
 }
 
 static size_t up256(size_t v) { return (v + 255) / 256 * 256; }
@@ -406,7 +448,7 @@ static size_t up256(size_t v) { return (v + 255) / 256 * 256; }
 TableLayout table_layout(const dd_plan &p) {
   TableLayout L;
   if (p.desc.dtype != DD_F32) {
-    if (!is_direct(p.fwd)) L.int_sbase = up256(p.itab.offs.size() * sizeof(uint32_t));
+    if (!is_direct(p.fwd)) L.int_sbase = up256(p.itab.offs_words * sizeof(uint32_t));
     return L;
   }
   size_t off = 0;
@@ -423,7 +465,7 @@ TableLayout table_layout(const dd_plan &p) {
 size_t table_bytes(const dd_plan &p) {
   if (p.desc.dtype != DD_F32 && is_direct(p.fwd)) return up256(p.shift.size() * sizeof(int32_t));
   if (p.desc.dtype != DD_F32)
-    return up256(p.itab.offs.size() * sizeof(uint32_t)) + up256(p.itab.sbase.size() * sizeof(int32_t));
+    return up256(p.itab.offs_words * sizeof(uint32_t)) + up256(p.itab.sbase_words * sizeof(int32_t));
   return up256(p.ftab_fwd.offs.size() * 2) + up256(p.ftab_fwd.sbase.size() * 4) + up256(p.ftab_adj.offs.size() * 2) +
          up256(p.ftab_adj.sbase.size() * 4);
 }

@@ -126,8 +126,8 @@ dd_status range_forward(const dd_survey &s, int r, const void *d_in, float *d_ou
   if (!s.split16 || slot < 0) return dd_execute(s.plans[r], range_input(s, r, d_in), d_out, out_pitch, stream);
   const uint8_t *lo = s.ws + s.slot_off[slot];
   const dd_plan &p = *s.plans[r];
-  int e = launch_forward_int(p, p.d_tables, lo, d_out, out_pitch, stream, 0, kOutRawTotals);
-  if (!e) e = launch_forward_int(p, p.d_tables, lo + s.split_off[slot], d_out, out_pitch, stream, 0, kOutCombineHigh);
+  int e = launch_forward(p, p.d_tables, lo, d_out, out_pitch, stream, 0, kOutRawTotals);
+  if (!e) e = launch_forward(p, p.d_tables, lo + s.split_off[slot], d_out, out_pitch, stream, 0, kOutCombineHigh);
   if (e) return hip_error(e, "forward launch");
   return DD_OK;
 }

@@ -84,7 +84,12 @@ void apply_tune_cache(dd_plan &p) {
   }
   fclose(f);
   for (int dir = 0; dir < dirs; ++dir)
-    if (want_shape[dir] >= 0) set_tiles(p, dir, want_shape[dir], want_order[dir]);  // keeps the default on failure
+    if (want_shape[dir] >= 0) {
+      // the default choice keeps its group sums; another one is set (the default stays on failure)
+      int shape, order;
+      current_tiles(p, dir, &shape, &order);
+      if (want_shape[dir] != shape || want_order[dir] != order) set_tiles(p, dir, want_shape[dir], want_order[dir]);
+    }
 }
 
 static void append_tune_cache(const dd_plan &p, int dir, int shape, int order, double ms) {
@@ -150,6 +155,7 @@ dd_status dd_plan_autotune(dd_plan *p, int32_t dir, const void *src, float *dst,
 
   int orig_shape, orig_order;
   current_tiles(*p, dir, &orig_shape, &orig_order);
+  const bool orig_group = dir == 0 && p->gtab.use;  // set_tiles leaves the group tables, not their use
   p->bound = false;
   const int64_t out_len = dir == 0 ? p->n_out : p->desc.n_samp;
   // Timed span: an eighth of the job (so that the input streamed per output
@@ -172,7 +178,7 @@ dd_status dd_plan_autotune(dd_plan *p, int32_t dir, const void *src, float *dst,
   auto run = [&]() -> int {
     if (dir == 1) return launch_adjoint(*p, p->d_tables, (const float *)src, pitch, dst, stream, lim);
     if (p->desc.dtype == DD_F32) return launch_forward_f32(*p, p->d_tables, src, dst, pitch, stream, lim);
-    return launch_forward_int(*p, p->d_tables, src, dst, pitch, stream, lim);
+    return launch_forward(*p, p->d_tables, src, dst, pitch, stream, lim);
   };
   // Upload the current tables, warm up, then time two launches.
   auto time_current = [&](double *ms) -> dd_status {
@@ -223,6 +229,7 @@ dd_status dd_plan_autotune(dd_plan *p, int32_t dir, const void *src, float *dst,
     const std::string msg = dd_last_error();
     (void)hipStreamSynchronize(st);  // no upload may still read host tables that set_tiles replaces
     set_tiles(*p, dir, orig_shape, orig_order);
+    if (orig_group) p->gtab.use = true;
     p->bound = false;
     return fail(status, msg);
   }
@@ -235,6 +242,7 @@ dd_status dd_plan_autotune(dd_plan *p, int32_t dir, const void *src, float *dst,
     best_ms = default_ms;
   }
   status = set_tiles(*p, dir, best_shape, best_order);
+  if (status == DD_OK && orig_group && best_shape == orig_shape && best_order == orig_order) p->gtab.use = true;
   if (status == DD_OK) status = upload_tables(*p, ws, stream);
   if (status == DD_OK) {
     const hipError_t se = hipStreamSynchronize(st);
