@@ -25,6 +25,7 @@ namespace {
 // of resident workgroups are kept apart.)
 struct BatchGroup {
   int shape = 0;                // plan shape index (staged below kNumIntShapes, direct-read above)
+  bool sums = false;            // group sums instead of the shape's kernel
   int per_cu = 0;               // workgroups per CU its beams' LDS allows (0: direct-read, no LDS)
   int lds_bytes = 0;            // largest of its beams' LDS needs
   std::vector<int> beams;       // original beam indices, in decreasing per-item cost
@@ -38,7 +39,8 @@ struct dd_batch {
   std::vector<const dd_plan *> plans;
   int dtype = 0;
   std::vector<int> shape;         // per beam (original index): its shape
-  std::vector<IntTables> tables;  // per beam (original index), for its shape (empty for direct-read)
+  std::vector<char> sums;         // per beam: it runs by group sums (beams at their default shape)
+  std::vector<IntTables> tables;  // per beam (original index), for its shape (empty for direct-read and group sums)
   std::vector<int> order;         // beams in decreasing per-item cost
   std::vector<BatchGroup> groups;
   std::vector<BeamDesc> descs;    // group after group, each group's beams in cost order
@@ -82,13 +84,22 @@ static void int_table_bytes(const dd_plan &p, const int *k, size_t *offs, size_t
 static size_t counters_bytes() { return (size_t)kMaxGroups * 256; }
 static size_t descs_offset() { return counters_bytes(); }
 
-// Give beam i shape shapes[i], for every beam: tables, groups, work items.
-// DD_ERR_RANGE (batch unchanged) if a beam cannot be staged with its shape.
-static dd_status batch_assign(dd_batch *b, const std::vector<int> &shapes) {
+// An assignment of kernels: a shape per beam, and which beams run by group sums.
+struct Assignment {
+  std::vector<int> shapes;
+  std::vector<char> sums;
+  bool operator==(const Assignment &o) const { return shapes == o.shapes && sums == o.sums; }
+};
+
+// Give beam i shape shapes[i] (or group sums), for every beam: tables, groups, work
+// items.  DD_ERR_RANGE (batch unchanged) if a beam cannot be staged with its shape.
+static dd_status batch_assign(dd_batch *b, const Assignment &as) {
+  const std::vector<int> &shapes = as.shapes;
   const int n = (int)b->plans.size();
   std::vector<IntTables> tabs(n);
   for (int i = 0; i < n; ++i) {
     const dd_plan &p = *b->plans[i];
+    if (as.sums[i]) continue;  // reads the plan's group-sum table
     if (direct_shape(shapes[i])) {  // reads the plan's shift table; its descriptors stay inside the row pitch
       const int bits = p.desc.dtype == DD_U4 ? 4 : p.desc.dtype == DD_U16 ? 16 : 8;
       if ((int64_t)p.max_shift * bits / 8 >= p.in_pitch_bytes) return fail(DD_ERR_RANGE, "delay exceeds the row pitch");
@@ -102,13 +113,16 @@ static dd_status batch_assign(dd_batch *b, const std::vector<int> &shapes) {
   for (int q = 0; q < n; ++q) {  // groups in order of their costliest beam
     const int i = b->order[q];
     // the staged kernel keeps 64 bytes of LDS of its own
-    const int per_cu = direct_shape(shapes[i]) ? 0 : (kBatchLdsLimit + 64) / (tabs[i].lds_bytes + 64);
-    auto g = std::find_if(groups.begin(), groups.end(),
-                          [&](const BatchGroup &x) { return x.shape == shapes[i] && x.per_cu == per_cu; });
+    const bool sums = as.sums[i];
+    const int per_cu = sums || direct_shape(shapes[i]) ? 0 : (kBatchLdsLimit + 64) / (tabs[i].lds_bytes + 64);
+    auto g = std::find_if(groups.begin(), groups.end(), [&](const BatchGroup &x) {
+      return x.sums == sums && (sums || (x.shape == shapes[i] && x.per_cu == per_cu));
+    });
     if (g == groups.end()) {
       groups.emplace_back();
       g = groups.end() - 1;
       g->shape = shapes[i];
+      g->sums = sums;
       g->per_cu = per_cu;
     }
     g->beams.push_back(i);
@@ -119,7 +133,11 @@ static dd_status batch_assign(dd_batch *b, const std::vector<int> &shapes) {
   size_t q = 0;
   for (BatchGroup &g : groups) {
     const int *k = int_shape(g.shape);
-    const int dm_tile = k[1] * k[2], t_tile = direct_shape(g.shape) ? direct_tile_samples(b->dtype) : 64 * k[0];
+    const int bits = b->dtype == DD_U4 ? 4 : b->dtype == DD_U16 ? 16 : 8;
+    const int dm_tile = g.sums ? group_rows(bits) : k[1] * k[2];
+    const int t_tile = g.sums                  ? group_tile_samples(b->dtype)
+                       : direct_shape(g.shape) ? direct_tile_samples(b->dtype)
+                                               : 64 * k[0];
     g.desc_first = q;
     long long items = 0;
     for (int i : g.beams) {
@@ -144,6 +162,7 @@ static dd_status batch_assign(dd_batch *b, const std::vector<int> &shapes) {
   b->groups = std::move(groups);
   b->descs = std::move(descs);
   b->shape = shapes;
+  b->sums = as.sums;
   b->bound = false;
   return DD_OK;
 }
@@ -167,6 +186,17 @@ static int default_shape(const dd_plan &p) {
       if (build_int_tables(p, k[0], k[1], k[2], k[3], k[4], kBatchLdsLimit, &t, false) == DD_OK) return s;
     }
   return kNumIntShapes + (p.desc.dtype == DD_U4 ? 1 : 0);
+}
+
+// Every beam at its plan's default: group sums where the plan holds tables for
+// them that pay in a batch, and its tiles were not chosen explicitly.
+static Assignment default_assignment(const dd_batch &b) {
+  Assignment as;
+  for (const dd_plan *p : b.plans) {
+    as.shapes.push_back(default_shape(*p));
+    as.sums.push_back(p->gtab.batch);
+  }
+  return as;
 }
 
 static void fill_tiles(int s, dd_tiles *t) {
@@ -220,9 +250,7 @@ dd_status dd_batch_create(const dd_plan *const *plans, int32_t n, dd_batch **out
     off += sbb;
   }
   b->ws_bytes = off;
-  std::vector<int> shapes(n);
-  for (int i = 0; i < n; ++i) shapes[i] = default_shape(*b->plans[i]);
-  const dd_status st = batch_assign(b, shapes);
+  const dd_status st = batch_assign(b, default_assignment(*b));
   if (st != DD_OK) { delete b; return st; }
   *out = b;
   return DD_OK;
@@ -262,6 +290,11 @@ dd_status dd_batch_bind(dd_batch *b, const void *const *d_in, float *const *d_ou
   hipStream_t st = (hipStream_t)stream;
   e = hipMemcpyAsync(base + descs_offset(), b->descs.data(), sizeof(BeamDesc) * n, hipMemcpyHostToDevice, st);
   for (int i = 0; i < n && e == hipSuccess; ++i) {
+    if (b->sums[i]) {
+      const std::vector<uint32_t> &t = b->plans[i]->gtab.data;
+      e = hipMemcpyAsync(base + b->table_offs[i], t.data(), t.size() * 4, hipMemcpyHostToDevice, st);
+      continue;
+    }
     if (direct_shape(b->shape[i])) {
       const std::vector<int32_t> &sh = b->plans[i]->shift;
       e = hipMemcpyAsync(base + b->table_offs[i], sh.data(), sh.size() * 4, hipMemcpyHostToDevice, st);
@@ -286,8 +319,9 @@ dd_status dd_batch_bind(dd_batch *b, const void *const *d_in, float *const *d_ou
     const BatchGroup &g = b->groups[gi];
     const int *k = int_shape(g.shape);
     BatchLaunch L = {};
-    const int le = direct_shape(g.shape) ? batch_direct_kernels(k[1], k[2], b->dtype, &L)
-                                         : batch_kernels(k[0], k[1], k[2], k[3], k[4], b->dtype, g.lds_bytes, &L);
+    const int le = g.sums                  ? batch_group_kernels(b->dtype, &L)
+                   : direct_shape(g.shape) ? batch_direct_kernels(k[1], k[2], b->dtype, &L)
+                                           : batch_kernels(k[0], k[1], k[2], k[3], k[4], b->dtype, g.lds_bytes, &L);
     if (le) {
       release_graph(b);
       return fail(DD_ERR_HIP, std::string("batch kernel setup: ") + hipGetErrorString((hipError_t)le));
@@ -361,7 +395,7 @@ dd_status dd_batch_get_beam_tiles(const dd_batch *b, int32_t beam, dd_tiles *t) 
 dd_status dd_batch_set_tiles(dd_batch *b, int32_t shape) {
   if (!b) return fail(DD_ERR_ARG, "null batch");
   if (shape < 0 || shape >= num_batch_shapes()) return fail(DD_ERR_ARG, "no such tile shape");
-  const dd_status st = batch_assign(b, std::vector<int>(b->plans.size(), shape));
+  const dd_status st = batch_assign(b, {std::vector<int>(b->plans.size(), shape), std::vector<char>(b->plans.size(), 0)});
   if (st == DD_ERR_RANGE) return fail(st, "a beam's delay spread does not fit this shape");
   return st;
 }
@@ -369,7 +403,7 @@ dd_status dd_batch_set_tiles(dd_batch *b, int32_t shape) {
 dd_status dd_batch_autotune(dd_batch *b, const void *const *d_in, float *const *d_out, const int64_t *out_pitch,
                             void *ws, size_t bytes, void *stream, dd_tune_report *rep) {
   if (!b) return fail(DD_ERR_ARG, "null batch");
-  const std::vector<int> orig = b->shape;
+  const Assignment orig = {b->shape, b->sums};
   hipStream_t st = (hipStream_t)stream;
   hipEvent_t e0 = nullptr, e1 = nullptr;
   hipError_t he = hipEventCreate(&e0);
@@ -379,8 +413,8 @@ dd_status dd_batch_autotune(dd_batch *b, const void *const *d_in, float *const *
     return hip_error(he, "hipEventCreate");
   }
   // Bind an assignment, replay once to warm up, then time one replay.
-  auto time_assign = [&](const std::vector<int> &shapes, double *ms) -> dd_status {
-    dd_status r = batch_assign(b, shapes);
+  auto time_assign = [&](const Assignment &as, double *ms) -> dd_status {
+    dd_status r = batch_assign(b, as);
     if (r != DD_OK) return r;
     r = dd_batch_bind(b, d_in, d_out, out_pitch, ws, bytes, stream);
     if (r != DD_OK) return r;
@@ -395,19 +429,20 @@ dd_status dd_batch_autotune(dd_batch *b, const void *const *d_in, float *const *
     *ms = t;
     return DD_OK;
   };
-  // Candidates: the current assignment, every beam at its default shape, and
+  // Candidates: the current assignment, every beam at its default (and there without group sums), and
   // every staged shape with at least 32 DM rows per workgroup, and every
   // direct-read shape, shared by all beams (smaller staged ones only pay where
   // a beam's default had to fall back to them).
-  std::vector<std::vector<int>> cands;
+  const std::vector<char> none(b->plans.size(), 0);
+  std::vector<Assignment> cands;
   cands.push_back(orig);
-  std::vector<int> defaults(orig.size());
-  for (size_t i = 0; i < orig.size(); ++i) defaults[i] = default_shape(*b->plans[i]);
-  if (defaults != orig) cands.push_back(defaults);
+  const Assignment defaults = default_assignment(*b);
+  if (!(defaults == orig)) cands.push_back(defaults);
+  if (defaults.sums != none) cands.push_back({defaults.shapes, none});
   for (int s = 0; s < num_batch_shapes(); ++s) {
     if (!direct_shape(s) && kIntShapes[s][1] * kIntShapes[s][2] < 32) continue;
-    std::vector<int> all(orig.size(), s);
-    if (all != orig && all != defaults) cands.push_back(all);
+    const Assignment all = {std::vector<int>(b->plans.size(), s), none};
+    if (!(all == orig) && !(all == defaults)) cands.push_back(all);
   }
   double default_ms = 0.0, best_ms = 0.0;
   size_t best = 0;

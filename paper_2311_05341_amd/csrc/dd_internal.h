@@ -101,7 +101,8 @@ dd_status choose_forward_tiles(dd_plan &p);
 // Rebuild the tables of one direction (0 forward, 1 adjoint) for compiled
 // shape `shape` and TileOrder `order`.  DD_ERR_RANGE if the shape cannot hold
 // the plan's delay spread; the plan is unchanged then.
-// An integer plan's forward then runs that shape's kernel (gtab.use is cleared).
+// An integer plan's forward (and its beam in a batch) then runs that shape's kernel
+// (gtab.use and gtab.batch are cleared).
 // With fill false an integer plan's staged tables are only sized.
 dd_status set_tiles(dd_plan &p, int direction, int shape, int order, bool fill = true);
 int num_shapes(const dd_plan &p);
@@ -206,6 +207,10 @@ int batch_kernels(int ns, int dm_per_wave, int waves, int chan_block, int segs, 
 // dm_per_wave rows, and a beam's table is its plain int32 shift table.
 int batch_direct_kernels(int dm_per_wave, int waves, int dtype, BatchLaunch *out);
 int direct_tile_samples(int dtype);
+// The same for group sums (fwd_group.hip): work items of group_tile_samples(dtype)
+// outputs by group_rows rows; a beam's table is its plan's group-sum table.
+int batch_group_kernels(int dtype, BatchLaunch *out);
+int group_tile_samples(int dtype);
 
 // Time binning (bin.hip): bytes per output element, and the launch.  The
 // caller has validated every argument (sizes, alignment, factor 1..256).

@@ -419,26 +419,27 @@ bool build_group_tables(const int32_t *shift, int n_dm, int n_chan, int bits, in
     }
     if (bad) return false;
     size_t recs = 0, ops = kGrpBlockWords, sums = 0;
-    t->lo = 0;  // the idle operation block loads the tile's own samples of channel 0
-    t->hi = kGrpChunk + 12;
+    t->head.lo = 0;  // the idle operation block loads the tile's own samples of channel 0
+    t->head.hi = kGrpChunk + 12;
     for (const Block &b : blocks) {
       if (!b.ok) return false;
       for (const auto &r : b.rec) recs += r.size();
       sums += b.sum.size();
       ops += b.ops.size();
-      t->lo = std::min(t->lo, b.lo);
-      t->hi = std::max(t->hi, b.hi);
+      t->head.lo = std::min(t->head.lo, b.lo);
+      t->head.hi = std::max(t->head.hi, b.hi);
       t->cost += b.cost;
       t->lds_bytes = std::max(t->lds_bytes, b.lds);
     }
     if (max_cost > 0 && t->cost > max_cost) return false;
     t->n_blk = n_blk;
-    t->rec_off = ((int64_t)n_blk * (int64_t)(sizeof(GroupBlock) / 4) + 63) / 64 * 64;
-    t->op_off = (t->rec_off + (int64_t)recs + 4 * kGrpRecWords + 63) / 64 * 64;  // records are loaded ahead
-    t->sum_off = (t->op_off + (int64_t)ops + 63) / 64 * 64;
-    const int64_t total = t->sum_off + (int64_t)sums + 64;  // a wave loads 64 entries
+    t->head.rec_off = (kGrpHeadWords + (int64_t)n_blk * (int64_t)(sizeof(GroupBlock) / 4) + 63) / 64 * 64;
+    t->head.op_off = (t->head.rec_off + (int64_t)recs + 4 * kGrpRecWords + 63) / 64 * 64;  // records are loaded ahead
+    t->head.sum_off = (t->head.op_off + (int64_t)ops + 63) / 64 * 64;
+    const int64_t total = t->head.sum_off + (int64_t)sums + 64;  // a wave loads 64 entries
     if (total >= ((int64_t)1 << 31)) return false;
     t->data.assign((size_t)total, 0);
+    memcpy(t->data.data(), &t->head, sizeof t->head);
     size_t ro = 0, oo = kGrpBlockWords, so = 0;
     for (int b = 0; b < n_blk; ++b) {
       GroupBlock g = {};
@@ -448,17 +449,17 @@ bool build_group_tables(const int32_t *shift, int n_dm, int n_chan, int bits, in
         for (size_t i = 0; i < r.size(); i += kGrpRecWords)
           if (r[i]) r[i] += op0;
         g.rec_first[k] = (uint32_t)(ro / kGrpRecWords);
-        std::copy(r.begin(), r.end(), t->data.begin() + t->rec_off + ro);
+        std::copy(r.begin(), r.end(), t->data.begin() + t->head.rec_off + ro);
         ro += r.size();
       }
-      std::copy(blocks[b].ops.begin(), blocks[b].ops.end(), t->data.begin() + t->op_off + oo);
+      std::copy(blocks[b].ops.begin(), blocks[b].ops.end(), t->data.begin() + t->head.op_off + oo);
       oo += blocks[b].ops.size();
       g.sum_first = (uint32_t)so;
       g.n_steps = (uint32_t)blocks[b].n_steps;
       g.n_steps = (uint32_t)blocks[b].n_steps;
-      std::copy(blocks[b].sum.begin(), blocks[b].sum.end(), t->data.begin() + t->sum_off + so);
+      std::copy(blocks[b].sum.begin(), blocks[b].sum.end(), t->data.begin() + t->head.sum_off + so);
       so += blocks[b].sum.size();
-      memcpy(&t->data[(size_t)b * (sizeof g / 4)], &g, sizeof g);
+      memcpy(&t->data[kGrpHeadWords + (size_t)b * (sizeof g / 4)], &g, sizeof g);
       blocks[b] = Block();
     }
   } catch (const std::bad_alloc &) {

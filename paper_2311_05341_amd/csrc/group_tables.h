@@ -72,13 +72,21 @@ struct GroupBlock {
   uint32_t n_steps;
 };
 
+// The head of the table (16 words), followed by the GroupBlocks.
+struct GroupHead {
+  int64_t rec_off, op_off, sum_off;  // word offsets of the records, operation blocks and sum entries
+  int64_t lo, hi;                    // samples read relative to a tile's start: [lo, hi)
+  int64_t spare[3];
+};
+constexpr int kGrpHeadWords = sizeof(GroupHead) / 4;
+
 struct GroupTables {
   bool use = false;            // the plan runs the group-sum kernel
+  bool batch = false;          // its beam of a batch does
   int n_blk = 0;
-  std::vector<uint32_t> data;  // [n_blk] GroupBlock, records, operation blocks, sum entries
-  int64_t rec_off = 0, op_off = 0, sum_off = 0;  // word offsets in `data`
+  std::vector<uint32_t> data;  // GroupHead, [n_blk] GroupBlock, records, operation blocks, sum entries
+  GroupHead head = {};
   int lds_bytes = 0;           // of both sets
-  int64_t lo = 0, hi = 0;      // samples read relative to a tile's start: [lo, hi)
   double cost = 0;             // modelled CU clocks for all blocks, per time tile
 };
 

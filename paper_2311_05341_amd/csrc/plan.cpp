@@ -308,7 +308,7 @@ dd_status set_tiles(dd_plan &p, int direction, int shape, int order, bool fill) 
     p.fwd = t;
     p.span_fwd = max_dm_block_span(p, t.waves * t.dm_per_wave);
     p.itab = IntTables();
-    p.gtab.use = false;
+    p.gtab.use = p.gtab.batch = false;
     return DD_OK;
   }
   const dd_status st = build_int_tables(p, k[0], k[1], k[2], k[3], int_shape_segs(shape), kLdsLimit, &tab, fill);
@@ -323,7 +323,7 @@ dd_status set_tiles(dd_plan &p, int direction, int shape, int order, bool fill) 
   p.fwd = t;
   p.span_fwd = max_dm_block_span(p, t.waves * t.dm_per_wave);
   p.itab = std::move(tab);
-  p.gtab.use = false;
+  p.gtab.use = p.gtab.batch = false;
   return DD_OK;
 }
 
@@ -410,7 +410,8 @@ static dd_status choose_shapes(dd_plan &p) {
 // CU, the other kernels two of 32 rows x 512 samples.  kModel: the group kernel's
 // measured time against its model (8192 ch x 2^20 x 4000 DMs 8-bit: 353 ms against 513;
 // 1024 ch x 101773 x 700: 1.09 against 1.48); rate: additions per CU clock of the other
-// kernels (8-bit 40.8 Tadds/s, 4-bit 50, 16-bit 28).  On the two plans above, 4-bit 8192
+// kernels (8-bit 40.8 Tadds/s on the 8-wave staged shape, 33-34 on the others; 4-bit 50;
+// 16-bit 30 and 17).  On the two plans above, 4-bit 8192
 // ch x 2^18 x 500 and 16-bit the same, group sums against the other kernels: 353 / 820,
 // 1.09 / 1.78, 13.1 / 22.4 and 21.7 / 37.7 ms; 128 ch x 32768 x 256 DMs of step 1 (28
 // patterns per 8 channels) stays: 42 against 36 us.
@@ -418,26 +419,36 @@ static void choose_group_sums(dd_plan &p) {
   if (p.desc.dtype == DD_F32) return;
   const double kModel = 0.74, kCus = 256;
   const int bits = p.desc.dtype == DD_U4 ? 4 : p.desc.dtype == DD_U16 ? 16 : 8;
-  const double rate = bits == 16 ? 46.0 : bits == 4 ? 80.0 : 64.0;
+  const bool best_staged = !is_direct(p.fwd) && p.fwd.waves == 8;
+  const double rate = bits == 4 ? 80.0 : bits == 16 ? (best_staged ? 47.0 : 27.0) : best_staged ? 64.0 : 53.0;
   const int64_t tile = bits == 16 ? kGrpWin : 2 * kGrpWin;
   const int64_t n_blk = (p.desc.n_dm + group_rows(bits) - 1) / group_rows(bits);
   const double groups = ceil((double)n_blk * (double)((p.n_out + tile - 1) / tile) / kCus);
   const double others = ceil((double)((p.desc.n_dm + 31) / 32) * (double)((p.n_out + 511) / 512) / (2 * kCus));
-  // the group kernel's rounds at its mean cost per block against the others' rounds
-  const double limit = 0.9 * others * (2.0 * 32 * 512) * p.desc.n_chan / rate / (groups * kModel) * (double)n_blk;
-  if (!build_group_tables(p.shift.data(), p.desc.n_dm, p.desc.n_chan, bits, p.in_pitch_bytes, &p.gtab, limit) ||
+  // the group kernel's rounds at its mean cost per block against the others' rounds, and
+  // (a beam of a batch) all its tiles against the plan's additions
+  const double round_limit = 0.9 * others * (2.0 * 32 * 512) * p.desc.n_chan / rate / (groups * kModel) * (double)n_blk;
+  const double batch_limit = 0.9 * (double)p.desc.n_dm * (double)p.n_out * p.desc.n_chan / rate / kModel /
+                             (double)((p.n_out + tile - 1) / tile);
+  if (!build_group_tables(p.shift.data(), p.desc.n_dm, p.desc.n_chan, bits, p.in_pitch_bytes, &p.gtab,
+                          std::max(round_limit, batch_limit)) ||
       p.gtab.data.size() * 4 > table_bytes(p)) {
     p.gtab = GroupTables();
     return;
   }
-  p.gtab.use = true;
+  p.gtab.use = p.gtab.cost <= round_limit;
+  p.gtab.batch = p.gtab.cost <= batch_limit;
 }
 
 dd_status choose_forward_tiles(dd_plan &p) {
   dd_status st = choose_shapes(p);
   if (st != DD_OK) return st;
   choose_group_sums(p);
-  if (p.desc.dtype != DD_F32 && !p.gtab.use) st = set_tiles(p, 0, p.fwd.shape, p.fwd.order);  // fill its tables
+  if (p.desc.dtype != DD_F32 && !p.gtab.use) {
+    const bool batch = p.gtab.batch;
+    st = set_tiles(p, 0, p.fwd.shape, p.fwd.order);  // fill its tables
+    p.gtab.batch = batch;
+  }
   return st;
 }
 

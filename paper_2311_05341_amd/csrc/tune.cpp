@@ -155,7 +155,7 @@ dd_status dd_plan_autotune(dd_plan *p, int32_t dir, const void *src, float *dst,
 
   int orig_shape, orig_order;
   current_tiles(*p, dir, &orig_shape, &orig_order);
-  const bool orig_group = dir == 0 && p->gtab.use;  // set_tiles leaves the group tables, not their use
+  const bool orig_use = p->gtab.use, orig_batch = p->gtab.batch;  // set_tiles leaves the group tables, not their use
   p->bound = false;
   const int64_t out_len = dir == 0 ? p->n_out : p->desc.n_samp;
   // Timed span: an eighth of the job (so that the input streamed per output
@@ -229,7 +229,8 @@ dd_status dd_plan_autotune(dd_plan *p, int32_t dir, const void *src, float *dst,
     const std::string msg = dd_last_error();
     (void)hipStreamSynchronize(st);  // no upload may still read host tables that set_tiles replaces
     set_tiles(*p, dir, orig_shape, orig_order);
-    if (orig_group) p->gtab.use = true;
+    p->gtab.use = orig_use;
+    p->gtab.batch = orig_batch;
     p->bound = false;
     return fail(status, msg);
   }
@@ -242,7 +243,10 @@ dd_status dd_plan_autotune(dd_plan *p, int32_t dir, const void *src, float *dst,
     best_ms = default_ms;
   }
   status = set_tiles(*p, dir, best_shape, best_order);
-  if (status == DD_OK && orig_group && best_shape == orig_shape && best_order == orig_order) p->gtab.use = true;
+  if (status == DD_OK && best_shape == orig_shape && best_order == orig_order) {
+    p->gtab.use = orig_use;
+    p->gtab.batch = orig_batch;
+  }
   if (status == DD_OK) status = upload_tables(*p, ws, stream);
   if (status == DD_OK) {
     const hipError_t se = hipStreamSynchronize(st);

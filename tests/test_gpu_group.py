@@ -98,3 +98,30 @@ def test_replayed_graph_and_side_stream(dd):
         assert np.array_equal(out[:, : plan.n_out].cpu().numpy(), want)
         if k == 0:
             assert np.array_equal(eager.cpu().numpy(), want)
+
+
+@pytest.mark.parametrize("dtype", ["u8", "u4", "u16"])
+def test_batch_of_group_sum_and_other_beams(dd, dtype):
+    """Beams on group sums next to one on its explicitly chosen shape and one whose delays spread too
+    wide for group sums: every beam equals the oracle, on every replay."""
+    sizes = [(512, 32768, 96, 0.25), (300, 9000, 40, 0.5), (1024, 20000, 33, 0.25), (64, 16384, 64, 30.0)]
+    plans, xs, want = [], [], []
+    for k, (n_chan, n_samp, n_dm, step) in enumerate(sizes):
+        cfg = dict(dtype=dtype, n_chan=n_chan, n_samp=n_samp, f_high=1500.0, chan_bw=300.0 / n_chan, t_samp=64e-6,
+                   dm_start=0.0, dm_step=step if k < 3 else 0.7 * step, n_dm=n_dm if k < 3 else 10)
+        s = oracle_table(cfg)
+        x = _input(dtype, n_chan, n_samp, 20 + k)
+        plans.append(plan_for(dd, cfg, in_pitch_bytes=x.strides[0]))
+        xs.append(torch.from_numpy(x).cuda())
+        want.append(oracle.forward(x, dtype, n_samp, s))
+    t = plans[1].tiles(0)
+    plans[1].set_tiles(0, t["shape"], t["order"])
+    batch = dd.Batch(plans, xs)
+    for _ in range(3):
+        for o in batch.outputs:
+            o.fill_(-1.0)
+        for got, w in zip(batch.run(), want):
+            assert np.array_equal(got[:, : w.shape[1]].cpu().numpy(), w)
+    batch.set_tiles(plans[0].n_shapes - 2)  # one shape for every beam: no group sums
+    for got, w in zip(batch.run(), want):
+        assert np.array_equal(got[:, : w.shape[1]].cpu().numpy(), w)

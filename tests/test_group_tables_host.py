@@ -37,9 +37,10 @@ int main(int argc, char **argv) {
   if (!build_group_tables(sh.data(), n_dm, n_chan, bits, pitch, &t)) { printf("refused\n"); return 0; }
   CHECK(t.lds_bytes <= 2 * kGrpSetBytes && 2 * kGrpSetBytes + kGrpZeroBytes + kGrpTrashBytes <= 160 * 1024);
   const uint32_t *D = t.data.data();
+  CHECK(!memcmp(D, &t.head, sizeof t.head));
   const int64_t total = (int64_t)t.data.size();
   for (int b = 0; b < t.n_blk; ++b) {
-    const GroupBlock *gb = (const GroupBlock *)D + b;
+    const GroupBlock *gb = (const GroupBlock *)(D + kGrpHeadWords) + b;
     const int halves = packed_max ? 2 : 1;
     std::vector<int64_t> lds[2];
     const uint32_t zero = 2 * kGrpSetBytes;
@@ -53,8 +54,8 @@ int main(int argc, char **argv) {
         std::vector<int64_t> P[2], S[2];
         int phase = -1;
         for (bool last = false; !last;) {
-          const int64_t ro = t.rec_off + ((int64_t)gb->rec_first[wave] + pos[wave]++) * kGrpRecWords;
-          CHECK(ro + 4 * kGrpRecWords <= t.op_off);  // the kernel loads three records ahead
+          const int64_t ro = t.head.rec_off + ((int64_t)gb->rec_first[wave] + pos[wave]++) * kGrpRecWords;
+          CHECK(ro + 4 * kGrpRecWords <= t.head.op_off);  // the kernel loads three records ahead
           const uint32_t *r = D + ro;
           last = (r[1] & kRecLast) != 0;
           const int lanes = (int)(r[1] >> 8) & 255, k0 = (int)(r[1] >> 16), n = 4 * lanes;
@@ -62,8 +63,8 @@ int main(int argc, char **argv) {
           if (r[1] & kRecStart)
             for (int h = 0; h < halves; ++h) P[h].assign(n, 0), S[h].assign(n, 0);
           uint32_t slot = r[2];
-          const int64_t oo = t.op_off + (int64_t)r[0] * kGrpBlockWords;
-          CHECK(oo + kGrpBlockWords <= t.sum_off);
+          const int64_t oo = t.head.op_off + (int64_t)r[0] * kGrpBlockWords;
+          CHECK(oo + kGrpBlockWords <= t.head.sum_off);
           const uint32_t *o = D + oo;
           const int64_t base = (int64_t)((uint64_t)o[1] << 32 | o[0]);
           for (int q = 0; q < kGrpOps; ++q) {
@@ -73,7 +74,7 @@ int main(int argc, char **argv) {
             off -= c * pitch;
             const int64_t s = off * 8 / bits + (w & 3);
             CHECK(off % (bits == 4 ? 2 : 4) == 0 && (bits != 16 || !(w & 2)));
-            CHECK(c >= 0 && c < n_chan && off * 8 / bits >= t.lo && s + k0 + kGrpChunk + 8 <= t.hi);
+            CHECK(c >= 0 && c < n_chan && off * 8 / bits >= t.head.lo && s + k0 + kGrpChunk + 8 <= t.head.hi);
             const bool move = (w & kOpMove) != 0;
             if (!(w & (kOpMove | kOpAdd))) { CHECK(!(w & kOpWrite)); continue; }
             CHECK(lanes > 0 && (int)P[0].size() == n && move == !(w & kOpAdd));
@@ -110,7 +111,7 @@ int main(int argc, char **argv) {
         CHECK(pair < kGrpStepPairs);
         uint32_t marks = 0;
         for (int d = 0; d < kGrpRows; ++d) {
-          const int64_t eo = t.sum_off + gb->sum_first + ((int64_t)step * kGrpWaves + d / R) * kSumWords + pair * 2 * R;
+          const int64_t eo = t.head.sum_off + gb->sum_first + ((int64_t)step * kGrpWaves + d / R) * kSumWords + pair * 2 * R;
           CHECK(eo - pair * 2 * R + 64 <= total);
           if (d == 0) marks = D[eo] & ~kSumOffset;
           CHECK((D[eo] & ~kSumOffset) == marks);  // every wave sees the same marks
@@ -137,8 +138,8 @@ int main(int argc, char **argv) {
     for (int h = 0; h < halves; ++h)
       for (int64_t v : acc[h]) CHECK(v == 0);  // the last group flushes
     for (int wave = 0; wave < kGrpWaves; ++wave) {  // one idle record ends each stream
-      const int64_t ro = t.rec_off + ((int64_t)gb->rec_first[wave] + pos[wave]) * kGrpRecWords;
-      CHECK(ro + 4 * kGrpRecWords <= t.op_off && D[ro] == 0 && D[ro + 1] == kRecLast);
+      const int64_t ro = t.head.rec_off + ((int64_t)gb->rec_first[wave] + pos[wave]) * kGrpRecWords;
+      CHECK(ro + 4 * kGrpRecWords <= t.head.op_off && D[ro] == 0 && D[ro + 1] == kRecLast);
     }
     for (int d = 0; d < kGrpRows && b * kGrpRows + d < n_dm; ++d)
       for (int h = 0; h < halves; ++h)
