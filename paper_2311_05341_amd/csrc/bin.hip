@@ -11,15 +11,17 @@
 // is read once with 16-byte loads that are contiguous across a wave, every
 // output written once.  A workgroup takes 256 * 4 consecutive units of one row
 // (unit = one 16-byte input chunk, or one bin for the generic kernel); grid y
-// walks the channel rows.
+// walks the channel rows.  (The generic kernel's are per_block bins.)
 //
 //   bin_chunk_kernel  F divides the samples of a chunk: one lane turns its
 //                     chunk into whole bins (SWAR adds for 8- and 4-bit data).
 //   bin_group_kernel  F a larger power of two: L = F / (samples per chunk)
 //                     consecutive lanes each sum one chunk, then add across
 //                     the group with cross-lane shuffles.
-//   bin_any_kernel    any other F: one lane per bin, one sample at a time.
+//   bin_any_kernel    any other F: the samples go through LDS, one lane per bin.
 #include <hip/hip_runtime.h>
+
+#include <algorithm>
 
 #include "dd_internal.h"
 
@@ -38,6 +40,7 @@ struct BinArgs {
   int64_t n_bins;
   int64_t n_units;  // units of work per row (chunks, or bins for the generic kernel)
   int factor;
+  int per_block;  // generic kernel: bins per workgroup
 };
 
 template <int DT>
@@ -269,28 +272,40 @@ __device__ __forceinline__ uint32_t int_sample(const uint8_t *row, int64_t t) {
   else return ((const uint16_t *)row)[t];
 }
 
+// Any other factor: the samples of `per_block` bins (a multiple of 32, so that they
+// start on 16 bytes) go through LDS with 16-byte loads, then one lane adds up a bin,
+// in index order.  About 16 KiB of samples leave eight workgroups a CU.  Read straight
+// from memory, a lane's strided narrow loads bound it; 4096 x 390000 samples by 3, so /
+// now: 8-bit 1520 / 486 us, 4-bit 1466 / 378, 16-bit 1813 / 1011, float 1722 / 1584.
 template <int DT>
 __global__ __launch_bounds__(kBinThreads) void bin_any_kernel(BinArgs a) {
   using Out = typename BinTraits<DT>::Out;
+  constexpr int kBits = DT == DD_U4 ? 4 : DT == DD_U8 ? 8 : DT == DD_U16 ? 16 : 32;
+  extern __shared__ __align__(16) uint8_t stage[];
+  const int64_t j0 = (int64_t)blockIdx.x * a.per_block;
+  const int bins = (int)min((int64_t)a.per_block, a.n_bins - j0);
+  const int chunks = (int)((((int64_t)bins * a.factor * kBits + 7) / 8 + 15) / 16);  // each holds a sample of a whole bin
+  const int64_t b0 = j0 * a.factor * kBits / 8;
   for (int c = blockIdx.y; c < a.n_chan; c += gridDim.y) {
     const uint8_t *row = a.in + (int64_t)c * a.in_pitch;
     Out *orow = (Out *)(a.out + (int64_t)c * a.out_pitch);
-    const int64_t j0 = (int64_t)blockIdx.x * (kBinThreads * kBinUnits) + threadIdx.x;
-    for (int u = 0; u < kBinUnits; ++u) {
-      const int64_t j = j0 + u * kBinThreads;
-      if (j >= a.n_bins) break;
-      const int64_t t0 = j * a.factor;
+    for (int k = threadIdx.x; k < chunks; k += kBinThreads)
+      ((uint4 *)stage)[k] = *(const uint4 *)(row + b0 + 16 * k);
+    __syncthreads();
+    for (int j = threadIdx.x; j < bins; j += kBinThreads) {
+      const int t0 = j * a.factor;
       if constexpr (DT == DD_F32) {
-        const float *r = (const float *)row;
-        float s = r[t0];
-        for (int i = 1; i < a.factor; ++i) s += r[t0 + i];
-        orow[j] = s;
+        const float *r = (const float *)stage + t0;
+        float s = r[0];
+        for (int i = 1; i < a.factor; ++i) s += r[i];
+        orow[j0 + j] = s;
       } else {
         uint32_t s = 0;
-        for (int i = 0; i < a.factor; ++i) s += int_sample<DT>(row, t0 + i);
-        orow[j] = (Out)s;
+        for (int i = 0; i < a.factor; ++i) s += int_sample<DT>(stage, t0 + i);
+        orow[j0 + j] = (Out)s;
       }
     }
+    __syncthreads();
   }
 }
 
@@ -375,7 +390,8 @@ int launch_bin(int dtype, const void *in, int64_t in_pitch, int n_chan, int64_t 
   a.n_bins = n_samp / factor;
   a.factor = factor;
   BinKernel k = nullptr;
-  int unit = 0;
+  int unit = 0, lds = 0;
+  a.per_block = 0;
   if ((factor & (factor - 1)) == 0) {
     switch (dtype) {
       case DD_U8: k = pick_pow2<DD_U8>(factor, &unit); break;
@@ -395,11 +411,15 @@ int launch_bin(int dtype, const void *in, int64_t in_pitch, int n_chan, int64_t 
       case DD_F32: k = bin_any_kernel<DD_F32>; break;
       default: return (int)hipErrorInvalidValue;
     }
+    // about 16 KiB of samples per workgroup, at least 32 bins
+    const int bits = dtype == DD_U4 ? 4 : dtype == DD_U8 ? 8 : dtype == DD_U16 ? 16 : 32;
+    a.per_block = 32 * std::max(1, 16384 * 8 / (32 * factor * bits));
     a.n_units = a.n_bins;
+    lds = a.per_block * factor * bits / 8;
   }
-  const int64_t per_block = (int64_t)kBinThreads * kBinUnits;
+  const int64_t per_block = lds ? a.per_block : (int64_t)kBinThreads * kBinUnits;
   const dim3 grid((unsigned)((a.n_units + per_block - 1) / per_block), (unsigned)(n_chan < 65535 ? n_chan : 65535));
-  hipLaunchKernelGGL(k, grid, dim3(kBinThreads), 0, (hipStream_t)stream, a);
+  hipLaunchKernelGGL(k, grid, dim3(kBinThreads), lds, (hipStream_t)stream, a);
   return (int)hipGetLastError();
 }
 
