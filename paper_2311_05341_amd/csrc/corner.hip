@@ -7,9 +7,7 @@
 // An HBM-bound LDS-tiled transpose.  A workgroup of 256 lanes takes a tile of
 // TC channels x TT samples: it reads the tile's TT spectrum segments of 256
 // bytes with 16-byte loads (16 lanes per segment, several loads in flight per
-// lane) into LDS, then writes TC output segments of 128 bytes.  Workgroups walk
-// the channel tiles of one time tile consecutively, so the spectra are read as
-// contiguous runs.
+// lane) into LDS, then writes TC output segments of 128 bytes.
 //
 // 8-bit, 16-bit and float data (corner_turn_words_kernel): a lane takes one
 // 32-bit column of the tile (4, 2 or 1 channels) over the samples of one
@@ -20,14 +18,25 @@
 // XOR-swizzled with the output piece r belongs to, which makes those reads
 // conflict-free.  4-bit data (corner_turn_kernel) assemble each output piece
 // from nibble reads.
+//
+// Each XCD takes a contiguous run of time tiles, kCtGroup channel tiles at a time: a row
+// segment rarely starts on a 128-byte line (row pitches are multiples of 16 bytes), and
+// its line is completed by the next time tile's segment in the same L2 instead of
+// reaching HBM in two parts from two XCDs.  Four channel tiles keep the spectra read in
+// runs of 1 KiB and few enough unfinished lines for the L2.  4096 ch x 390000 samples
+// (float: 195000), channel tiles of the whole band fastest over all XCDs / 1 / 4 / 8 / 16
+// together: 8-bit 901 / 905 / 681 / 716 / 799 us, 16-bit 1513 / 1467 / 1267 / 1324 / 1358,
+// float 1361 / 1401 / 1214 / 1255 / 1255, 4-bit 523 / 500 / 471 / 480 / 475.
 #include <hip/hip_runtime.h>
 
 #include "dd_internal.h"
+#include "tile_order.h"
 
 namespace dd {
 namespace {
 
 constexpr int kCtThreads = 256;
+constexpr int kCtGroup = 4;  // channel tiles that an XCD walks together
 
 template <int DT>
 struct CtGeom;
@@ -59,8 +68,26 @@ struct CtArgs {
   int64_t n_samp;
   int64_t in_row_bytes;   // bytes of one spectrum
   int64_t out_row_bytes;  // bytes of one channel row
-  int n_ctiles;
+  int n_ctiles, n_ttiles;
 };
+
+// This workgroup's tile.  Workgroup w runs on XCD w % 8, which takes the time tiles
+// [x * n, (x + 1) * n), n = n_ttiles / 8, for kCtGroup channel tiles after another
+// (channel tiles of a group fastest); time tiles left over go last.
+__device__ __forceinline__ void tile_of_block(const CtArgs &a, int &ct, int64_t &tt) {
+  const unsigned w = blockIdx.x, nc = (unsigned)a.n_ctiles;
+  const unsigned per = (unsigned)a.n_ttiles / kXcds, main = kXcds * per * nc;
+  if (w < main) {
+    const unsigned k = w / kXcds, g = k / (per * kCtGroup), c0 = g * kCtGroup;
+    const unsigned r = k - g * per * kCtGroup, n = min(nc - c0, (unsigned)kCtGroup);
+    ct = (int)(c0 + r % n);
+    tt = (int64_t)(w % kXcds) * per + r / n;
+  } else {
+    const unsigned r = w - main;
+    ct = (int)(r % nc);
+    tt = (int64_t)kXcds * per + r / nc;
+  }
+}
 
 template <int DT>
 __global__ __launch_bounds__(kCtThreads) void corner_turn_kernel(CtArgs a) {
@@ -73,8 +100,9 @@ __global__ __launch_bounds__(kCtThreads) void corner_turn_kernel(CtArgs a) {
   static_assert(kInChunks % kCtThreads == 0 && kOutChunks % kCtThreads == 0, "tile shape");
   __shared__ __attribute__((aligned(16))) uint8_t tile[G::TT * kPitch];
 
-  const int ct = (int)(blockIdx.x % (unsigned)a.n_ctiles);
-  const int64_t tt = blockIdx.x / (unsigned)a.n_ctiles;
+  int ct;
+  int64_t tt;
+  tile_of_block(a, ct, tt);
   const int64_t t0 = tt * G::TT;
   const int64_t b0 = (int64_t)ct * kInSeg;  // first byte of the tile in a spectrum
   const int c0 = ct * G::TC;
@@ -159,8 +187,10 @@ __global__ __launch_bounds__(kCtThreads) void corner_turn_words_kernel(CtArgs a)
   static_assert(G::TC * ES == 256 && G::TT == 8 * R, "tile shape");
   __shared__ __attribute__((aligned(16))) uint8_t tile[G::TT * 256];
 
-  const int ct = (int)(blockIdx.x % (unsigned)a.n_ctiles);
-  const int64_t t0 = (int64_t)(blockIdx.x / (unsigned)a.n_ctiles) * G::TT;
+  int ct;
+  int64_t tt;
+  tile_of_block(a, ct, tt);
+  const int64_t t0 = tt * G::TT;
   const int64_t b0 = (int64_t)ct * 256;
   const int c0 = ct * G::TC;
 
@@ -238,6 +268,7 @@ int launch_ct(const CtArgs &a0, hipStream_t st) {
   const int64_t n_ttiles = (a.n_samp + G::TT - 1) / G::TT;
   const int64_t blocks = n_ttiles * a.n_ctiles;
   if (blocks > 0x7fffffff) return (int)hipErrorInvalidValue;
+  a.n_ttiles = (int)n_ttiles;
   if constexpr (DT == DD_U4)
     hipLaunchKernelGGL(corner_turn_kernel<DT>, dim3((unsigned)blocks), dim3(kCtThreads), 0, st, a);
   else
@@ -256,7 +287,7 @@ int launch_corner_turn(int dtype, const void *in, int64_t in_pitch, int n_chan, 
   a.out_pitch = out_pitch;
   a.n_chan = n_chan;
   a.n_samp = n_samp;
-  a.n_ctiles = 0;
+  a.n_ctiles = a.n_ttiles = 0;
   hipStream_t st = (hipStream_t)stream;
   switch (dtype) {
     case DD_U8:

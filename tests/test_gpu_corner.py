@@ -86,6 +86,14 @@ def test_corner_turn_large(dd):
     _check_turn(dd, "u4", 4097, 30000, seed=4)
 
 
+@pytest.mark.parametrize("n_ttiles", [7, 8, 9, 23, 24])
+@pytest.mark.parametrize("n_ctiles", [3, 4, 5, 9])
+def test_corner_turn_tile_runs(n_ctiles, n_ttiles, dd):
+    """Runs of time tiles per XCD (8 of them) and groups of 4 channel tiles, whole and left over:
+    8-bit tiles are 256 channels x 128 samples."""
+    _check_turn(dd, "u8", 256 * n_ctiles - 3, 128 * n_ttiles - 6, seed=100 * n_ctiles + n_ttiles)
+
+
 def _survey_args(cfg, n_samp):
     return (cfg["n_chan"], n_samp, cfg["dtype"], cfg["f_high"], cfg["chan_bw"], cfg["t_samp"], cfg["ranges"])
 
