@@ -160,8 +160,9 @@ dd_status dd_plan_bind(dd_plan *plan, void *d_workspace, size_t bytes, void *str
  * n_chan <= 65793 resp. 1118481); 16-bit sums (n_chan <= 65537) are exact
  * below 2^24 and rounded to nearest even above, as the conversion of the exact
  * sum would be.  Float input
- * accumulates in float32 in a fixed order: channels in groups of 32 summed in
- * order, then the group sums in order; the result does not depend on the tile shape.
+ * accumulates in float32 in a fixed order: channels in fours, ((x0 + x1) + x2) + x3, the
+ * sums of the eight fours of 32 channels in order, then those sums in order; the result
+ * does not depend on the tile shape.
  * Errors: DD_ERR_ARG, DD_ERR_ALIGN, DD_ERR_NOT_BOUND, DD_ERR_HIP.
  */
 dd_status dd_execute(const dd_plan *plan, const void *d_in, float *d_out, int64_t out_pitch,
@@ -196,7 +197,7 @@ dd_status dd_execute_noalloc(const dd_plan *plan, const void *d_in, float *d_out
  *   d_grad_in  device pointer, float32 [n_chan] rows of in_pitch_bytes; columns
  *              0..n_samp-1 of every row are overwritten (exact zeros where no
  *              output reads the sample).
- * No atomics; DMs are summed in a fixed order (groups of 32 in order), so the
+ * No atomics; DMs are summed in the same fixed order (fours, 32, all), so the
  * result is deterministic and independent of the tile shape.
  * Errors: DD_ERR_DTYPE (integer plan), DD_ERR_ARG, DD_ERR_ALIGN (d_y not 4-byte or d_grad
  * not 16-byte aligned), DD_ERR_NOT_BOUND, DD_ERR_HIP.

@@ -49,6 +49,11 @@ int copy_tables(const dd_plan &p, void *dst, void *stream) {
   } else {
     const FloatTables *tabs[2] = {&p.ftab_fwd, &p.ftab_adj};
     for (int k = 0; k < 2 && e == hipSuccess; ++k) {
+      const QuadTables &q = p.qtab[k];
+      if (q.use) {  // in the place of the direction's other tables
+        e = hipMemcpyAsync(base + L.f_offs[k], q.data.data(), q.data.size() * 4, hipMemcpyHostToDevice, st);
+        continue;
+      }
       e = hipMemcpyAsync(base + L.f_offs[k], tabs[k]->offs.data(), tabs[k]->offs.size() * 2, hipMemcpyHostToDevice, st);
       if (e == hipSuccess)
         e = hipMemcpyAsync(base + L.f_sbase[k], tabs[k]->sbase.data(), tabs[k]->sbase.size() * 4,

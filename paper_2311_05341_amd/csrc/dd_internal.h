@@ -8,6 +8,7 @@
 
 #include "../../include/dd.h"
 #include "group_tables.h"
+#include "quad_tables.h"
 
 namespace dd {
 
@@ -86,6 +87,7 @@ struct dd_plan {
   dd::GroupTables gtab;        // integer plans: group-sum tables; in use until tiles are chosen explicitly
   dd::FloatTables ftab_fwd;    // float plans: forward kernel tables
   dd::FloatTables ftab_adj;    // float plans: adjoint kernel tables
+  dd::QuadTables qtab[2];      // float plans: quad tables (forward, adjoint); in use until tiles are chosen explicitly
   // binding
   const void *d_tables = nullptr;
   int device = -1;
@@ -101,8 +103,8 @@ dd_status choose_forward_tiles(dd_plan &p);
 // Rebuild the tables of one direction (0 forward, 1 adjoint) for compiled
 // shape `shape` and TileOrder `order`.  DD_ERR_RANGE if the shape cannot hold
 // the plan's delay spread; the plan is unchanged then.
-// An integer plan's forward (and its beam in a batch) then runs that shape's kernel
-// (gtab.use and gtab.batch are cleared).
+// The direction (an integer plan's forward: its beam in a batch too) then runs that
+// shape's kernel (gtab.use and gtab.batch, qtab[direction].use are cleared).
 // With fill false an integer plan's staged tables are only sized.
 dd_status set_tiles(dd_plan &p, int direction, int shape, int order, bool fill = true);
 int num_shapes(const dd_plan &p);
@@ -171,6 +173,10 @@ inline int launch_forward(const dd_plan &p, const void *tables, const void *d_in
 int launch_forward_f32(const dd_plan &p, const void *tables, const void *d_in, float *d_out, int64_t out_pitch,
                        void *stream, int64_t out_limit = 0);
 // Float tile shapes compiled into the library: (ns, per_wave, waves, row_block).
+// Quad sums (quad_f32.hip): out[n_outputs][out_pitch], samples 0..out_len-1, from the rows x
+// of row_len floats.
+int launch_quad(const QuadTables &q, const void *tables, const float *x, int64_t row_pitch, int n_rows, int64_t row_len,
+                float *out, int64_t out_pitch, int n_outputs, int64_t out_len, void *stream);
 extern const int kF32Shapes[][4];
 extern const int kNumF32Shapes;
 // Integer tile shapes compiled into the library: (ns, dm_per_wave, waves,

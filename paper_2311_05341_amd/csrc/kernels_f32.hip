@@ -17,11 +17,14 @@
 // word aligned: lane i owns words i, i+64, ... of the window, so each LDS read
 // is a contiguous, bank-conflict-free 256-byte wave access; no realignment.
 //
-// Float sums use a fixed order that depends only on the row index: rows in
-// groups of 32 summed in order into a partial, then the partials in order.
+// Float sums use a fixed order that depends only on the row index: rows in quads,
+// ((x0 + x1) + x2) + x3, the quads of 32 rows in order into a partial, then the
+// partials in order (the order in which quad_f32.hip shares sums).
 // Results are bitwise independent of the tile shape; no atomics.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
+
+#include <type_traits>
 
 #include "dd_internal.h"
 #include "tile_order.h"
@@ -169,11 +172,11 @@ __device__ __forceinline__ void f32_tile(uint8_t *lds, const FArgs &a, int oblk,
   const int slot_bytes = CB * a.row_bytes;
   const int nblk = rows_pad / CB;
 
-  float tot[R][NS], part[R][NS];
+  float tot[R][NS], part[R][NS], quad[NS];
 #pragma unroll
   for (int r = 0; r < R; ++r)
 #pragma unroll
-    for (int j = 0; j < NS; ++j) tot[r][j] = part[r][j] = 0.0f;
+    for (int j = 0; j < NS; ++j) tot[r][j] = part[r][j] = quad[j] = 0.0f;
 
   uint8_t *sink = lds + kRing * slot_bytes;  // 1 KiB after the ring: target of the padding loads
   const DmaPlan<MAXT> dp = dma_plan<NW, CB, MAXT>(a.row_bytes, a.row_bytes, wave, lane);
@@ -189,7 +192,10 @@ __device__ __forceinline__ void f32_tile(uint8_t *lds, const FArgs &a, int oblk,
   for (int q = 0; q < CB * NOW; ++q) ow[q] = scalar_load(woffs, q);
 
   const uint8_t *lane_base = lds + 4 * lane;
-  for (int b = 0; b < nblk; ++b) {
+  // One block; U: its place among the blocks of a quad (-1: any).
+  static_assert(CB >= 4 || (R == 1 && (CB == 1 || NW == 16)), "one quad open per wave");
+  auto block = [&](int b, auto uc) {
+    constexpr int U = decltype(uc)::value;
     // Block b's loads have landed (this wave's); after the barrier every
     // wave's have, and nobody reads the slot of block b-1 any more.
     wait_vmcnt<(kRing - 2) * MAXT>();
@@ -197,22 +203,41 @@ __device__ __forceinline__ void f32_tile(uint8_t *lds, const FArgs &a, int oblk,
     stage_dma<MAXT>(a, dp, bases, t0, (b + kRing - 1) * CB, lds + ((b + kRing - 1) % kRing) * slot_bytes,
                     sink);  // zeros past the end
     const uint8_t *blk = lane_base + (b % kRing) * slot_bytes;
-    // Reads run one (row, output) pair ahead of the adds in a second register set.
+    // Reads run one (row, output) pair ahead of the adds; a quad's rows of one output
+    // follow each other.
+    constexpr int QR = CB < 4 ? CB : 4;  // rows of a quad in this block
     float wv[2][NS];
     auto read_pair = [&](int q, float (&dst)[NS]) {
-      const int kk = q / R, r = q % R;
+      const int kk = q / (QR * R) * QR + q % QR, r = q / QR % R;
       const uint32_t e = (ow[kk * NOW + (r >> 1)] >> (16 * (r & 1))) & 0xFFFFu;
       const float *p = (const float *)(blk + kk * a.row_bytes + e);
 #pragma unroll
       for (int j = 0; j < NS; ++j) dst[j] = p[64 * j];
     };
     read_pair(0, wv[0]);
+    if constexpr (U < 0) {  // CB = 1, any place
 #pragma unroll
-    for (int q = 0; q < CB * R; ++q) {
-      if (q + 1 < CB * R) read_pair(q + 1, wv[(q + 1) & 1]);
+      for (int j = 0; j < NS; ++j) quad[j] += wv[0][j];
+      if (b % 4 == 3 || b + 1 == nblk)
 #pragma unroll
-      for (int j = 0; j < NS; ++j) part[q % R][j] += wv[q & 1][j];
+        for (int j = 0; j < NS; ++j) {
+          part[0][j] += quad[j];
+          quad[j] = 0.0f;
+        }
     }
+#pragma unroll
+    for (int q = 0; U >= 0 && q < CB * R; ++q) {
+      if (q + 1 < CB * R) read_pair(q + 1, wv[(q + 1) & 1]);
+      const int c = QR < 4 ? U * CB + q : q % 4, r = q / QR % R;  // row of the quad, output
+#pragma unroll
+      for (int j = 0; j < NS; ++j) {
+        quad[j] = c == 0 ? wv[q & 1][j] : quad[j] + wv[q & 1][j];
+        if (c == 3) part[r][j] += quad[j];
+      }
+    }
+    if (U >= 0 && QR < 4 && U * CB + CB < 4 && b + 1 == nblk)  // the rows end inside a quad
+#pragma unroll
+      for (int j = 0; j < NS; ++j) part[0][j] += quad[j];
     if (((b + 1) * CB) % 32 == 0 || b + 1 == nblk) {  // end of a group of 32 rows
 #pragma unroll
       for (int r = 0; r < R; ++r)
@@ -229,6 +254,18 @@ __device__ __forceinline__ void f32_tile(uint8_t *lds, const FArgs &a, int oblk,
 #pragma unroll
     for (int q = 0; q < CB * NOW; ++q) ow[q] = scalar_load(woffs, oi + q);
     stage_bases<MAXT>(a, sb, (b + kRing) * CB, dp, bases);
+  };
+  // The blocks of a quad in a row of code each (the 4-wave shapes' loads leave no scalar
+  // registers for that: 1813 against 1517 us on 256 ch x 132132 x 64 DMs).
+  constexpr int kBlocks = CB >= 4 || NW < 16 ? 1 : 4 / CB;
+  for (int b = 0; b < nblk; b += kBlocks) {
+    block(b, std::integral_constant<int, CB < 4 && kBlocks == 1 ? -1 : 0>());
+    if constexpr (kBlocks >= 2)
+      if (b + 1 < nblk) block(b + 1, std::integral_constant<int, 1>());
+    if constexpr (kBlocks == 4) {
+      if (b + 2 < nblk) block(b + 2, std::integral_constant<int, 2>());
+      if (b + 3 < nblk) block(b + 3, std::integral_constant<int, 3>());
+    }
   }
   wait_vmcnt<0>();
   lds_barrier();
@@ -272,8 +309,12 @@ int launch_f32_shape(const FArgs &a, int lds_bytes, int order, hipStream_t st) {
   return (int)hipGetLastError();
 }
 
+int64_t limited(int64_t out_len, int64_t out_limit) {
+  return out_limit > 0 && out_limit < out_len ? out_limit : out_len;
+}
+
 int launch_f32(const FloatTables &t, FArgs a, int64_t out_limit, hipStream_t st) {
-  if (out_limit > 0 && out_limit < a.out_len) a.out_len = (int32_t)out_limit;
+  a.out_len = (int32_t)limited(a.out_len, out_limit);
 #define DD_TRY(NS, R, NW, CB)                                               \
   if (t.ns == NS && t.per_wave == R && t.waves == NW && t.row_block == CB) \
     return launch_f32_shape<NS, R, NW, CB>(a, t.lds_bytes, t.order, st);
@@ -293,6 +334,9 @@ int launch_forward_f32(const dd_plan &p, const void *tables, const void *d_in, f
                        void *stream, int64_t out_limit) {
   const FloatTables &t = p.ftab_fwd;
   const TableLayout L = table_layout(p);
+  if (p.qtab[0].use)
+    return launch_quad(p.qtab[0], (const uint8_t *)tables + L.f_offs[0], (const float *)d_in, p.in_pitch_bytes / 4,
+                       p.desc.n_chan, p.desc.n_samp, d_out, out_pitch, p.desc.n_dm, limited(p.n_out, out_limit), stream);
   FArgs a;
   a.x = (const float *)d_in;
   a.offs = (const uint32_t *)((const uint8_t *)tables + L.f_offs[0]);
@@ -312,6 +356,9 @@ int launch_adjoint(const dd_plan &p, const void *tables, const float *d_y, int64
                    void *stream, int64_t out_limit) {
   const FloatTables &t = p.ftab_adj;
   const TableLayout L = table_layout(p);
+  if (p.qtab[1].use)
+    return launch_quad(p.qtab[1], (const uint8_t *)tables + L.f_offs[1], d_y, y_pitch, p.desc.n_dm, p.n_out, d_grad,
+                       p.in_pitch_bytes / 4, p.desc.n_chan, limited(p.desc.n_samp, out_limit), stream);
   FArgs a;
   a.x = d_y;
   a.offs = (const uint32_t *)((const uint8_t *)tables + L.f_offs[1]);

@@ -283,6 +283,7 @@ dd_status set_tiles(dd_plan &p, int direction, int shape, int order, bool fill) 
     if (st != DD_OK) return st;
     ft.shape = shape;
     ft.order = order;
+    p.qtab[direction].use = false;
     if (direction == 1) {
       p.ftab_adj = std::move(ft);
       return DD_OK;
@@ -403,6 +404,8 @@ static dd_status choose_shapes(dd_plan &p) {
   return DD_OK;
 }
 
+static size_t up256(size_t v) { return (v + 255) / 256 * 256; }
+
 // Whether an integer plan's forward runs by group sums (fwd_group.hip) instead of
 // its shape's kernel: where the modelled time is smaller by a tenth (the model is
 // good to that; plans near the line run equally fast either way: 210 against 206 us
@@ -440,10 +443,44 @@ static void choose_group_sums(dd_plan &p) {
   p.gtab.batch = p.gtab.cost <= batch_limit;
 }
 
+// Whether a direction of a float plan runs by quad sums (quad_f32.hip) instead of its
+// shape's kernel, and with how many outputs per block: where the modelled time, in rounds
+// of one workgroup per CU, is below 0.62 of the other kernel's (kRate: additions per CU
+// clock; 22.7 measured on 1024 ch x 131900 x 512 DMs).  At 1200-1500 MHz, quad sums against
+// the other kernel by what the model says: 0.26-0.40 of it: 0.35-0.57 measured (that plan's
+// forward: 1706 against 4919 us); 0.41-0.53: 0.41-0.73; 0.58-0.62: 0.77-0.93; 0.64 (512 ch x
+// 35996 x 200 DMs of step 1, 256 ch x 16944 x 70): 1.14 and 1.26, since steps of one or two
+// quads wait at their barriers.
+static void choose_quads(dd_plan &p, int dir) {
+  const FloatTables &t = dir ? p.ftab_adj : p.ftab_fwd;
+  const double kRate = 23.0, kCus = 256;
+  const int nd = p.desc.n_dm, nc = p.desc.n_chan;
+  const QuadShifts sh = {p.shift.data(), dir ? 1 : (int64_t)nc, dir ? (int64_t)nc : 1, dir ? -1 : 1, dir ? nc : nd,
+                         dir ? nd : nc};
+  const int64_t out_len = dir ? p.desc.n_samp : p.n_out, tiles = (out_len + kQuadWin - 1) / kQuadWin;
+  const int64_t oblk = t.waves * t.per_wave, n_oblk = (sh.n_out + oblk - 1) / oblk;
+  const int64_t others_tiles = (out_len + 64 * t.ns - 1) / (64 * t.ns);
+  double best = 0.62 * ceil((double)(n_oblk * others_tiles) / kCus) * (double)(oblk * 64 * t.ns) * sh.n_rows / kRate;
+  int rows = 0;
+  for (int r : {64, 32}) {
+    const int64_t n_blk = (sh.n_out + r - 1) / r;
+    const double v = ceil((double)(n_blk * tiles) / kCus) * guess_quad_cost(sh, r) / (double)n_blk;
+    if (v < best) best = v, rows = r;
+  }
+  QuadTables q;
+  if (!rows || !build_quad_tables(sh, rows, &q) ||
+      q.data.size() * 4 > up256(t.offs.size() * 2) + up256(t.sbase.size() * 4))  // (they take those tables' place)
+    return;
+  q.use = true;
+  p.qtab[dir] = std::move(q);
+}
+
 dd_status choose_forward_tiles(dd_plan &p) {
   dd_status st = choose_shapes(p);
   if (st != DD_OK) return st;
   choose_group_sums(p);
+  if (p.desc.dtype == DD_F32)
+    for (int dir = 0; dir < 2; ++dir) choose_quads(p, dir);
   if (p.desc.dtype != DD_F32 && !p.gtab.use) {
     const bool batch = p.gtab.batch;
     st = set_tiles(p, 0, p.fwd.shape, p.fwd.order);  // fill its tables
@@ -451,8 +488,6 @@ dd_status choose_forward_tiles(dd_plan &p) {
   }
   return st;
 }
-
-static size_t up256(size_t v) { return (v + 255) / 256 * 256; }
 
 // Device workspace layout.  Integer plans: [offs words][sbase int32].
 // Float plans: [forward offs][forward sbase][adjoint offs][adjoint sbase].

@@ -1,0 +1,93 @@
+"""The quad kernel: what a float plan runs by default, forward and adjoint, where rows share few
+delay patterns.  Explicitly chosen tiles run that shape's kernel, which adds in the same order:
+every case is checked against the oracle and, bit for bit, against its own default shape chosen
+explicitly.
+"""
+import numpy as np
+import pytest
+import torch
+
+import oracle
+from helpers import oracle_table, plan_for
+
+pytestmark = pytest.mark.gpu
+
+EPS = 2.0 ** -24
+
+
+@pytest.fixture(scope="module")
+def dd():
+    import paper_2311_05341_amd as dd
+    assert torch.cuda.is_available()
+    return dd
+
+
+# (channels, samples, trials, dm_start, dm_step): a tail in rows, outputs and the last quad, less
+# than one tile, a last tile of one sample, no delay at all, blocks of 32 and of 64 outputs, spreads
+# that need several tasks a row or leave the quad kernel
+CASES = [(256, 20011, 300, 0.0, 0.5), (513, 9000, 130, 0.0, 0.25), (1024, 3000, 257, 0.0, 0.02), (301, 1025, 33, 0.0, 0.0),
+         (1, 700, 64, 0.0, 0.5), (1024, 24577, 96, 200.0, 1.0), (130, 8193, 65, 0.0, 0.1), (64, 6000, 100, 0.0, 2.0)]
+
+
+@pytest.mark.parametrize("case", CASES)
+def test_default_equals_oracle_and_explicit_shape(dd, case):
+    n_chan, n_samp, n_dm, start, step = case
+    cfg = dict(dtype="f32", n_chan=n_chan, n_samp=n_samp, f_high=1500.0, chan_bw=300.0 / n_chan, t_samp=256e-6,
+               dm_start=start, dm_step=step, n_dm=n_dm)
+    s = oracle_table(cfg)
+    rng = np.random.default_rng(n_chan + n_dm)
+    pitch = (n_samp + 3) // 4 * 4 + 4
+    x = np.full((n_chan, pitch), np.nan, dtype=np.float32)  # the padding must not be read
+    x[:, :n_samp] = rng.standard_normal((n_chan, n_samp))
+    plan = plan_for(dd, cfg, in_pitch_bytes=4 * pitch)
+    n_out = plan.n_out
+    xd = torch.from_numpy(x).cuda()
+    y = np.full((n_dm, n_out + 3), np.nan, dtype=np.float32)  # a pitch that is no multiple of 16 bytes
+    y[:, :n_out] = rng.standard_normal((n_dm, n_out))
+    yd = torch.from_numpy(y).cuda()
+    out = torch.full((n_dm, plan.out_pitch + 8), -7.0, device="cuda")
+    grad = torch.full((n_chan, pitch), -7.0, device="cuda")
+    print("f32 n_chan=%d n_samp=%d n_dm=%d step=%g" % (n_chan, n_samp, n_dm, step), flush=True)
+    plan.forward(xd, out=out)
+    plan.adjoint(yd[:, :n_out], out=grad)
+    torch.cuda.synchronize()
+    want, ab = oracle.forward_f32(np.ascontiguousarray(x[:, :n_samp]), n_samp, s)
+    got = out[:, :n_out].cpu().numpy()
+    assert np.all(np.abs(got.astype(np.float64) - want) <= (n_chan + 32) * EPS * ab + 1e-30)
+    yc = np.ascontiguousarray(y[:, :n_out])
+    wantg, abg = oracle.adjoint(yc, n_chan, n_samp, s), oracle.adjoint(np.abs(yc), n_chan, n_samp, s)
+    gotg = grad[:, :n_samp].cpu().numpy()
+    assert np.all(np.abs(gotg.astype(np.float64) - wantg) <= (n_dm + 32) * EPS * abg + 1e-30)
+    assert bool((out[:, n_out:] == -7.0).all()) and bool((grad[:, n_samp:] == -7.0).all())
+    for d in (0, 1):
+        t = plan.tiles(d)
+        plan.set_tiles(d, t["shape"], t["order"])
+        if d == 0:  # the other direction keeps its kernel and finds its tables
+            assert np.array_equal(plan.adjoint(yd[:, :n_out]).cpu().numpy(), gotg)
+    assert np.array_equal(plan.forward(xd).cpu().numpy(), got)
+    assert np.array_equal(plan.adjoint(yd[:, :n_out]).cpu().numpy(), gotg)
+    for shape in range(plan.n_shapes):  # every shape adds in the same order
+        try:
+            plan.set_tiles(0, shape, 0)
+        except dd.DDError:
+            continue
+        assert np.array_equal(plan.forward(xd).cpu().numpy(), got), shape
+
+
+def test_replayed_graph(dd):
+    cfg = dict(dtype="f32", n_chan=256, n_samp=20000, f_high=1500.0, chan_bw=300.0 / 256, t_samp=256e-6, dm_start=0.0,
+               dm_step=0.5, n_dm=128)
+    plan = plan_for(dd, cfg)
+    x = torch.randn((256, 20000), device="cuda")
+    out = torch.empty((128, plan.out_pitch), device="cuda")
+    grad = torch.empty((256, 20000), device="cuda")
+    plan.adjoint(plan.forward(x, out=out), out=grad)
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        plan.adjoint(plan.forward(x, out=out), out=grad)
+    for k in range(3):
+        x.copy_(torch.roll(x, k + 1, 1))
+        g.replay()
+        torch.cuda.synchronize()
+        y = plan.forward(x)
+        assert torch.equal(out[:, : plan.n_out], y) and torch.equal(grad, plan.adjoint(y)[:, :20000])
