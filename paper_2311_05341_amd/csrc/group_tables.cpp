@@ -6,6 +6,7 @@
 #include <algorithm>
 #include <climits>
 #include <new>
+#include <system_error>
 #include <thread>
 
 namespace dd {
@@ -413,7 +414,12 @@ bool build_group_tables(const int32_t *shift, int n_dm, int n_chan, int bits, in
     } else {
       std::vector<std::thread> th;
       std::vector<uint8_t> failed(nthr, 0);
-      for (int k = 0; k < nthr; ++k) th.emplace_back(run, k, (bool *)&failed[k]);
+      th.reserve(nthr);
+      for (int k = 0; k < nthr; ++k) try {
+          th.emplace_back(run, k, (bool *)&failed[k]);
+        } catch (const std::system_error &) {  // no more threads: here then
+          run(k, (bool *)&failed[k]);
+        }
       for (auto &x : th) x.join();
       for (uint8_t f : failed) bad |= f != 0;
     }
