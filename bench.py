@@ -91,6 +91,11 @@ def accumulate_form(dtype, tiles):
     return FORMS[dtype][0], FORMS[dtype][1], LDS_BYTES_PER_ADD[dtype]
 
 
+# Shared sums: additions are shared between rows, so a sample-add has no instruction form; the
+# line prices it at the VALU lane-operations per add that the committed counters show.
+SHARED_FORM = "shared sums (no price per sample-add)"
+
+
 def log(msg):
     print(msg, file=sys.stderr, flush=True)
 
@@ -216,6 +221,8 @@ def attach_measured_peaks(rec, dd, torch, dtype):
     mb = microbench.measure(torch, sclk_hz=sclk)
     rec["microbench"] = mb
     achieved = rec["roofline"]["achieved"]
+    if rec["roofline"]["instruction_form"] == SHARED_FORM:
+        return
     form = mb["valu"][MEASURED_FORM[dtype]]
     direct = [k for k, v in DIRECT_FORMS.items() if v[0] == rec["roofline"]["instruction_form"]]
     if direct:
@@ -248,15 +255,16 @@ def attach_measured_peaks(rec, dd, torch, dtype):
     rec["lds_roofline"]["frac_measured"] = rec["lds_roofline"]["achieved"] / lds
 
 
-def measured_traffic(workload, tiles):
+def measured_traffic(workload, tiles, shared=False):
     """Memory traffic per launch from a committed rocprofv3 counter summary.
 
     profiles/*_counters.md hold a ```traffic block (FETCH_SIZE + WRITE_SIZE per
     launch, calibrated against a 1 GiB copy) with the workload, the tile choice
     and the SHA-256 of the kernel source they were measured on.  The figure is
     used only if all three match the run; otherwise the traffic is unknown (None).
+    Runs by shared sums have "shared" for their tiles.
     """
-    want_tiles = "%d,%d" % (tiles["shape"], tiles["order"])
+    want_tiles = "shared" if shared else "%d,%d" % (tiles["shape"], tiles["order"])
     for path in sorted(glob.glob(os.path.join(ROOT, "profiles", "*_counters.md"))):
         with open(path) as fh:
             text = fh.read()
@@ -272,6 +280,16 @@ def measured_traffic(workload, tiles):
                     continue
             return int(kv["traffic_bytes_per_launch"]), os.path.relpath(path, ROOT)
     return None, None
+
+
+def shared_ops_per_add(path):
+    """VALU lane-operations per sample-add of a run by shared sums, from the counter summary
+    measured_traffic named (None without one)."""
+    if path is None:
+        return None
+    with open(os.path.join(ROOT, path)) as fh:
+        m = re.search(r"^valu_lane_ops_per_add: ([0-9.]+)$", fh.read(), re.M)
+    return float(m.group(1)) if m else None
 
 
 def make_input(dd, torch, synth, cfg, plan):
@@ -607,12 +625,11 @@ def bench_batch48(args, dd, torch, synth):
                         "calls_per_step": sum(len(c) for c in chunkers)},
         "batched_over_plain": ms_plain / ms_batched,
         "x_realtime_beams": beam_seconds / (ms_batched * 1e-3),
-        "roofline": {"bound": "alu", "achieved": achieved, "peak": VALU_PEAK_TOPS, "unit": "Tadds/s",
-                     "frac": achieved / VALU_PEAK_TOPS, "traffic": None, "kernel": "fwd_int_batched_kernel",
-                     "kernel_ms": kernel_ms, "instruction_form": INT_FORM, "peak_instruction_form": 2 * VALU_PEAK_TOPS,
-                     "frac_instruction_form": achieved / (2 * VALU_PEAK_TOPS)},
-        "lds_roofline": {"achieved": achieved, "peak": LDS_PEAK_TBS, "unit": "TB/s", "frac": achieved / LDS_PEAK_TBS,
-                         "bytes_per_add": 1},
+        "roofline": {"bound": "alu", "achieved": achieved, "peak": None, "unit": "Tadds/s",
+                     "frac": None, "traffic": None, "kernel": "fwd_group_batched_kernel and others",
+                     "kernel_ms": kernel_ms, "instruction_form": SHARED_FORM, "peak_instruction_form": None,
+                     "frac_instruction_form": None},
+        "lds_roofline": None,
         "batch_tiles": batches[0][1].tiles(),
         "beams_per_shape": batch_shapes(batches[0][1]),
         "batch_autotune": tune,
@@ -666,7 +683,10 @@ def bench_batch_set(args, dd, torch, synth):
     torch.cuda.synchronize()
     same = all(torch.equal(g, o[:, : p.n_out]) for g, o, p in zip(got, outputs, plans))
     direct = all(p.tiles(0)["row_block"] == 0 for p in plans)
-    form, per_op, lds_b = accumulate_form(dtype, plans[0].tiles(0))
+    # the plans' own calls tell which beams share sums well; a beam of a batch may do so where
+    # its plan alone does not, so a mixed batch is priced by no one form either
+    shared = any(p.shares_sums(0) for p in plans)
+    form, per_op, lds_b = (SHARED_FORM, None, 0) if shared else accumulate_form(dtype, plans[0].tiles(0))
     achieved = adds / (b_ms * 1e-3) / 1e12
     rec = {
         "metric": "Tadds/s (%d %s beams, batched)" % (len(beams), "wide-spread" if direct else "small"),
@@ -691,12 +711,13 @@ def bench_batch_set(args, dd, torch, synth):
                         "calls_per_step": len(plans)},
         "batched_over_plain": p_ms / b_ms,
         "batched_equals_plain": same,
-        "roofline": {"bound": "alu", "achieved": achieved, "peak": VALU_PEAK_TOPS, "unit": "Tadds/s",
-                     "frac": achieved / VALU_PEAK_TOPS, "traffic": None,
-                     "kernel": "fwd_direct_batched_kernel" if direct else "fwd_int_batched_kernel",
+        "roofline": {"bound": "alu", "achieved": achieved, "peak": None if shared else VALU_PEAK_TOPS, "unit": "Tadds/s",
+                     "frac": None if shared else achieved / VALU_PEAK_TOPS, "traffic": None,
+                     "kernel": ("fwd_group_batched_kernel and others" if shared else
+                                "fwd_direct_batched_kernel" if direct else "fwd_int_batched_kernel"),
                      "kernel_ms": b_ms, "kernel_ms_median": b_med, "instruction_form": form,
-                     "peak_instruction_form": per_op * VALU_PEAK_TOPS,
-                     "frac_instruction_form": achieved / (per_op * VALU_PEAK_TOPS)},
+                     "peak_instruction_form": per_op * VALU_PEAK_TOPS if per_op else None,
+                     "frac_instruction_form": achieved / (per_op * VALU_PEAK_TOPS) if per_op else None},
         "lds_roofline": None if not lds_b else {"achieved": achieved * lds_b, "peak": LDS_PEAK_TBS, "unit": "TB/s",
                                                 "frac": achieved * lds_b / LDS_PEAK_TBS, "bytes_per_add": lds_b},
         "batch_tiles": batch.tiles(),
@@ -816,8 +837,8 @@ def bench_survey(args, dd, torch, synth):
                    "f_high_mhz": cfg["f_high"], "band_mhz": cfg["chan_bw"] * n_chan, "ranges": cfg["ranges"],
                    "adds_per_step": adds, "input_layout": "time-major spectra" if tm else "channel-major rows"},
         "x_realtime": n_samp * t_samp / (ms_step * 1e-3),
-        "roofline": {"bound": "alu", "achieved": dom["Tadds_s"], "peak": VALU_PEAK_TOPS, "unit": "Tadds/s",
-                     "frac": dom["Tadds_s"] / VALU_PEAK_TOPS, "traffic": None, "kernel": "fwd_int_kernel",
+        "roofline": {"bound": "alu", "achieved": dom["Tadds_s"], "peak": None, "unit": "Tadds/s",
+                     "frac": None, "traffic": None, "kernel": "fwd_group_kernel or the range's shape",
                      "range": dom["range"], "kernel_ms": dom["ms"]},
         "parts": parts, "binning": bins, "corner_turn": turn, "autotune_s": tune_s,
         "sum_of_parts_ms": sum(q["ms"] for q in parts) + sum(q["ms"] for q in bins) + (turn["ms"] if turn else 0.0),
@@ -925,8 +946,13 @@ def main():
     k_avg = float(np.mean(kernel_ms))
     k_med = float(np.median(kernel_ms))
     achieved = adds / (k_avg * 1e-3) / 1e12
-    traffic, traffic_src = (None, None) if args.adjoint else measured_traffic(args.workload, tiles)
-    form = accumulate_form(cfg["dtype"], tiles)
+    shared = plan.shares_sums(direction)
+    traffic, traffic_src = (None, None) if args.adjoint else measured_traffic(args.workload, tiles, shared)
+    form = (SHARED_FORM, None, 0) if shared else accumulate_form(cfg["dtype"], tiles)
+    peak = VALU_PEAK_TOPS  # one lane-operation per add
+    if shared:
+        ops = shared_ops_per_add(traffic_src)
+        peak = VALU_PEAK_TOPS / ops if ops else None
     log("steps: kernel ms %s, wall ms/step %.3f" % (["%.3f" % v for v in kernel_ms], ms_step))
     rec = {
         "metric": "Tadds/s" + (" (adjoint)" if args.adjoint else ""),
@@ -948,15 +974,16 @@ def main():
                    "direction": "adjoint" if args.adjoint else "forward"},
         "x_realtime": cfg["n_samp"] * cfg["t_samp"] / (ms_step * 1e-3),
         "x_realtime_streaming": plan.n_out * cfg["t_samp"] / (ms_step * 1e-3),
-        "roofline": {"bound": "alu", "achieved": achieved, "peak": VALU_PEAK_TOPS, "unit": "Tadds/s",
-                     "frac": achieved / VALU_PEAK_TOPS, "traffic": traffic, "traffic_unit": "bytes per launch",
+        "roofline": {"bound": "alu", "achieved": achieved, "peak": peak, "unit": "Tadds/s",
+                     "frac": achieved / peak if peak else None, "traffic": traffic, "traffic_unit": "bytes per launch",
                      "traffic_source": traffic_src,
-                     "kernel": ("f32_kernel" if cfg["dtype"] == "f32" else
+                     "kernel": ("quad_kernel" if shared and cfg["dtype"] == "f32" else
+                                "fwd_group_kernel" if shared else "f32_kernel" if cfg["dtype"] == "f32" else
                                 "fwd_direct_kernel" if tiles["row_block"] == 0 else "fwd_int_kernel"),
                      "kernel_ms": k_avg, "kernel_ms_median": k_med,
                      "instruction_form": form[0],
-                     "peak_instruction_form": VALU_PEAK_TOPS * form[1],
-                     "frac_instruction_form": achieved / (VALU_PEAK_TOPS * form[1])},
+                     "peak_instruction_form": VALU_PEAK_TOPS * form[1] if form[1] else None,
+                     "frac_instruction_form": achieved / (VALU_PEAK_TOPS * form[1]) if form[1] else None},
         "lds_roofline": None if form[2] == 0 else {
             "achieved": achieved * form[2], "peak": LDS_PEAK_TBS, "unit": "TB/s",
             "frac": achieved * form[2] / LDS_PEAK_TBS, "bytes_per_add": form[2]},
@@ -965,7 +992,7 @@ def main():
         "clocks": clocks.report(),
         "host": host_cpu(),
     }
-    if tiles["row_block"] == 0 and cfg["dtype"] != "f32":
+    if tiles["row_block"] == 0 and cfg["dtype"] != "f32" and not shared:
         # The direct-read kernel loads 16 bytes per 16 samples of 8-bit (or 32 of 4-bit) input from
         # L1/L2 for every (channel, DM) pair (the word after them comes from the next lane); lane 63
         # of each wave loads a window only for lane 62 and outputs nothing, so 64 loads per 63.

@@ -220,8 +220,16 @@ dd_status dd_execute_adjoint(const dd_plan *plan, const float *d_y, int64_t y_pi
  * their spread; or the choice recorded for an identical plan in the tuning
  * cache (below).
  *
+ * Until tiles are chosen explicitly (dd_plan_set_tiles, or an autotune or cache line that
+ * picks another shape than the default), a direction whose neighbouring rows share few
+ * delay patterns runs by shared sums instead of its shape's kernel: partial sums over
+ * groups of neighbouring channels (integer input) or of four rows (float input) are
+ * computed once per pattern.  The results are the same; dd_plan_shares_sums tells which.
+ *
  * direction: 0 = forward; 1 = adjoint (DD_F32 plans only).
  *
+ * dd_plan_shares_sums: 1 if `direction` runs by shared sums, else 0 (also for a null plan
+ *   or another direction).
  * dd_plan_shape_count: number of compiled shapes for the plan's dtype.
  * dd_plan_get_tiles: current choice for `direction`.
  * dd_plan_set_tiles: rebuild the plan's tables for compiled shape `shape` and
@@ -248,6 +256,7 @@ dd_status dd_execute_adjoint(const dd_plan *plan, const float *d_y, int64_t y_pi
  *   Errors: DD_ERR_ARG, DD_ERR_ALIGN, DD_ERR_DTYPE, DD_ERR_HIP (plan unbound then).
  */
 dd_status dd_plan_shape_count(const dd_plan *plan, int32_t *n);
+int32_t dd_plan_shares_sums(const dd_plan *plan, int32_t direction);
 dd_status dd_plan_get_tiles(const dd_plan *plan, int32_t direction, dd_tiles *tiles);
 dd_status dd_plan_set_tiles(dd_plan *plan, int32_t direction, int32_t shape, int32_t order);
 dd_status dd_plan_autotune(dd_plan *plan, int32_t direction, const void *d_src, float *d_dst, int64_t pitch,

@@ -77,6 +77,8 @@ _lib.dd_execute_adjoint.argtypes = [_vp, _vp, _i64, _vp, _vp]
 _lib.dd_execute_adjoint.restype = _i32
 _lib.dd_plan_shape_count.argtypes = [_vp, ctypes.POINTER(_i32)]
 _lib.dd_plan_shape_count.restype = _i32
+_lib.dd_plan_shares_sums.argtypes = [_vp, _i32]
+_lib.dd_plan_shares_sums.restype = _i32
 _lib.dd_plan_get_tiles.argtypes = [_vp, _i32, ctypes.POINTER(Tiles)]
 _lib.dd_plan_get_tiles.restype = _i32
 _lib.dd_plan_set_tiles.argtypes = [_vp, _i32, _i32, _i32]
@@ -214,6 +216,10 @@ class Plan:
         t = Tiles()
         _check(_lib.dd_plan_get_tiles(self._h, int(direction), ctypes.byref(t)), "dd_plan_get_tiles")
         return t.as_dict()
+
+    def shares_sums(self, direction=0) -> bool:
+        """Whether the forward (0) or adjoint (1) runs by shared sums instead of its shape's kernel."""
+        return bool(_lib.dd_plan_shares_sums(self._h, int(direction)))
 
     def set_tiles(self, direction, shape, order=0, stream=None):
         """Switch to compiled shape `shape` with workgroup order `order` and re-bind."""

@@ -116,6 +116,11 @@ dd_status dd_plan_shape_count(const dd_plan *p, int32_t *n) {
   return DD_OK;
 }
 
+int32_t dd_plan_shares_sums(const dd_plan *p, int32_t dir) {
+  if (!p || (dir != 0 && dir != 1)) return 0;
+  return p->desc.dtype == DD_F32 ? p->qtab[dir].use : dir == 0 && p->gtab.use;
+}
+
 dd_status dd_plan_get_tiles(const dd_plan *p, int32_t dir, dd_tiles *t) {
   if (!p || !t) return fail(DD_ERR_ARG, "null argument");
   if (dir == 1 && p->desc.dtype != DD_F32) return fail(DD_ERR_DTYPE, "the adjoint is defined for float32 plans only");
