@@ -94,6 +94,12 @@ def test_corner_turn_tile_runs(n_ctiles, n_ttiles, dd):
     _check_turn(dd, "u8", 256 * n_ctiles - 3, 128 * n_ttiles - 6, seed=100 * n_ctiles + n_ttiles)
 
 
+@pytest.mark.parametrize("n_samp", [32 * 25 - 4, 32 * 25 - 8])
+def test_corner_turn_float_rows_on_lines(n_samp, dd):
+    """Float rows whose pitch is a multiple of 128 bytes (800 floats) and one that is not."""
+    _check_turn(dd, "f32", 64 * 5 - 1, n_samp, seed=n_samp)
+
+
 def _survey_args(cfg, n_samp):
     return (cfg["n_chan"], n_samp, cfg["dtype"], cfg["f_high"], cfg["chan_bw"], cfg["t_samp"], cfg["ranges"])
 
