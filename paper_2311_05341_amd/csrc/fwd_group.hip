@@ -23,8 +23,8 @@
 // chunk of a pattern row, later samples come from lane i + 1 (DPP; lane 63 only
 // loads).
 //
-// Bound by instruction issue: on 8192 ch x 2^17 x 500 DMs (8-bit) the vector units
-// are 57% busy, LDS 33%, and waves wait half their time for the barrier or for issue.
+// Bound by instruction issue: on 8192 ch x 2^20 x 4000 DMs (8-bit) the vector units
+// are 67% busy, LDS 58%, and waves wait 39% of their time.
 // Measured (8-bit 8192 ch x 2^20 x 4000 DMs): 353 ms, 94 Tadds/s, against 820 ms for
 // the staged kernel.  What mattered, on the way there: branches (a branch-free move
 // and one load site per operation: 464 -> 400 ms; waves specialised into builders and
