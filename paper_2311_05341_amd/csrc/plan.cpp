@@ -471,6 +471,12 @@ static void choose_quads(dd_plan &p, int dir) {
   if (!rows || !build_quad_tables(sh, rows, &q) ||
       q.data.size() * 4 > up256(t.offs.size() * 2) + up256(t.sbase.size() * 4))  // (they take those tables' place)
     return;
+  // Orders, measured on 1024 ch x 135212 x 512 DMs of step 0.5, the same of step 0.1 and 512
+  // ch x 33576 x 200 (two rounds of workgroups).  Forward, by tiles per XCD / groups of
+  // blocks / runs of tiles / tiles first: 2157 / 2258 / 2397 / 2417, 1607 / 1707 / 1796 /
+  // 1822 and 177 / 174 / 179 / 174 us.  Adjoint: 2218 / 2245 / 2177 / 2171, 1633 / 1706 /
+  // 1706 / 1715 and 164 / 173 / 154 / 152 us; 1024 ch x 2^17 x 1024: 4885 / 4817 / 4743 / 4751.
+  q.order = dir ? kOrderXcdRuns : q.n_blk * tiles > 2 * (int64_t)kCus ? kOrderXcdTiles : kOrderDmGroups;
   q.use = true;
   p.qtab[dir] = std::move(q);
 }

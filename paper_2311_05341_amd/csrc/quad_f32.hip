@@ -316,11 +316,10 @@ int launch_quad(const QuadTables &q, const void *tables, const float *x, int64_t
   hipError_t e = hipFuncSetAttribute(fn, hipFuncAttributeMaxDynamicSharedMemorySize, lds);
   if (e != hipSuccess) return (int)e;
   const dim3 grid((unsigned)(tiles * q.n_blk)), block(64 * kQuadWaves);
-  const int order = 2;  // a few blocks share each tile's rows in an XCD's L2 (tile_order.h)
   if (q.rows == 64)
-    hipLaunchKernelGGL(quad_kernel<64 / kQuadWaves>, grid, block, lds, (hipStream_t)stream, a, (int)tiles, order);
+    hipLaunchKernelGGL(quad_kernel<64 / kQuadWaves>, grid, block, lds, (hipStream_t)stream, a, (int)tiles, q.order);
   else
-    hipLaunchKernelGGL(quad_kernel<32 / kQuadWaves>, grid, block, lds, (hipStream_t)stream, a, (int)tiles, order);
+    hipLaunchKernelGGL(quad_kernel<32 / kQuadWaves>, grid, block, lds, (hipStream_t)stream, a, (int)tiles, q.order);
   return (int)hipGetLastError();
 }
 

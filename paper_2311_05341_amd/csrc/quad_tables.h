@@ -49,6 +49,7 @@ struct QuadBlock {
 // idle), sums: [n_blk][wave][n_quads][rows / 16] uint16 LDS words of the outputs' windows.
 struct QuadTables {
   bool use = false;
+  int order = 0;              // TileOrder
   int rows = 0, n_blk = 0;    // outputs per block (32 or 64), blocks
   int n_quads = 0;            // padded to a multiple of 2
   uint32_t op_off = 0, sum_off = 0;  // word offsets of the operation blocks and the sums
