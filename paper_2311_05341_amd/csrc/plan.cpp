@@ -448,7 +448,7 @@ static void choose_group_sums(dd_plan &p) {
 // of one workgroup per CU, is below 0.62 of the other kernel's (kRate: additions per CU
 // clock; 22.7 measured on 1024 ch x 131900 x 512 DMs).  At 1200-1500 MHz, quad sums against
 // the other kernel by what the model says: 0.26-0.40 of it: 0.35-0.57 measured (that plan's
-// forward: 1706 against 4919 us); 0.41-0.53: 0.41-0.73; 0.58-0.62: 0.77-0.93; 0.64 (512 ch x
+// forward: 1618 against 4919 us); 0.41-0.53: 0.41-0.73; 0.58-0.62: 0.77-0.93; 0.64 (512 ch x
 // 35996 x 200 DMs of step 1, 256 ch x 16944 x 70): 1.14 and 1.26, since steps of one or two
 // quads wait at their barriers.
 static void choose_quads(dd_plan &p, int dir) {

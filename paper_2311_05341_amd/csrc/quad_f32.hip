@@ -13,7 +13,7 @@
 // stage rows read one per row (they run at 80% of it).  Bound by instruction issue and the
 // barriers: on 1024 ch x 2^17 x 1024 DMs (6 patterns of 770 words per quad) LDS is 45% busy,
 // vector units 45%.  Forward and adjoint of that plan: 17.0 ms by staged rows, 8.8 by quad
-// sums; 1024 ch x 131900 x 512 DMs of step 0.1: 9.6 and 3.4.  On the way there: windows
+// sums; 1024 ch x 131900 x 512 DMs of step 0.1: 9.6 and 3.3.  On the way there: windows
 // loaded when a pattern needs them, one pattern after another: 10.9; a stream loaded ahead
 // with a bounded descriptor per operation: 13.4, without where the block's windows lie
 // inside their rows: 10.8; rows taken over by one asm branch instead of the compiler's
