@@ -192,7 +192,7 @@ __device__ __forceinline__ void f32_tile(uint8_t *lds, const FArgs &a, int oblk,
   for (int q = 0; q < CB * NOW; ++q) ow[q] = scalar_load(woffs, q);
 
   const uint8_t *lane_base = lds + 4 * lane;
-  // One block; U: its place among the blocks of a quad (-1: any).
+  // One block; U: its place among the blocks of a whole quad (-1: any).
   static_assert(CB >= 4 || (R == 1 && (CB == 1 || NW == 16)), "one quad open per wave");
   auto block = [&](int b, auto uc) {
     constexpr int U = decltype(uc)::value;
@@ -214,16 +214,22 @@ __device__ __forceinline__ void f32_tile(uint8_t *lds, const FArgs &a, int oblk,
 #pragma unroll
       for (int j = 0; j < NS; ++j) dst[j] = p[64 * j];
     };
-    read_pair(0, wv[0]);
-    if constexpr (U < 0) {  // CB = 1, any place
+    if constexpr (U < 0) {
+      int q = 0;
+      if (b * CB % 4 == 0) {
+        read_pair(0, quad);
+        asm volatile("; the first row of a quad");  // (keeps the branches apart)
+        q = 1;
+      }
+      if (CB > 1 || q == 0) {
+        for (; q < CB; ++q) {
+          read_pair(q, wv[0]);
 #pragma unroll
-      for (int j = 0; j < NS; ++j) quad[j] += wv[0][j];
-      if (b % 4 == 3 || b + 1 == nblk)
-#pragma unroll
-        for (int j = 0; j < NS; ++j) {
-          part[0][j] += quad[j];
-          quad[j] = 0.0f;
+          for (int j = 0; j < NS; ++j) quad[j] += wv[0][j];
         }
+      }
+    } else {
+      read_pair(0, wv[0]);
     }
 #pragma unroll
     for (int q = 0; U >= 0 && q < CB * R; ++q) {
@@ -235,17 +241,18 @@ __device__ __forceinline__ void f32_tile(uint8_t *lds, const FArgs &a, int oblk,
         if (c == 3) part[r][j] += quad[j];
       }
     }
-    if (U >= 0 && QR < 4 && U * CB + CB < 4 && b + 1 == nblk)  // the rows end inside a quad
+    if (U < 0 ? (b + 1) * CB % 4 == 0 : (U + 1) * CB % 4 == 0) {  // the end of a quad
+      if constexpr (U < 0)
 #pragma unroll
-      for (int j = 0; j < NS; ++j) part[0][j] += quad[j];
-    if (((b + 1) * CB) % 32 == 0 || b + 1 == nblk) {  // end of a group of 32 rows
+        for (int j = 0; j < NS; ++j) part[0][j] += quad[j];
+      if ((b + 1) * CB % 32 == 0)  // the end of a group of 32 rows
 #pragma unroll
-      for (int r = 0; r < R; ++r)
+        for (int r = 0; r < R; ++r)
 #pragma unroll
-        for (int j = 0; j < NS; ++j) {
-          tot[r][j] += part[r][j];
-          part[r][j] = 0.0f;
-        }
+          for (int j = 0; j < NS; ++j) {
+            tot[r][j] += part[r][j];
+            part[r][j] = 0.0f;
+          }
     }
     // Scalar loads for the next iteration (its offsets, the stage bases of the
     // block it stages), after this block's LDS reads: LDS and scalar loads
@@ -255,18 +262,32 @@ __device__ __forceinline__ void f32_tile(uint8_t *lds, const FArgs &a, int oblk,
     for (int q = 0; q < CB * NOW; ++q) ow[q] = scalar_load(woffs, oi + q);
     stage_bases<MAXT>(a, sb, (b + kRing) * CB, dp, bases);
   };
-  // The blocks of a quad in a row of code each (the 4-wave shapes' loads leave no scalar
-  // registers for that: 1813 against 1517 us on 256 ch x 132132 x 64 DMs).
+  // The blocks of a quad in a row of code each, without a look at where the rows end: that
+  // look after every block made the one-row shapes of 16 waves 4 to 9% slower than sums
+  // without quads (1024 ch x 60000 x 256 DMs: 5104 us without quads, 5398 with the look, 4902
+  // so; two-row blocks: 3063, 2887, 2795).  The 4-wave shapes' loads leave no scalar registers
+  // for four blocks in a row (256 ch x 132132 x 64 DMs: 1813 against 1517 us); theirs branch
+  // on the place in the quad, at 1.005 of the time without quads.
   constexpr int kBlocks = CB >= 4 || NW < 16 ? 1 : 4 / CB;
-  for (int b = 0; b < nblk; b += kBlocks) {
-    block(b, std::integral_constant<int, CB < 4 && kBlocks == 1 ? -1 : 0>());
-    if constexpr (kBlocks >= 2)
-      if (b + 1 < nblk) block(b + 1, std::integral_constant<int, 1>());
+  constexpr int kAny = CB < 4 && kBlocks == 1 ? -1 : 0;
+  int b = 0;
+  for (; b + kBlocks <= nblk; b += kBlocks) {
+    block(b, std::integral_constant<int, kAny>());
+    if constexpr (kBlocks >= 2) block(b + 1, std::integral_constant<int, 1>());
     if constexpr (kBlocks == 4) {
-      if (b + 2 < nblk) block(b + 2, std::integral_constant<int, 2>());
-      if (b + 3 < nblk) block(b + 3, std::integral_constant<int, 3>());
+      block(b + 2, std::integral_constant<int, 2>());
+      block(b + 3, std::integral_constant<int, 3>());
     }
   }
+  if constexpr (kBlocks > 1)
+    for (; b < nblk; ++b) block(b, std::integral_constant<int, -1>());
+  if (CB < 4 && nblk * CB % 4)  // the rows end inside a quad
+#pragma unroll
+    for (int j = 0; j < NS; ++j) part[0][j] += quad[j];
+#pragma unroll
+  for (int r = 0; r < R; ++r)
+#pragma unroll
+    for (int j = 0; j < NS; ++j) tot[r][j] += part[r][j];
   wait_vmcnt<0>();
   lds_barrier();
 

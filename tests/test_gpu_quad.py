@@ -91,3 +91,27 @@ def test_replayed_graph(dd):
         torch.cuda.synchronize()
         y = plan.forward(x)
         assert torch.equal(out[:, : plan.n_out], y) and torch.equal(grad, plan.adjoint(y)[:, :20000])
+
+
+# rows that end one, two or three into a quad, with and without whole fours and 32s before them
+@pytest.mark.parametrize("n_chan", [1, 2, 3, 5, 34, 63, 67, 129])
+def test_every_shape_where_rows_end_inside_a_quad(dd, n_chan):
+    cfg = dict(dtype="f32", n_chan=n_chan, n_samp=3000, f_high=1500.0, chan_bw=300.0 / n_chan, t_samp=256e-6,
+               dm_start=0.0, dm_step=0.5, n_dm=n_chan + 2)
+    s = oracle_table(cfg)
+    rng = np.random.default_rng(n_chan)
+    x = rng.standard_normal((n_chan, 3000)).astype(np.float32)
+    plan = plan_for(dd, cfg)
+    y = rng.standard_normal((plan.n_dm, plan.n_out)).astype(np.float32)
+    xd, yd = torch.from_numpy(x).cuda(), torch.from_numpy(y).cuda()
+    want, ab = oracle.forward_f32(x, 3000, s)
+    wantg, abg = oracle.adjoint(y, n_chan, 3000, s), oracle.adjoint(np.abs(y), n_chan, 3000, s)
+    first = [None, None]
+    for shape in range(plan.n_shapes):
+        for d in (0, 1):
+            plan.set_tiles(d, shape, 0)
+            got = (plan.adjoint(yd) if d else plan.forward(xd)).cpu().numpy()[:, : 3000 if d else plan.n_out]
+            w, a, n = (wantg, abg, plan.n_dm) if d else (want, ab, n_chan)
+            assert np.all(np.abs(got.astype(np.float64) - w) <= (n + 32) * EPS * a + 1e-30), (shape, d)
+            first[d] = got if first[d] is None else first[d]
+            assert np.array_equal(got, first[d]), (shape, d)
