@@ -33,7 +33,7 @@ struct Block {
   std::vector<uint32_t> sum;
   int n_steps = 0;
   int64_t lo = INT64_MAX, hi = INT64_MIN;
-  double cost = 0;
+  double cost = 0, work = 0;  // GroupTables
   int lds = 0;
   bool ok = true;
 };
@@ -306,7 +306,7 @@ void build_block(const Input &in, int blk, bool cost_only, Block *b) {
     struct Task {
       int part, chunk;
     };
-    double best = 1e300;
+    double best = 1e300, best_simd = 0;
     std::vector<uint32_t> best_ops;
     std::vector<Part> best_parts;
     std::vector<int> best_wave;
@@ -340,6 +340,7 @@ void build_block(const Input &in, int blk, bool cost_only, Block *b) {
       const double cost = *std::max_element(load, load + kGrpWaves) + kCostShared * total / kGrpWaves;
       if (cost < best) {
         best = cost;
+        best_simd = *std::max_element(simd, simd + 4);
         best_ops.assign(b->ops.begin() + ops_mark, b->ops.end());
         best_parts = std::move(parts);
         best_tasks = std::move(tasks);
@@ -347,6 +348,7 @@ void build_block(const Input &in, int blk, bool cost_only, Block *b) {
       }
       b->ops.resize(ops_mark);
     }
+    b->work += best_simd;
     b->ops.insert(b->ops.end(), best_ops.begin(), best_ops.end());
     size_t mark[kGrpWaves];
     for (int w = 0; w < kGrpWaves; ++w) mark[w] = b->rec[w].size();
@@ -435,6 +437,8 @@ bool build_group_tables(const int32_t *shift, int n_dm, int n_chan, int bits, in
       t->head.lo = std::min(t->head.lo, b.lo);
       t->head.hi = std::max(t->head.hi, b.hi);
       t->cost += b.cost;
+      t->work += b.work;
+      t->max_work = std::max(t->max_work, b.work);
       t->lds_bytes = std::max(t->lds_bytes, b.lds);
     }
     if (max_cost > 0 && t->cost > max_cost) return false;
@@ -461,7 +465,6 @@ bool build_group_tables(const int32_t *shift, int n_dm, int n_chan, int bits, in
       std::copy(blocks[b].ops.begin(), blocks[b].ops.end(), t->data.begin() + t->head.op_off + oo);
       oo += blocks[b].ops.size();
       g.sum_first = (uint32_t)so;
-      g.n_steps = (uint32_t)blocks[b].n_steps;
       g.n_steps = (uint32_t)blocks[b].n_steps;
       std::copy(blocks[b].sum.begin(), blocks[b].sum.end(), t->data.begin() + t->head.sum_off + so);
       so += blocks[b].sum.size();

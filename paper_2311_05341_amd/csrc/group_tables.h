@@ -87,7 +87,8 @@ struct GroupTables {
   std::vector<uint32_t> data;  // GroupHead, [n_blk] GroupBlock, records, operation blocks, sum entries
   GroupHead head = {};
   int lds_bytes = 0;           // of both sets
-  double cost = 0;             // modelled CU clocks for all blocks, per time tile
+  double cost = 0;             // modelled CU clocks for all blocks, per time tile, from the patterns alone
+  double work = 0, max_work = 0;  // building instructions of the busiest SIMD, step by step: all blocks, the largest
 };
 
 // Tables for shift[n_dm][n_chan] (never decreasing with d) and samples of

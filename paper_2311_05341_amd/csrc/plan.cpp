@@ -406,18 +406,36 @@ static dd_status choose_shapes(dd_plan &p) {
 
 static size_t up256(size_t v) { return (v + 255) / 256 * 256; }
 
+// Modelled us of a launch: `longest` and `mean` of its workgroups, `rounds` of resident ones.
+// Past the first round, workgroups in different phases overlap.
+static double launch_us(double longest, double mean, double rounds, double overlap, double tail) {
+  return rounds <= 1 ? longest : std::max(longest, overlap * mean * (rounds + tail));
+}
+
 // Whether an integer plan's forward runs by group sums (fwd_group.hip) instead of
-// its shape's kernel: where the modelled time is smaller by a tenth (the model is
-// good to that; plans near the line run equally fast either way: 210 against 206 us
-// on one).  Both run in rounds of resident workgroups (256 CUs): group sums one per
-// CU, the other kernels two of 32 rows x 512 samples.  kModel: the group kernel's
-// measured time against its model (8192 ch x 2^20 x 4000 DMs 8-bit: 353 ms against 513;
-// 1024 ch x 101773 x 700: 1.09 against 1.48); rate: additions per CU clock of the other
-// kernels (8-bit 40.8 Tadds/s on the 8-wave staged shape, 33-34 on the others; 4-bit 50;
-// 16-bit 30 and 17).  On the two plans above, 4-bit 8192
-// ch x 2^18 x 500 and 16-bit the same, group sums against the other kernels: 353 / 820,
-// 1.09 / 1.78, 13.1 / 22.4 and 21.7 / 37.7 ms; 128 ch x 32768 x 256 DMs of step 1 (28
-// patterns per 8 channels) stays: 42 against 36 us.
+// its shape's kernel.  Two models in turn:
+//
+// From the patterns alone (max_cost), before any tables are built: where group sums cannot
+// come out a tenth ahead.  Both kernels run in rounds of resident workgroups (256 CUs): group
+// sums one per CU, the other kernels two of 32 rows x 512 samples.  kModel: the group
+// kernel's measured time against this model (8192 ch x 2^20 x 4000 DMs 8-bit: 353 ms
+// against 513; 1024 ch x 101773 x 700: 1.09 against 1.48); rate: additions per CU clock of
+// the other kernels (8-bit 40.8 Tadds/s on the 8-wave staged shape, 33-34 on the others;
+// 4-bit 50; 16-bit 30 and 17).  This model is rough: it is up to 5 times off where a plan has few
+// channels or workgroups, and refuses 128 ch x 32768 x 256 DMs of step 1 (42 us against 36)
+// by far more than that.
+//
+// From the tables: a workgroup of group sums takes a start of 9 us (16-bit: 11) and about
+// 8 clocks per building instruction of its busiest SIMD, step by step; one of the other
+// kernels a start and a time per channel, less where a CU has only one of them.  Constants
+// fitted to 1160 plans (32-4096 ch, 16-1500 DMs of step 0.02-2, 2000-300000 outputs at
+// 1200-1550 MHz), timed both ways: group sums to 7-10%, the others to 5-9%.  Without this
+// model 128 of 593 8-bit plans of that set ran by group sums that are up to 1.86 times as
+// slow as their shape (200 ch x 82109 x 116 DMs: 98 against 78 us), 19 of 259 4-bit and 5 of 241
+// 16-bit ones up to 1.31 and 1.39; with it 5, none and 1, at most 1.07, and 21 that would gain 2%
+// or more (one 22%, the others up to 17%) run their shape.  On the two plans above, 4-bit 8192 ch x
+// 2^18 x 500 and 16-bit the same, group sums against the other kernels: 353 / 820, 1.09 /
+// 1.78, 13.1 / 22.4 and 21.7 / 37.7 ms.
 static void choose_group_sums(dd_plan &p) {
   if (p.desc.dtype == DD_F32) return;
   const double kModel = 0.74, kCus = 256;
@@ -425,22 +443,42 @@ static void choose_group_sums(dd_plan &p) {
   const bool best_staged = !is_direct(p.fwd) && p.fwd.waves == 8;
   const double rate = bits == 4 ? 80.0 : bits == 16 ? (best_staged ? 47.0 : 27.0) : best_staged ? 64.0 : 53.0;
   const int64_t tile = bits == 16 ? kGrpWin : 2 * kGrpWin;
-  const int64_t n_blk = (p.desc.n_dm + group_rows(bits) - 1) / group_rows(bits);
-  const double groups = ceil((double)n_blk * (double)((p.n_out + tile - 1) / tile) / kCus);
+  const int64_t n_blk = (p.desc.n_dm + group_rows(bits) - 1) / group_rows(bits), tiles = (p.n_out + tile - 1) / tile;
+  const double groups = ceil((double)n_blk * (double)tiles / kCus);
   const double others = ceil((double)((p.desc.n_dm + 31) / 32) * (double)((p.n_out + 511) / 512) / (2 * kCus));
   // the group kernel's rounds at its mean cost per block against the others' rounds, and
   // (a beam of a batch) all its tiles against the plan's additions
   const double round_limit = 0.9 * others * (2.0 * 32 * 512) * p.desc.n_chan / rate / (groups * kModel) * (double)n_blk;
-  const double batch_limit = 0.9 * (double)p.desc.n_dm * (double)p.n_out * p.desc.n_chan / rate / kModel /
-                             (double)((p.n_out + tile - 1) / tile);
+  const double batch_limit = 0.9 * (double)p.desc.n_dm * (double)p.n_out * p.desc.n_chan / rate / kModel / (double)tiles;
   if (!build_group_tables(p.shift.data(), p.desc.n_dm, p.desc.n_chan, bits, p.in_pitch_bytes, &p.gtab,
                           std::max(round_limit, batch_limit)) ||
       p.gtab.data.size() * 4 > table_bytes(p)) {
     p.gtab = GroupTables();
     return;
   }
-  p.gtab.use = p.gtab.cost <= round_limit;
-  p.gtab.batch = p.gtab.cost <= batch_limit;
+  struct Model {
+    double start, op, overlap, tail;  // group sums: us of a workgroup, and per instruction; several rounds
+    int rows;
+    double samples;                   // the other kernel's workgroup, two of which share a CU,
+    double own_start, own_chan, alone, own_overlap, own_tail;  // its us, per channel (share of it where alone on its CU)
+    double batch_start, batch_op, batch_own_start, batch_own_chan;  // the same among many beams
+  };
+  const Model m = bits == 8   ? Model{8.64, 0.00331, 0.665, 1.13, 32, 512, 5.84, 0.229, 0.64, 0.79, 0.72, 7.1, 0.003, 5.8, 0.206}
+                  : bits == 4 ? Model{8.95, 0.00347, 0.687, 1.30, 16, 1008, 9.45, 0.243, 0.82, 0.68, 0.85, 9.0, 0.00286, 7.0, 0.18}
+                              : Model{11.4, 0.00378, 0.864, 0.75, 32, 1024, 7.96, 0.651, 0.65, 0.81, 0.65, 7.7, 0.0028, 6.0, 0.955};
+  const double slow = bits == 4 || best_staged ? 1.0 : bits == 8 ? 1.2 : 1.7;  // staged shapes of 16 waves, direct reads
+  const double wgs = (double)n_blk * (double)tiles, mean_work = p.gtab.work / (double)n_blk;
+  const double own_wgs = ceil((double)p.desc.n_dm / m.rows) * ceil((double)p.n_out / m.samples);
+  const double own_rounds = own_wgs / (2 * kCus), own_wg = m.own_start + m.own_chan * slow * p.desc.n_chan;
+  const double sums_us = launch_us(m.start + m.op * p.gtab.max_work, m.start + m.op * mean_work, wgs / kCus, m.overlap, m.tail);
+  const double own_us = own_rounds <= 0.5 ? m.own_start + m.alone * m.own_chan * slow * p.desc.n_chan
+                                          : launch_us(own_wg, own_wg, own_rounds, m.own_overlap, m.own_tail);
+  p.gtab.use = p.gtab.cost <= round_limit && sums_us < (bits == 4 ? 0.95 : 1.0) * own_us;
+  // a beam of a batch (220 plans as batches of themselves): 2 of 106 8-bit and 10 of 49 4-bit ones
+  // were up to 1.57 times as slow by group sums without this line, 1 and 2 with it
+  p.gtab.batch = p.gtab.cost <= batch_limit && (m.batch_start + m.batch_op * mean_work) * wgs / kCus <
+                                                   0.95 * (m.batch_own_start + m.batch_own_chan * slow * p.desc.n_chan) * own_rounds;
+  if (!p.gtab.use && !p.gtab.batch) p.gtab = GroupTables();
 }
 
 // Whether a direction of a float plan runs by quad sums (quad_f32.hip) instead of its

@@ -1,0 +1,45 @@
+"""Which kernel a plan runs by default, where both were timed (no GPU needed).
+
+``Plan.shares_sums`` tells whether a direction runs by shared sums.  Every row holds a plan, the
+measured us by shared sums and by the plan's own shape, and the faster of the two is the default.
+"""
+import pytest
+
+
+@pytest.fixture(scope="module")
+def dd():
+    import paper_2311_05341_amd as dd
+    return dd
+
+
+def _plan(dd, dtype, n_chan, n_samp, n_dm, start, step, f_high, t_us, band=300.0):
+    per = {"u4": 0.5, "u8": 1, "u16": 2, "f32": 4}[dtype]
+    pitch = (int(n_samp * per) + 15) // 16 * 16
+    return dd.Plan(n_chan, n_samp, dtype, f_high, band / n_chan, t_us * 1e-6, start, step, n_dm, in_pitch_bytes=pitch,
+                   bind=False)
+
+
+# (dtype, channels, samples, trials, dm_start, dm_step, f_high, t_us, shared us, own shape's us)
+INTEGER = [
+    # few workgroups or channels: shared sums start and end slower
+    ("u8", 200, 82109, 116, 300.0, 0.25, 1500.0, 64.0, 97.9, 77.7), ("u8", 256, 4418, 49, 0.0, 0.5, 1500.0, 64.0, 79.9, 42.9),
+    ("u8", 128, 8002, 154, 800.0, 1.0, 1550.0, 256.0, 44.0, 23.3), ("u8", 256, 7092, 240, 800.0, 2.0, 1550.0, 256.0, 79.7, 43.1),
+    ("u4", 160, 17386, 624, 800.0, 0.25, 1550.0, 64.0, 55.3, 40.5), ("u4", 512, 31240, 267, 0.0, 1.0, 1550.0, 128.0, 189.0, 144.4),
+    ("u4", 256, 45918, 171, 50.0, 0.25, 1550.0, 128.0, 90.5, 76.0), ("u16", 32, 107844, 1247, 50.0, 0.02, 1550.0, 64.0, 284.4, 205.2),
+    ("u16", 64, 154472, 96, 800.0, 0.05, 1550.0, 128.0, 64.9, 53.6),
+    # and where they pay
+    ("u8", 512, 118615, 251, 0.0, 0.25, 1550.0, 64.0, 293.0, 434.6), ("u8", 1024, 29844, 616, 50.0, 0.25, 1550.0, 64.0, 365.5, 547.2),
+    ("u8", 768, 164212, 35, 0.0, 0.1, 1550.0, 256.0, 98.9, 254.2), ("u8", 1024, 49254, 162, 0.0, 1.0, 1550.0, 64.0, 239.4, 491.2),
+    ("u4", 200, 48394, 146, 0.0, 0.1, 1500.0, 128.0, 39.1, 59.7), ("u4", 1024, 170480, 175, 50.0, 0.5, 1500.0, 64.0, 615.8, 716.2),
+    ("u16", 128, 102299, 77, 300.0, 0.1, 1500.0, 256.0, 56.4, 87.0), ("u16", 512, 14880, 22, 0.0, 0.02, 1550.0, 128.0, 56.7, 220.6),
+]
+
+
+@pytest.mark.parametrize("row", INTEGER, ids=lambda r: "%s-%d-%d-%d" % r[:4])
+def test_integer_default_is_the_faster_kernel(dd, row):
+    p = _plan(dd, *row[:8])
+    assert p.shares_sums(0) == (row[8] < row[9])
+    assert not p.shares_sums(1)
+    t = p.tiles(0)
+    p.set_tiles(0, t["shape"], t["order"])  # an explicit choice runs that shape's kernel
+    assert not p.shares_sums(0)
