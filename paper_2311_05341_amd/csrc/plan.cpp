@@ -488,7 +488,13 @@ static void choose_group_sums(dd_plan &p) {
 // the other kernel by what the model says: 0.26-0.40 of it: 0.35-0.57 measured (that plan's
 // forward: 1618 against 4919 us); 0.41-0.53: 0.41-0.73; 0.58-0.62: 0.77-0.93; 0.64 (512 ch x
 // 35996 x 200 DMs of step 1, 256 ch x 16944 x 70): 1.14 and 1.26, since steps of one or two
-// quads wait at their barriers.
+// quads wait at their barriers.  Then, with the tables at hand, where it is also faster in a
+// second model: a start per workgroup, a time per record of the busiest SIMD, step by step,
+// and per quad, against the two-outputs-per-wave shapes' start and time per row.  Constants
+// fitted to 658 plans and directions (32-1024 ch, 24-1024 DMs), both kernels to 7%.  Without it 7 of the 633
+// taken were slower by shared sums, up to 1.26 times (adjoint of 200 ch x 66828 x 126 DMs of
+// step 0.5: 198 against 157 us), with it 2 (that one and 1.07), and one that would gain 23% of
+// 33 us runs its shape.
 static void choose_quads(dd_plan &p, int dir) {
   const FloatTables &t = dir ? p.ftab_adj : p.ftab_fwd;
   const double kRate = 23.0, kCus = 256;
@@ -509,6 +515,14 @@ static void choose_quads(dd_plan &p, int dir) {
   if (!rows || !build_quad_tables(sh, rows, &q) ||
       q.data.size() * 4 > up256(t.offs.size() * 2) + up256(t.sbase.size() * 4))  // (they take those tables' place)
     return;
+  if (t.per_wave == 2) {
+    const double start = rows == 64 ? 8.30 : 6.78, rec = rows == 64 ? 0.307 : 0.42, quad = rows == 64 ? 0.255 : 0.071;
+    const double fixed = start + quad * ((sh.n_rows + 3) / 4);
+    const double sums = launch_us(fixed + rec * q.max_records, fixed + rec * q.records / q.n_blk,
+                                  (double)(q.n_blk * tiles) / kCus, 0.9, 0.86);
+    const double own_wg = t.row_block == 8 ? 10.4 + 0.533 * sh.n_rows : 9.0 + 0.61 * sh.n_rows;
+    if (sums > launch_us(own_wg, own_wg, (double)(n_oblk * others_tiles) / kCus, 0.925, 0.82)) return;
+  }
   // Orders, measured on 1024 ch x 135212 x 512 DMs of step 0.5, the same of step 0.1 and 512
   // ch x 33576 x 200 (two rounds of workgroups).  Forward, by tiles per XCD / groups of
   // blocks / runs of tiles / tiles first: 2157 / 2258 / 2397 / 2417, 1607 / 1707 / 1796 /

@@ -68,9 +68,9 @@ bool fill_quad(const QuadShifts &sh, int blk, int rows, int k, Quad *q) {
   return q->bytes() <= kQuadSetBytes;
 }
 
-// Order the patterns so that successive ones differ in few rows; returns the reloads.
-int order_patterns(Quad *q, int rows) {
-  int place[kMaxOutputs], total = 0;
+// Order the patterns so that successive ones differ in few rows.
+void order_patterns(Quad *q, int rows) {
+  int place[kMaxOutputs];
   Pattern out[kMaxOutputs];
   bool used[kMaxOutputs] = {};
   int cur = 0;
@@ -81,12 +81,10 @@ int order_patterns(Quad *q, int rows) {
     int next = -1, best = INT_MAX;
     for (int k = 0; k < q->n_pat; ++k)
       if (!used[k] && changes(q->pat[cur], q->pat[k]) < best) best = changes(q->pat[cur], q->pat[k]), next = k;
-    if (next >= 0) total += best;
     cur = next;
   }
   std::copy_n(out, q->n_pat, q->pat);
   for (int d = 0; d < rows; ++d) q->pat_of[d] = place[q->pat_of[d]];
-  return total;
 }
 
 struct Task {
@@ -128,7 +126,7 @@ size_t task_ops(const Quad &q, int k, int p0, int p1, int n_rows, std::vector<ui
 
 struct Block {
   bool ok = false;
-  double cost = 0;
+  double records = 0;  // QuadTables
   int64_t lo = 0, hi = 64 * quad_lane_words(32);  // (an idle record reads the tile's first samples)
   std::vector<uint32_t> rec[kQuadWaves], steps, ops;  // operation blocks numbered from 1 (0: the idle one)
 };
@@ -143,7 +141,7 @@ void build_block(const QuadShifts &sh, int b, int rows, int nqp, uint16_t *sums,
   for (int k = 0; k < nq; ++k) {
     if (!fill_quad(sh, b, rows, 4 * k, &quads[k])) return;  // (B.ok stays false)
     const Quad &q = quads[k];
-    B.cost += quad_cost(q, rows, order_patterns(&quads[k], rows));
+    order_patterns(&quads[k], rows);
     for (int p = 0; p < q.n_pat; ++p) {
       const auto r = std::minmax({0, q.pat[p].r[0], q.pat[p].r[1], q.pat[p].r[2]});
       B.lo = std::min<int64_t>(B.lo, (int64_t)q.base + r.first);
@@ -160,7 +158,7 @@ void build_block(const QuadShifts &sh, int b, int rows, int nqp, uint16_t *sums,
     std::vector<int> wave, best_wave;
     std::vector<uint32_t> ops, best_ops;
     const size_t op0 = B.ops.size() / kQuadOpWords;
-    size_t best_load = SIZE_MAX;
+    size_t best_load = SIZE_MAX, best_simd = 0;
     for (int split = 1; split <= 4; ++split) {
       todo.clear();
       ops.clear();
@@ -173,17 +171,20 @@ void build_block(const QuadShifts &sh, int b, int rows, int nqp, uint16_t *sums,
         }
       }
       std::stable_sort(todo.begin(), todo.end(), [](const Task &x, const Task &y) { return x.recs > y.recs; });
-      size_t load[kQuadWaves] = {}, total = 0;
+      size_t load[kQuadWaves] = {}, simd[4] = {}, total = 0;
       wave.clear();
       for (const Task &x : todo) {
         const int w = (int)(std::min_element(load, load + kQuadWaves) - load);
         load[w] += x.recs;
+        simd[w & 3] += x.recs;
         total += x.recs;
         wave.push_back(w);
       }
       const size_t v = kQuadWaves * *std::max_element(load, load + kQuadWaves) + total;
-      if (v < best_load) best_load = v, best = todo, best_wave = wave, best_ops = ops;
+      if (v < best_load)
+        best_load = v, best_simd = *std::max_element(simd, simd + 4), best = todo, best_wave = wave, best_ops = ops;
     }
+    B.records += (double)best_simd;
     B.ops.insert(B.ops.end(), best_ops.begin(), best_ops.end());
     uint32_t slot[kQuadStep], at = set / 4;
     for (int k = i; k < j; ++k) {
@@ -270,7 +271,8 @@ bool build_quad_tables(const QuadShifts &sh, int rows, QuadTables *t) {
       if (f) return false;
     for (const Block &B : blocks) {
       if (!B.ok) return false;
-      t->cost += B.cost;
+      t->records += B.records;
+      t->max_records = std::max(t->max_records, B.records);
     }
     size_t n_steps = 0, n_recs = 0, n_ops = kQuadOpWords;
     for (const Block &B : blocks) {

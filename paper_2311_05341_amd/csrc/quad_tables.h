@@ -54,7 +54,7 @@ struct QuadTables {
   int n_quads = 0;            // padded to a multiple of 2
   uint32_t op_off = 0, sum_off = 0;  // word offsets of the operation blocks and the sums
   std::vector<uint32_t> data;
-  double cost = 0;            // modelled CU clocks of all blocks, per tile
+  double records = 0, max_records = 0;  // of the busiest SIMD, step by step: all blocks, the largest
 };
 
 // The plan's delays: output o sums row k at sign * shift[o * out_stride + k * row_stride].
@@ -69,8 +69,8 @@ struct QuadShifts {
   }
 };
 
-// Modelled clocks (QuadTables::cost) for `rows` outputs per block, from two of the blocks;
-// 1e300 where a quad's sums do not fit a set.
+// Modelled CU clocks of all blocks, per tile, for `rows` outputs per block, from two of the
+// blocks' patterns; 1e300 where a quad's sums do not fit a set.
 double guess_quad_cost(const QuadShifts &sh, int rows);
 // false if a quad's sums do not fit a set, or on bad_alloc.
 bool build_quad_tables(const QuadShifts &sh, int rows, QuadTables *t);

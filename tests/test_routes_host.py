@@ -43,3 +43,23 @@ def test_integer_default_is_the_faster_kernel(dd, row):
     t = p.tiles(0)
     p.set_tiles(0, t["shape"], t["order"])  # an explicit choice runs that shape's kernel
     assert not p.shares_sums(0)
+
+
+# (channels, samples, trials, dm_start, dm_step, f_high, t_us, direction, shared us, own shape's us)
+FLOAT = [
+    (200, 28745, 137, 50.0, 1.0, 1550.0, 128.0, 1, 110.0, 94.0), (200, 21952, 258, 800.0, 0.5, 1550.0, 256.0, 1, 187.0, 157.0),
+    (128, 21590, 374, 800.0, 0.1, 1500.0, 128.0, 1, 269.0, 240.0),
+    (1024, 21994, 79, 0.0, 0.1, 1550.0, 256.0, 0, 118.1, 550.5), (1024, 21994, 79, 0.0, 0.1, 1550.0, 256.0, 1, 70.3, 155.4),
+    (512, 44666, 258, 0.0, 1.0, 1550.0, 128.0, 0, 307.0, 560.8), (256, 38454, 246, 50.0, 1.0, 1500.0, 128.0, 1, 236.6, 282.4),
+    (1000, 118215, 512, 300.0, 1.0, 1550.0, 64.0, 1, 3585.6, 4169.1),
+]
+
+
+@pytest.mark.parametrize("row", FLOAT, ids=lambda r: "%d-%d-%d-dir%d" % (r[0], r[1], r[2], r[7]))
+def test_float_default_is_the_faster_kernel(dd, row):
+    p, d = _plan(dd, "f32", *row[:7]), row[7]
+    assert p.shares_sums(d) == (row[8] < row[9])
+    other = p.shares_sums(1 - d)
+    t = p.tiles(d)
+    p.set_tiles(d, t["shape"], t["order"])  # that direction only
+    assert not p.shares_sums(d) and p.shares_sums(1 - d) == other
