@@ -19,16 +19,17 @@
 // conflict-free.  4-bit data (corner_turn_kernel) assemble each output piece
 // from nibble reads.
 //
-// Each XCD takes a contiguous run of time tiles, kCtGroup channel tiles at a time: a row
-// segment rarely starts on a 128-byte line (row pitches are multiples of 16 bytes), and
-// its line is completed by the next time tile's segment in the same L2 instead of
-// reaching HBM in two parts from two XCDs.  Four channel tiles keep the spectra read in
-// runs of 1 KiB and few enough unfinished lines for the L2.  4096 ch x 390000 samples
-// (float: 195000), channel tiles of the whole band fastest over all XCDs / 1 / 4 / 8 / 16
+// Where it pays (corner_order.h), each XCD takes a contiguous run of time tiles, kCtGroup
+// channel tiles at a time: a row segment rarely starts on a 128-byte line (row pitches are
+// multiples of 16 bytes), and its line is completed by the next time tile's segment in the
+// same L2 instead of reaching HBM in two parts from two XCDs.  Four channel tiles keep the
+// spectra read in runs of 1 KiB and few enough unfinished lines for the L2.  4096 ch x 390000
+// samples (float: 195000), channel tiles of the whole band fastest over all XCDs / 1 / 4 / 8 / 16
 // together: 8-bit 901 / 905 / 681 / 716 / 799 us, 16-bit 1513 / 1467 / 1267 / 1324 / 1358,
 // float 1361 / 1401 / 1214 / 1255 / 1255, 4-bit 523 / 500 / 471 / 480 / 475.
 #include <hip/hip_runtime.h>
 
+#include "corner_order.h"
 #include "dd_internal.h"
 #include "tile_order.h"
 
@@ -271,10 +272,8 @@ int launch_ct(const CtArgs &a0, hipStream_t st) {
   const int64_t blocks = n_ttiles * a.n_ctiles;
   if (blocks > 0x7fffffff) return (int)hipErrorInvalidValue;
   a.n_ttiles = (int)n_ttiles;
-  // Row segments that are whole lines need no runs; float spectra are then read a little
-  // faster in order (1024 ch x 100000: 166 us by runs, 158 in order; 2048 x 52350: 171 and
-  // 168), 16-bit ones not (2048 x 52350: 86 and 94), 8-bit the same (40).
-  a.runs = !(DT == DD_F32 && ((uint64_t)a.out | (uint64_t)a.out_pitch) % 128 == 0);
+  constexpr int kBits = DT == DD_U4 ? 4 : DT == DD_U8 ? 8 : DT == DD_U16 ? 16 : 32;
+  a.runs = corner_runs(kBits, a.n_chan, a.n_samp, a.in_pitch, (uint64_t)a.out | (uint64_t)a.out_pitch, G::TC);
   if constexpr (DT == DD_U4)
     hipLaunchKernelGGL(corner_turn_kernel<DT>, dim3((unsigned)blocks), dim3(kCtThreads), 0, st, a);
   else
