@@ -6,8 +6,8 @@
 #include <algorithm>
 #include <climits>
 #include <new>
-#include <system_error>
-#include <thread>
+
+#include "run_parts.h"
 
 namespace dd {
 namespace {
@@ -401,31 +401,18 @@ bool build_group_tables(const int32_t *shift, int n_dm, int n_chan, int bits, in
       if (mid.ok) build_block(in, n_blk - 1, true, &last);
       if (!mid.ok || !last.ok || 0.5 * n_blk * (mid.cost + last.cost) > 1.2 * max_cost) return false;
     }
-    const int nthr = (int)std::min<int64_t>({16, n_blk, std::max<int64_t>(1, work / 512),
+    const int nthr = (int)std::min<int64_t>({kMaxParts, n_blk, std::max<int64_t>(1, work / 512),
                                              std::max(1u, std::thread::hardware_concurrency())});
-    bool bad = false;
-    auto run = [&](int k, bool *failed) {
+    uint8_t failed[kMaxParts] = {};
+    run_parts(nthr, [&](int k) {
       try {
         for (int b = k; b < n_blk; b += nthr) build_block(in, b, false, &blocks[b]);
       } catch (const std::bad_alloc &) {
-        *failed = true;
+        failed[k] = 1;
       }
-    };
-    if (nthr == 1) {
-      run(0, &bad);
-    } else {
-      std::vector<std::thread> th;
-      std::vector<uint8_t> failed(nthr, 0);
-      th.reserve(nthr);
-      for (int k = 0; k < nthr; ++k) try {
-          th.emplace_back(run, k, (bool *)&failed[k]);
-        } catch (const std::system_error &) {  // no more threads: here then
-          run(k, (bool *)&failed[k]);
-        }
-      for (auto &x : th) x.join();
-      for (uint8_t f : failed) bad |= f != 0;
-    }
-    if (bad) return false;
+    });
+    for (uint8_t f : failed)
+      if (f) return false;
     size_t recs = 0, ops = kGrpBlockWords, sums = 0;
     t->head.lo = 0;  // the idle operation block loads the tile's own samples of channel 0
     t->head.hi = kGrpChunk + 12;

@@ -15,9 +15,9 @@
 #include <algorithm>
 #include <climits>
 #include <new>
-#include <thread>
 
 #include "dd_internal.h"
+#include "run_parts.h"
 
 namespace dd {
 
@@ -59,19 +59,10 @@ dd_status build_shift_table(dd_plan &p) {
     }
   };
   const size_t work = (size_t)nd * nc;
-  int nthr = work < (1u << 20) ? 1 : (int)std::min<unsigned>(16, std::max(1u, std::thread::hardware_concurrency()));
-  if (nthr == 1) {
-    rows(0, nd, &bad);
-  } else {
-    std::vector<std::thread> th;
-    std::vector<int> flags(nthr, 0);
-    for (int i = 0; i < nthr; ++i) {
-      int lo = (int)((int64_t)nd * i / nthr), hi = (int)((int64_t)nd * (i + 1) / nthr);
-      th.emplace_back(rows, lo, hi, &flags[i]);
-    }
-    for (auto &x : th) x.join();
-    for (int f : flags) bad |= f;
-  }
+  int nthr = work < (1u << 20) ? 1 : (int)std::min<unsigned>(kMaxParts, std::max(1u, std::thread::hardware_concurrency()));
+  int flags[kMaxParts] = {};
+  run_parts(nthr, [&](int i) { rows((int)((int64_t)nd * i / nthr), (int)((int64_t)nd * (i + 1) / nthr), &flags[i]); });
+  for (int f : flags) bad |= f;
   if (bad) return fail(DD_ERR_RANGE, "a shift does not fit in int32");
   // The kernels rely on delays never decreasing with d (each DM block is
   // staged from its first row's delays); Eq. 1 with dm_step >= 0 and

@@ -6,8 +6,8 @@
 #include <algorithm>
 #include <climits>
 #include <new>
-#include <system_error>
-#include <thread>
+
+#include "run_parts.h"
 
 namespace dd {
 namespace {
@@ -248,25 +248,16 @@ bool build_quad_tables(const QuadShifts &sh, int rows, QuadTables *t) {
   try {
     std::vector<Block> blocks(n_blk);
     std::vector<uint16_t> sums((size_t)n_blk * kQuadWaves * nqp * per_wave, 0);
-    const int nthr = (int)std::min<int64_t>({16, n_blk, std::max<int64_t>(1, (int64_t)n_blk * nq / 512),
+    const int nthr = (int)std::min<int64_t>({kMaxParts, n_blk, std::max<int64_t>(1, (int64_t)n_blk * nq / 512),
                                              std::max(1u, std::thread::hardware_concurrency())});
-    std::vector<uint8_t> failed(nthr, 0);
-    auto run = [&](int k) {
+    uint8_t failed[kMaxParts] = {};
+    run_parts(nthr, [&](int k) {
       try {
         for (int b = k; b < n_blk; b += nthr) build_block(sh, b, rows, nqp, sums.data(), &blocks[b]);
       } catch (const std::bad_alloc &) {
         failed[k] = 1;
       }
-    };
-    std::vector<std::thread> th;
-    th.reserve(nthr);
-    for (int k = 1; k < nthr; ++k) try {
-        th.emplace_back(run, k);
-      } catch (const std::system_error &) {  // no more threads: here then
-        run(k);
-      }
-    run(0);
-    for (auto &x : th) x.join();
+    });
     for (uint8_t f : failed)
       if (f) return false;
     for (const Block &B : blocks) {
