@@ -8,6 +8,7 @@
 #include <string.h>
 
 #include <algorithm>
+#include <memory>
 #include <new>
 #include <numeric>
 #include <string>
@@ -41,6 +42,8 @@ struct dd_batch {
   std::vector<int> shape;         // per beam (original index): its shape
   std::vector<char> sums;         // per beam: it runs by group sums (beams at their default shape)
   std::vector<IntTables> tables;  // per beam (original index), for its shape (empty for direct-read and group sums)
+  std::vector<signed char> pay;   // per beam: whether group sums pay (-1: not looked at)
+  std::vector<std::shared_ptr<const GroupTables>> gtabs;  // per beam: their table where its plan holds none
   std::vector<int> order;         // beams in decreasing per-item cost
   std::vector<BatchGroup> groups;
   std::vector<BeamDesc> descs;    // group after group, each group's beams in cost order
@@ -99,7 +102,7 @@ static dd_status batch_assign(dd_batch *b, const Assignment &as) {
   std::vector<IntTables> tabs(n);
   for (int i = 0; i < n; ++i) {
     const dd_plan &p = *b->plans[i];
-    if (as.sums[i]) continue;  // reads the plan's group-sum table
+    if (as.sums[i]) continue;  // reads its group-sum table
     if (direct_shape(shapes[i])) {  // reads the plan's shift table; its descriptors stay inside the row pitch
       const int bits = p.desc.dtype == DD_U4 ? 4 : p.desc.dtype == DD_U16 ? 16 : 8;
       if ((int64_t)p.max_shift * bits / 8 >= p.in_pitch_bytes) return fail(DD_ERR_RANGE, "delay exceeds the row pitch");
@@ -188,15 +191,41 @@ static int default_shape(const dd_plan &p) {
   return kNumIntShapes + (p.desc.dtype == DD_U4 ? 1 : 0);
 }
 
-// Every beam at its plan's default: group sums where the plan holds tables for
-// them that pay in a batch, and its tiles were not chosen explicitly.
-static Assignment default_assignment(const dd_batch &b) {
+// Whether beam i runs by group sums unless its plan's tiles were chosen explicitly; found out
+// once, with the table where its plan holds none.
+static bool sums_pay(dd_batch *b, size_t i) {
+  if (b->pay[i] >= 0) return b->pay[i] > 0;
+  const dd_plan *p = b->plans[i];
+  const size_t first = std::find(b->plans.begin(), b->plans.end(), p) - b->plans.begin();
+  if (first < i) {
+    b->pay[i] = sums_pay(b, first);
+    b->gtabs[i] = b->gtabs[first];
+  } else {
+    try {
+      auto t = std::make_shared<GroupTables>();
+      b->pay[i] = build_group_sums(*p, true, t.get());
+      b->gtabs[i] = std::move(t);
+    } catch (const std::bad_alloc &) {
+      b->pay[i] = 0;
+    }
+  }
+  return b->pay[i] > 0;
+}
+
+// Every beam at its plan's default.
+static Assignment default_assignment(dd_batch *b) {
   Assignment as;
-  for (const dd_plan *p : b.plans) {
-    as.shapes.push_back(default_shape(*p));
-    as.sums.push_back(p->gtab.batch);
+  for (size_t i = 0; i < b->plans.size(); ++i) {
+    as.shapes.push_back(default_shape(*b->plans[i]));
+    as.sums.push_back(!b->plans[i]->chosen && sums_pay(b, i));
   }
   return as;
+}
+
+// The table of a beam that runs by group sums.
+static const std::vector<uint32_t> &group_data(const dd_batch &b, int i) {
+  const dd_plan &p = *b.plans[i];
+  return p.gtab.data.empty() ? b.gtabs[i]->data : p.gtab.data;
 }
 
 static void fill_tiles(int s, dd_tiles *t) {
@@ -250,7 +279,9 @@ dd_status dd_batch_create(const dd_plan *const *plans, int32_t n, dd_batch **out
     off += sbb;
   }
   b->ws_bytes = off;
-  const dd_status st = batch_assign(b, default_assignment(*b));
+  b->pay.assign(n, -1);
+  b->gtabs.resize(n);
+  const dd_status st = batch_assign(b, default_assignment(b));
   if (st != DD_OK) { delete b; return st; }
   *out = b;
   return DD_OK;
@@ -291,7 +322,7 @@ dd_status dd_batch_bind(dd_batch *b, const void *const *d_in, float *const *d_ou
   e = hipMemcpyAsync(base + descs_offset(), b->descs.data(), sizeof(BeamDesc) * n, hipMemcpyHostToDevice, st);
   for (int i = 0; i < n && e == hipSuccess; ++i) {
     if (b->sums[i]) {
-      const std::vector<uint32_t> &t = b->plans[i]->gtab.data;
+      const std::vector<uint32_t> &t = group_data(*b, i);
       e = hipMemcpyAsync(base + b->table_offs[i], t.data(), t.size() * 4, hipMemcpyHostToDevice, st);
       continue;
     }
@@ -436,7 +467,7 @@ dd_status dd_batch_autotune(dd_batch *b, const void *const *d_in, float *const *
   const std::vector<char> none(b->plans.size(), 0);
   std::vector<Assignment> cands;
   cands.push_back(orig);
-  const Assignment defaults = default_assignment(*b);
+  const Assignment defaults = default_assignment(b);
   if (!(defaults == orig)) cands.push_back(defaults);
   if (defaults.sums != none) cands.push_back({defaults.shapes, none});
   for (int s = 0; s < num_batch_shapes(); ++s) {

@@ -70,6 +70,7 @@ struct FloatTables {
   int row_bytes = 0, lds_bytes = 0;
   std::vector<uint16_t> offs;  // [n_oblk][waves][n_rows rounded up to row_block][max(per_wave, 2)]
   std::vector<int32_t> sbase;  // [n_oblk][n_rows]
+  size_t offs_count = 0, sbase_count = 0;  // their sizes, also where they are not filled in
 };
 
 }  // namespace dd
@@ -84,7 +85,10 @@ struct dd_plan {
   dd::TileCfg fwd;             // forward tile shape
   int32_t span_fwd = 0;        // largest delay spread inside a forward DM block
   dd::IntTables itab;          // integer plans: staged forward kernel's tables (sizes only while gtab is in use)
-  dd::GroupTables gtab;        // integer plans: group-sum tables; in use until tiles are chosen explicitly
+  dd::GroupTables gtab;        // integer plans that run by group sums by default: their tables
+  dd::TileCfg def_fwd;         // default forward tile shape,
+  size_t def_table_bytes = 0;  // and the default shapes' table bytes
+  bool chosen = false;         // integer plans: tiles chosen explicitly (no group sums in a batch)
   dd::FloatTables ftab_fwd;    // float plans: forward kernel tables
   dd::FloatTables ftab_adj;    // float plans: adjoint kernel tables
   dd::QuadTables qtab[2];      // float plans: quad tables (forward, adjoint); in use until tiles are chosen explicitly
@@ -104,9 +108,12 @@ dd_status choose_forward_tiles(dd_plan &p);
 // shape `shape` and TileOrder `order`.  DD_ERR_RANGE if the shape cannot hold
 // the plan's delay spread; the plan is unchanged then.
 // The direction (an integer plan's forward: its beam in a batch too) then runs that
-// shape's kernel (gtab.use and gtab.batch, qtab[direction].use are cleared).
-// With fill false an integer plan's staged tables are only sized.
+// shape's kernel (gtab.use, qtab[direction].use are cleared, chosen is set).
+// With fill false the staged tables are only sized.
 dd_status set_tiles(dd_plan &p, int direction, int shape, int order, bool fill = true);
+// Whether the plan (batch: as a beam of a batch), with its default tiles, runs by group sums: the
+// tables are then the plan's own, if it holds them, else *t.
+bool build_group_sums(const dd_plan &p, bool batch, GroupTables *t);
 int num_shapes(const dd_plan &p);
 size_t table_bytes(const dd_plan &p);
 // Byte offsets of the plan's current tables inside a table workspace of

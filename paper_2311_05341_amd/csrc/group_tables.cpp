@@ -21,7 +21,7 @@ struct Group {
   int c0 = 0, g = 0;
   int words = 0;                   // words of a pattern row (a multiple of 4)
   int n_pat = 0;
-  uint8_t slot_of[kGrpMaxRows];       // pattern of each DM row, in path order
+  uint8_t slot_of[kGrpMaxRows] = {};  // pattern of each DM row, in path order
   std::vector<int32_t> r;          // [n_pat][g] relative delays, in path order
   int base = 0;
   int lds() const { return n_pat * words * 4; }
@@ -33,6 +33,7 @@ struct Block {
   std::vector<uint32_t> sum;
   int n_steps = 0;
   int64_t lo = INT64_MAX, hi = INT64_MIN;
+  std::vector<int> split;     // group lengths, in steps of channels, found in a first pass
   double cost = 0, work = 0;  // GroupTables
   int lds = 0;
   bool ok = true;
@@ -60,19 +61,26 @@ double group_cost(int rows, int g, int n_pat, int words, double steps) {
 
 double guess_steps(int n_pat) { return n_pat - 1 + 0.04 * n_pat * n_pat; }
 
-int distinct(const uint64_t *h, int rows) {
-  uint64_t tab[2 * kGrpMaxRows];
-  bool used[2 * kGrpMaxRows] = {};
-  int n = 0;
-  for (int d = 0; d < rows; ++d) {
-    int i = (int)((h[d] * 0x9E3779B97F4A7C15ull) >> 57);
-    while (used[i] && tab[i] != h[d]) i = (i + 1) & (2 * kGrpMaxRows - 1);
-    if (!used[i]) {
-      used[i] = true;
-      tab[i] = h[d];
-      ++n;
+// How many of h[0..rows) differ, without branches on them (rows go back and forth between a
+// few patterns: a search costs a mispredicted branch each): every row against the one `back`
+// rows before it, for every `back`.  Before the first row stands a value that none has but by
+// an accident, which only makes a worse split.
+int distinct(const uint32_t *h, int rows) {
+  typedef uint32_t Four __attribute__((vector_size(16)));
+  uint32_t w[2 * kGrpMaxRows];
+  memset(w, 0xA5, rows * sizeof *w);
+  memcpy(w + rows, h, rows * sizeof *w);
+  Four seen[kGrpMaxRows / 4] = {};
+  for (int back = 1; back < rows; ++back)
+    for (int k = back / 4; k < rows / 4; ++k) {
+      Four x, y;
+      memcpy(&x, w + rows + 4 * k, sizeof x);
+      memcpy(&y, w + rows + 4 * k - back, sizeof y);
+      seen[k] |= (Four)(x == y);
     }
-  }
+  int n = 0;
+  for (int k = 0; k < rows / 4; ++k)
+    for (int e = 0; e < 4; ++e) n += seen[k][e] == 0;
   return n;
 }
 
@@ -82,16 +90,20 @@ void fill_group(const int32_t *sh, int rows, Group *G) {
   const int32_t *s0 = sh + (size_t)G->c0 * rows;
   int first[kGrpMaxRows], cls[kGrpMaxRows], n = 0;
   for (int d = 0; d < rows; ++d) {
-    int k = 0;
-    for (; k < n; ++k) {
-      bool same = true;
-      for (int c = 1; c < g && same; ++c) {
+    auto same = [&](int e) {  // row e follows the same pattern
+      for (int c = 1; c < g; ++c) {
         const int32_t *s = s0 + (size_t)c * rows;
-        same = s[d] - s0[d] == s[first[k]] - s0[first[k]];
+        if (s[d] - s0[d] != s[e] - s0[e]) return false;
       }
-      if (same) break;
+      return true;
+    };
+    int k = 0;
+    if (d && same(d - 1)) {
+      k = cls[d - 1];
+    } else {
+      while (k < n && !same(first[k])) ++k;
+      if (k == n) first[n++] = d;
     }
-    if (k == n) first[n++] = d;
     cls[d] = k;
   }
   std::vector<int32_t> pat((size_t)n * g);
@@ -146,7 +158,6 @@ struct Part {
   uint32_t slot;     // LDS address of its first pattern's row
   uint32_t block0;   // first operation block
   std::vector<int> rows;  // rows written by each block
-  double cost;       // of one chunk
 };
 
 // Append `ops` as operation blocks.  Spare operations of the last one repeat its
@@ -163,7 +174,6 @@ void emit_ops(const Input &in, const std::vector<Op> &ops, Block *b, Part *part)
       b->hi = std::max<int64_t>(b->hi, (int64_t)op.s + part->chunks * kGrpChunk + 12);
     }
     part->rows.push_back(0);
-    part->cost += kCostRecord;
     uint32_t words[kGrpBlockWords] = {(uint32_t)base, (uint32_t)(base >> 32)};
     for (int q = 0; q < kGrpOps; ++q) {
       if (off[q] - base > kGrpMaxOffset) b->ok = false;
@@ -171,12 +181,28 @@ void emit_ops(const Input &in, const std::vector<Op> &ops, Block *b, Part *part)
       if (i + q >= ops.size()) continue;
       const uint32_t kind = ops[i + q].flags | (uint32_t)(ops[i + q].s & (per_load - 1));
       words[2 + q / 4] |= kind << (8 * (q % 4));
-      part->cost += kind & kOpMove ? kCostMove : kCostAdd;
-      if (kind & kOpFold) part->cost += kCostFold;
-      if (kind & kOpWrite) ++part->rows.back(), part->cost += kCostWrite;
+      if (kind & kOpWrite) ++part->rows.back();
     }
     b->ops.insert(b->ops.end(), words, words + kGrpBlockWords);
   }
+}
+
+// A run of patterns [p0, p1) of a group, by its counts: what make_part will find.
+struct Run {
+  int group, p0, p1, chunks;
+  double cost;  // of one chunk
+};
+
+Run count_run(const Input &in, const Group &G, int group, int p0, int p1) {
+  const int g = G.g, per_load = in.bits == 16 ? 2 : 4;
+  uint32_t phases = 0;
+  int64_t moves = 0;
+  for (int c = 0; c < g; ++c) phases |= 1u << ((G.base + G.r[(size_t)p0 * g + c]) & (per_load - 1));
+  for (size_t k = (size_t)p0 * g; k < (size_t)(p1 - 1) * g; ++k) moves += std::abs((int64_t)G.r[k + g] - G.r[k]);
+  const int64_t blocks = (g + moves + kGrpOps - 1) / kGrpOps;
+  const double cost = kCostRecord * (double)blocks + kCostAdd * g + kCostFold * __builtin_popcount(phases) +
+                      kCostMove * (double)moves + kCostWrite * (p1 - p0);
+  return {group, p0, p1, (G.words + kGrpChunk - 1) / kGrpChunk, cost};
 }
 
 // Patterns [p0, p1) of a group: the first one's adds, phase by phase, then moves.
@@ -233,10 +259,11 @@ void build_block(const Input &in, int blk, bool cost_only, Block *b) {
   const uint32_t sample_max = in.sample_max();
   // delays of the block's rows, channel by channel; rows past the last repeat it
   std::vector<int32_t> sh((size_t)n_chan * rows);
-  for (int d = 0; d < rows; ++d) {
-    const int32_t *row = in.shift + (size_t)std::min(blk * rows + d, in.n_dm - 1) * n_chan;
-    for (int c = 0; c < n_chan; ++c) sh[(size_t)c * rows + d] = row[c];
-  }
+  for (int c0 = 0; c0 < n_chan; c0 += 16)  // (a cache line of each row at a time)
+    for (int d = 0; d < rows; ++d) {
+      const int32_t *row = in.shift + (size_t)std::min(blk * rows + d, in.n_dm - 1) * n_chan;
+      for (int c = c0; c < std::min(n_chan, c0 + 16); ++c) sh[(size_t)c * rows + d] = row[c];
+    }
   auto words_of = [&](int c) {
     const int32_t *s = &sh[(size_t)c * rows];
     return (int)std::min<int64_t>(((int64_t)kGrpWin + s[rows - 1] - s[0] + 3) / 4 * 4, INT_MAX);
@@ -244,22 +271,27 @@ void build_block(const Input &in, int blk, bool cost_only, Block *b) {
   // Split the band into groups of least modelled time (dynamic programming over
   // the multiples of kGroupStep).
   const int np = (n_chan + kGroupStep - 1) / kGroupStep;
-  std::vector<double> cost(np + 1, 1e300);
-  std::vector<int> len(np + 1, 0);
-  cost[0] = 0;
-  for (int p = 0; p < np; ++p) {
+  std::vector<int> len;
+  len.swap(b->split);
+  std::vector<double> cost(len.empty() ? np + 1 : 0, 1e300);
+  const bool known = !len.empty();
+  if (!known) {
+    len.assign(np + 1, 0);
+    cost[0] = 0;
+  }
+  for (int p = 0; p < np && !known; ++p) {
     if (cost[p] >= 1e300) continue;
     const int c0 = p * kGroupStep;
     const int words = words_of(c0);
     if (words > kGrpMaxWords) continue;
     const int32_t *s0 = &sh[(size_t)c0 * rows];
-    uint64_t h[kGrpMaxRows] = {};
+    uint32_t h[kGrpMaxRows] = {};  // of each row's pattern (two patterns of one hash only make a worse split)
     for (int k = 1; k <= kSizes && p + k <= np; ++k) {
       const int lo = std::max(c0 + 1, c0 + (k - 1) * kGroupStep), hi = std::min(n_chan, c0 + k * kGroupStep);
       for (int c = lo; c < hi; ++c) {
         const int32_t *s = &sh[(size_t)c * rows];
         for (int d = 0; d < rows; ++d)
-          h[d] = h[d] * 0xD1342543DE82EF95ull + (uint64_t)(uint32_t)(s[d] - s0[d]) + 1;
+          h[d] = (h[d] << 5) + h[d] + (uint32_t)(s[d] - s0[d]);
       }
       const int n = distinct(h, rows);
       if ((int64_t)n * words * 4 > kGrpSetBytes) break;
@@ -268,12 +300,15 @@ void build_block(const Input &in, int blk, bool cost_only, Block *b) {
       if (n > rows * 7 / 8) break;
     }
   }
-  if (cost[np] >= 1e300) {
+  if (!known && cost[np] >= 1e300) {
     b->ok = false;
     return;
   }
-  b->cost = cost[np];
-  if (cost_only) return;
+  if (!known) b->cost = cost[np];
+  if (cost_only) {
+    b->split.swap(len);
+    return;
+  }
   std::vector<Group> groups;
   for (int p = np; p > 0; p -= len[p]) {
     Group G;
@@ -291,8 +326,7 @@ void build_block(const Input &in, int blk, bool cost_only, Block *b) {
       return;
     }
   }
-  // Steps: as many groups as fit in one LDS set, at most
-  // 2 * kGrpStepPairs.  A group is
+  // Steps: as many groups as fit in one LDS set, at most 2 * kGrpStepPairs.  A group is
   // built in one or more parts (runs of its patterns), each chunk of a part by one
   // wave: the longest first to the wave with the least work, with as many parts
   // as make the busiest wave's work least.
@@ -304,56 +338,59 @@ void build_block(const Input &in, int blk, bool cost_only, Block *b) {
     while (j < groups.size() && j < i + 2 * kGrpStepPairs && bytes + groups[j].lds() <= kGrpSetBytes) bytes += groups[j++].lds();
     b->lds = std::max(b->lds, (int)set + bytes);
     struct Task {
-      int part, chunk;
+      int run, chunk;
     };
     double best = 1e300, best_simd = 0;
-    std::vector<uint32_t> best_ops;
-    std::vector<Part> best_parts;
-    std::vector<int> best_wave;
-    std::vector<Task> best_tasks;
-    const size_t ops_mark = b->ops.size();
-    for (int split = 1; split <= 4 && (split == 1 || 4 * best_tasks.size() < 3 * kGrpWaves); ++split) {
-      std::vector<Part> parts;
-      uint32_t slot = set;
+    std::vector<Run> runs, best_runs;
+    std::vector<int> wave, best_wave;
+    std::vector<Task> tasks, best_tasks;
+    bool more = true;  // a group has patterns left for another split
+    for (int split = 1; more && split <= 4 && (split == 1 || 4 * best_tasks.size() < 3 * kGrpWaves); ++split) {
+      more = false;
+      runs.clear();
+      tasks.clear();
+      wave.clear();
       for (size_t q = i; q < j; ++q) {
         const Group &G = groups[q];
         const int n = std::min(split, G.n_pat);
-        for (int k = 0; k < n; ++k) parts.push_back(make_part(in, G, G.n_pat * k / n, G.n_pat * (k + 1) / n, slot, b));
-        slot += (uint32_t)G.lds();
+        more |= G.n_pat > split;
+        for (int k = 0; k < n; ++k) runs.push_back(count_run(in, G, (int)q, G.n_pat * k / n, G.n_pat * (k + 1) / n));
       }
-      std::vector<Task> tasks;
-      for (size_t k = 0; k < parts.size(); ++k)
-        for (int c = 0; c < parts[k].chunks; ++c) tasks.push_back({(int)k, c});
+      for (size_t k = 0; k < runs.size(); ++k)
+        for (int c = 0; c < runs[k].chunks; ++c) tasks.push_back({(int)k, c});
       std::stable_sort(tasks.begin(), tasks.end(),
-                       [&](const Task &x, const Task &y) { return parts[x.part].cost > parts[y.part].cost; });
+                       [&](const Task &x, const Task &y) { return runs[x.run].cost > runs[y.run].cost; });
       double load[kGrpWaves] = {}, simd[4] = {}, total = 0;
-      std::vector<int> wave;
       for (const Task &t : tasks) {  // (waves w, w + 4, ... share a SIMD)
         int w = 0;
         for (int k = 1; k < kGrpWaves; ++k)
           if (load[k] < load[w] || (load[k] == load[w] && simd[k & 3] < simd[w & 3])) w = k;
-        load[w] += parts[t.part].cost;
-        simd[w & 3] += parts[t.part].cost;
-        total += parts[t.part].cost;
+        load[w] += runs[t.run].cost;
+        simd[w & 3] += runs[t.run].cost;
+        total += runs[t.run].cost;
         wave.push_back(w);
       }
       const double cost = *std::max_element(load, load + kGrpWaves) + kCostShared * total / kGrpWaves;
       if (cost < best) {
         best = cost;
         best_simd = *std::max_element(simd, simd + 4);
-        best_ops.assign(b->ops.begin() + ops_mark, b->ops.end());
-        best_parts = std::move(parts);
-        best_tasks = std::move(tasks);
-        best_wave = std::move(wave);
+        best_runs.swap(runs);
+        best_tasks.swap(tasks);
+        best_wave.swap(wave);
       }
-      b->ops.resize(ops_mark);
     }
     b->work += best_simd;
-    b->ops.insert(b->ops.end(), best_ops.begin(), best_ops.end());
+    std::vector<Part> parts;
+    uint32_t at = set;
+    for (size_t k = 0; k < best_runs.size(); ++k) {
+      const Run &r = best_runs[k];
+      if (k && best_runs[k - 1].group != r.group) at += (uint32_t)groups[best_runs[k - 1].group].lds();
+      parts.push_back(make_part(in, groups[r.group], r.p0, r.p1, at, b));
+    }
     size_t mark[kGrpWaves];
     for (int w = 0; w < kGrpWaves; ++w) mark[w] = b->rec[w].size();
     for (size_t k = 0; k < best_tasks.size(); ++k)
-      emit_chunk(best_parts[best_tasks[k].part], best_tasks[k].chunk, &b->rec[best_wave[k]]);
+      emit_chunk(parts[best_tasks[k].run], best_tasks[k].chunk, &b->rec[best_wave[k]]);
     for (int w = 0; w < kGrpWaves; ++w) end_step(&b->rec[w], mark[w]);
     const size_t sm = b->sum.size();
     b->sum.resize(sm + kGrpWaves * sum_words, kZeroRow);
@@ -386,7 +423,7 @@ void build_block(const Input &in, int blk, bool cost_only, Block *b) {
 }  // namespace
 
 bool build_group_tables(const int32_t *shift, int n_dm, int n_chan, int bits, int64_t pitch_bytes, GroupTables *t,
-                        double max_cost) {
+                        double max_cost, double max_work) {
   static_assert(sizeof(GroupBlock) == 72, "device layout");
   static_assert(kMaxGroup * 255 <= 65535, "a group's packed sums fit 16 bits");
   *t = GroupTables();
@@ -395,18 +432,23 @@ bool build_group_tables(const int32_t *shift, int n_dm, int n_chan, int bits, in
   try {
     std::vector<Block> blocks(n_blk);
     const int64_t work = (int64_t)n_blk * n_chan;
-    if (max_cost > 0 && n_blk > 3) {  // plans that are far from it: the costs of two blocks tell
-      Block mid, last;
-      build_block(in, n_blk / 2, true, &mid);
-      if (mid.ok) build_block(in, n_blk - 1, true, &last);
-      if (!mid.ok || !last.ok || 0.5 * n_blk * (mid.cost + last.cost) > 1.2 * max_cost) return false;
+    if (max_cost > 0) {  // plans that are far from it: the costs of two blocks tell
+      Block &mid = blocks[(n_blk - 1) / 2], &last = blocks[n_blk - 1];
+      build_block(in, (n_blk - 1) / 2, true, &mid);
+      if (mid.ok && n_blk > 1) build_block(in, n_blk - 1, true, &last);
+      if (!mid.ok || !last.ok || 0.5 * n_blk * (mid.cost + last.cost) > (n_blk > 2 ? 1.2 : 1.0) * max_cost) return false;
     }
-    const int nthr = (int)std::min<int64_t>({kMaxParts, n_blk, std::max<int64_t>(1, work / 512),
+    if (max_work > 0) {  // and the instructions of one
+      build_block(in, (n_blk - 1) / 2, false, &blocks[(n_blk - 1) / 2]);
+      if (!blocks[(n_blk - 1) / 2].ok || blocks[(n_blk - 1) / 2].work > 1.3 * max_work) return false;
+    }
+    const int nthr = (int)std::min<int64_t>({kMaxParts, n_blk, std::max<int64_t>(1, work / 1024),
                                              std::max(1u, std::thread::hardware_concurrency())});
     uint8_t failed[kMaxParts] = {};
     run_parts(nthr, [&](int k) {
       try {
-        for (int b = k; b < n_blk; b += nthr) build_block(in, b, false, &blocks[b]);
+        for (int b = k; b < n_blk; b += nthr)
+          if (!blocks[b].n_steps) build_block(in, b, false, &blocks[b]);
       } catch (const std::bad_alloc &) {
         failed[k] = 1;
       }
@@ -437,27 +479,39 @@ bool build_group_tables(const int32_t *shift, int n_dm, int n_chan, int bits, in
     if (total >= ((int64_t)1 << 31)) return false;
     t->data.assign((size_t)total, 0);
     memcpy(t->data.data(), &t->head, sizeof t->head);
+    struct Place {
+      size_t rec, op, sum;  // words
+    };
+    std::vector<Place> place(n_blk);
     size_t ro = 0, oo = kGrpBlockWords, so = 0;
     for (int b = 0; b < n_blk; ++b) {
-      GroupBlock g = {};
-      const uint32_t op0 = (uint32_t)(oo / kGrpBlockWords) - 1;  // the block's operation blocks count from 1
-      for (int k = 0; k < kGrpWaves; ++k) {
-        std::vector<uint32_t> &r = blocks[b].rec[k];
-        for (size_t i = 0; i < r.size(); i += kGrpRecWords)
-          if (r[i]) r[i] += op0;
-        g.rec_first[k] = (uint32_t)(ro / kGrpRecWords);
-        std::copy(r.begin(), r.end(), t->data.begin() + t->head.rec_off + ro);
-        ro += r.size();
-      }
-      std::copy(blocks[b].ops.begin(), blocks[b].ops.end(), t->data.begin() + t->head.op_off + oo);
+      place[b] = {ro, oo, so};
+      for (const auto &r : blocks[b].rec) ro += r.size();
       oo += blocks[b].ops.size();
-      g.sum_first = (uint32_t)so;
-      g.n_steps = (uint32_t)blocks[b].n_steps;
-      std::copy(blocks[b].sum.begin(), blocks[b].sum.end(), t->data.begin() + t->head.sum_off + so);
       so += blocks[b].sum.size();
-      memcpy(&t->data[kGrpHeadWords + (size_t)b * (sizeof g / 4)], &g, sizeof g);
-      blocks[b] = Block();
     }
+    const int ncopy = total >= (int64_t)1 << 20 ? nthr : 1;
+    run_parts(ncopy, [&](int k) {
+      for (int b = k; b < n_blk; b += ncopy) {
+        GroupBlock g = {};
+        Place at = place[b];
+        const uint32_t op0 = (uint32_t)(at.op / kGrpBlockWords) - 1;  // the block's operation blocks count from 1
+        for (int w = 0; w < kGrpWaves; ++w) {
+          std::vector<uint32_t> &r = blocks[b].rec[w];
+          for (size_t i = 0; i < r.size(); i += kGrpRecWords)
+            if (r[i]) r[i] += op0;
+          g.rec_first[w] = (uint32_t)(at.rec / kGrpRecWords);
+          std::copy(r.begin(), r.end(), t->data.begin() + t->head.rec_off + at.rec);
+          at.rec += r.size();
+        }
+        std::copy(blocks[b].ops.begin(), blocks[b].ops.end(), t->data.begin() + t->head.op_off + at.op);
+        g.sum_first = (uint32_t)at.sum;
+        g.n_steps = (uint32_t)blocks[b].n_steps;
+        std::copy(blocks[b].sum.begin(), blocks[b].sum.end(), t->data.begin() + t->head.sum_off + at.sum);
+        memcpy(&t->data[kGrpHeadWords + (size_t)b * (sizeof g / 4)], &g, sizeof g);
+        blocks[b] = Block();
+      }
+    });
   } catch (const std::bad_alloc &) {
     return false;
   }

@@ -82,7 +82,6 @@ constexpr int kGrpHeadWords = sizeof(GroupHead) / 4;
 
 struct GroupTables {
   bool use = false;            // the plan runs the group-sum kernel
-  bool batch = false;          // its beam of a batch does
   int n_blk = 0;
   std::vector<uint32_t> data;  // GroupHead, [n_blk] GroupBlock, records, operation blocks, sum entries
   GroupHead head = {};
@@ -94,8 +93,8 @@ struct GroupTables {
 // Tables for shift[n_dm][n_chan] (never decreasing with d) and samples of
 // `bits` (4, 8: two packed 16-bit sums per word; 16: one 32-bit sum) in channel
 // rows pitch_bytes apart.  false if some group cannot be held, if the modelled clocks
-// exceed max_cost (> 0), or on bad_alloc.
+// exceed max_cost (> 0), if one block's instructions are far above max_work (> 0), or on bad_alloc.
 bool build_group_tables(const int32_t *shift, int n_dm, int n_chan, int bits, int64_t pitch_bytes, GroupTables *t,
-                        double max_cost = 0);
+                        double max_cost = 0, double max_work = 0);
 
 }  // namespace dd

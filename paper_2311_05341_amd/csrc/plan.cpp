@@ -31,7 +31,13 @@ static double channel_freq(const dd_plan &p, int c) {
 dd_status build_shift_table(dd_plan &p) {
   const int nc = p.desc.n_chan, nd = p.desc.n_dm;
   const double fh = p.desc.f_high_mhz;
-  std::vector<double> k(nc);
+  std::vector<double> k;
+  try {
+    k.resize(nc);
+    p.shift.assign((size_t)nd * nc, 0);
+  } catch (const std::bad_alloc &) {
+    return fail(DD_ERR_NOMEM, "shift table allocation failed");
+  }
   for (int c = 0; c < nc; ++c) {
     double f = channel_freq(p, c);
     if (!(f > 0.0) || !(f <= fh) || !isfinite(f))
@@ -39,41 +45,52 @@ dd_status build_shift_table(dd_plan &p) {
                                     " MHz is not in (0, f_high]");
     k[c] = 1.0 / (f * f) - 1.0 / (fh * fh);
   }
-  try {
-    p.shift.assign((size_t)nd * nc, 0);
-  } catch (const std::bad_alloc &) {
-    return fail(DD_ERR_NOMEM, "shift table allocation failed");
-  }
   const double t = p.desc.t_samp_s, d0 = p.desc.dm_start, step = p.desc.dm_step;
-  int bad = 0;
-  auto rows = [&](int lo, int hi, int *flag) {
-    for (int d = lo; d < hi; ++d) {
-      const double dm = d0 + (double)d * step;
-      int32_t *row = p.shift.data() + (size_t)d * nc;
-      for (int c = 0; c < nc; ++c) {
-        const double v = ((dm * kDispersionConstant) * k[c]) / t;
-        const double s = floor(v + 0.5);
-        if (!(s >= 0.0 && s <= 2147483647.0)) { *flag = 1; return; }
-        row[c] = (int32_t)s;
-      }
-    }
-  };
   const size_t work = (size_t)nd * nc;
-  int nthr = work < (1u << 20) ? 1 : (int)std::min<unsigned>(kMaxParts, std::max(1u, std::thread::hardware_concurrency()));
-  int flags[kMaxParts] = {};
-  run_parts(nthr, [&](int i) { rows((int)((int64_t)nd * i / nthr), (int)((int64_t)nd * (i + 1) / nthr), &flags[i]); });
-  for (int f : flags) bad |= f;
-  if (bad) return fail(DD_ERR_RANGE, "a shift does not fit in int32");
+  const int nthr = work < (1u << 20) ? 1 : (int)std::min<unsigned>(kMaxParts, std::max(1u, std::thread::hardware_concurrency()));
   // The kernels rely on delays never decreasing with d (each DM block is
   // staged from its first row's delays); Eq. 1 with dm_step >= 0 and
   // f_c <= f_high guarantees it, and so does monotone FP64 rounding.  Check.
-  for (int d = 1; d < nd; ++d) {
-    const int32_t *a = p.shift.data() + (size_t)(d - 1) * nc, *b = a + nc;
-    for (int c = 0; c < nc; ++c)
-      if (b[c] < a[c]) return fail(DD_ERR_RANGE, "shift table decreases with DM");
-  }
+  struct Part {
+    bool bad = false, falls = false;
+    int32_t mx = 0;
+  } parts[kMaxParts];
+  run_parts(nthr, [&](int i) {
+    Part &part = parts[i];
+    const int lo = (int)((int64_t)nd * i / nthr), hi = (int)((int64_t)nd * (i + 1) / nthr);
+    for (int d = lo; d < hi; ++d) {
+      const double dm = d0 + (double)d * step;
+      int32_t *row = p.shift.data() + (size_t)d * nc;
+      const int32_t *prev = d > lo ? row - nc : row;
+      for (int c = 0; c < nc; ++c) {
+        const double v = ((dm * kDispersionConstant) * k[c]) / t;
+        const double s = floor(v + 0.5);
+        if (!(s >= 0.0 && s <= 2147483647.0)) {
+          part.bad = true;
+          return;
+        }
+        row[c] = (int32_t)s;
+      }
+      int32_t falls = 0, mx = 0;
+      for (int c = 0; c < nc; ++c) {
+        falls |= row[c] < prev[c];
+        mx = std::max(mx, row[c]);
+      }
+      part.falls |= falls != 0;
+      part.mx = std::max(part.mx, mx);
+    }
+  });
+  bool falls = false;
   int32_t mx = 0;
-  for (int32_t v : p.shift) mx = std::max(mx, v);
+  for (int i = 0; i < nthr; ++i) {
+    if (parts[i].bad) return fail(DD_ERR_RANGE, "a shift does not fit in int32");
+    falls |= parts[i].falls;
+    mx = std::max(mx, parts[i].mx);
+    const int lo = (int)((int64_t)nd * i / nthr);  // the parts' first rows against the rows before them
+    if (lo > 0)
+      for (int c = 0; c < nc; ++c) falls |= p.shift[(size_t)lo * nc + c] < p.shift[(size_t)(lo - 1) * nc + c];
+  }
+  if (falls) return fail(DD_ERR_RANGE, "shift table decreases with DM");
   p.max_shift = mx;
   p.n_out = p.desc.n_samp - (int64_t)mx;
   if (p.n_out <= 0)
@@ -196,7 +213,7 @@ dd_status build_int_tables(const dd_plan &p, int ns, int dm_per_wave, int waves,
 // Tables of the float kernel in direction `adjoint` for shape (ns, per_wave,
 // waves, row_block); see FloatTables.
 static dd_status build_float_tables(const dd_plan &p, bool adjoint, const int *shape, int lds_limit,
-                                    FloatTables *t) {
+                                    FloatTables *t, bool fill) {
   const int nc = p.desc.n_chan, nd = p.desc.n_dm;
   const int ns = shape[0], per_wave = shape[1], waves = shape[2], rb = shape[3];
   const int n_rows = adjoint ? nd : nc, n_out = adjoint ? nc : nd;
@@ -239,8 +256,11 @@ static dd_status build_float_tables(const dd_plan &p, bool adjoint, const int *s
   t->lds_bytes = (int)lds;
   const int rp = per_wave < 2 ? 2 : per_wave;
   const int nrp = (n_rows + rb - 1) / rb * rb;
+  t->offs_count = (size_t)n_oblk * waves * nrp * rp;
+  t->sbase_count = sbase.size();
+  if (!fill) return DD_OK;
   try {
-    t->offs.assign((size_t)n_oblk * waves * nrp * rp, 0);
+    t->offs.assign(t->offs_count, 0);
   } catch (const std::bad_alloc &) {
     return fail(DD_ERR_NOMEM, "table allocation failed");
   }
@@ -270,7 +290,7 @@ dd_status set_tiles(dd_plan &p, int direction, int shape, int order, bool fill) 
   t.order = order;
   if (p.desc.dtype == DD_F32) {
     FloatTables ft;
-    const dd_status st = build_float_tables(p, direction == 1, kF32Shapes[shape], kLdsLimit, &ft);
+    const dd_status st = build_float_tables(p, direction == 1, kF32Shapes[shape], kLdsLimit, &ft, fill);
     if (st != DD_OK) return st;
     ft.shape = shape;
     ft.order = order;
@@ -300,7 +320,8 @@ dd_status set_tiles(dd_plan &p, int direction, int shape, int order, bool fill) 
     p.fwd = t;
     p.span_fwd = max_dm_block_span(p, t.waves * t.dm_per_wave);
     p.itab = IntTables();
-    p.gtab.use = p.gtab.batch = false;
+    p.gtab.use = false;
+    p.chosen = true;
     return DD_OK;
   }
   const dd_status st = build_int_tables(p, k[0], k[1], k[2], k[3], int_shape_segs(shape), kLdsLimit, &tab, fill);
@@ -315,7 +336,8 @@ dd_status set_tiles(dd_plan &p, int direction, int shape, int order, bool fill) 
   p.fwd = t;
   p.span_fwd = max_dm_block_span(p, t.waves * t.dm_per_wave);
   p.itab = std::move(tab);
-  p.gtab.use = p.gtab.batch = false;
+  p.gtab.use = false;
+  p.chosen = true;
   return DD_OK;
 }
 
@@ -427,49 +449,67 @@ static double launch_us(double longest, double mean, double rounds, double overl
 // or more (one 22%, the others up to 17%) run their shape.  On the two plans above, 4-bit 8192 ch x
 // 2^18 x 500 and 16-bit the same, group sums against the other kernels: 353 / 820, 1.09 /
 // 1.78, 13.1 / 22.4 and 21.7 / 37.7 ms.
-static void choose_group_sums(dd_plan &p) {
-  if (p.desc.dtype == DD_F32) return;
+//
+// A beam of a batch: the same two models without rounds, for many workgroups in flight (220
+// plans as batches of themselves: 2 of 106 8-bit and 10 of 49 4-bit ones were up to 1.57 times as
+// slow by group sums without the second model, 1 and 2 with it).
+namespace {
+struct GroupModel {
+  double start, op, overlap, tail;  // group sums: us of a workgroup, and per instruction; several rounds
+  int rows;
+  double samples;                   // the other kernel's workgroup, two of which share a CU,
+  double own_start, own_chan, alone, own_overlap, own_tail;  // its us, per channel (share of it where alone on its CU)
+  double batch_start, batch_op, batch_own_start, batch_own_chan;  // the same among many beams
+};
+constexpr GroupModel kGroup8 = {8.64, 0.00331, 0.665, 1.13, 32, 512, 5.84, 0.229, 0.64, 0.79, 0.72, 7.1, 0.003, 5.8, 0.206};
+constexpr GroupModel kGroup4 = {8.95, 0.00347, 0.687, 1.30, 16, 1008, 9.45, 0.243, 0.82, 0.68, 0.85, 9.0, 0.00286, 7.0, 0.18};
+constexpr GroupModel kGroup16 = {11.4, 0.00378, 0.864, 0.75, 32, 1024, 7.96, 0.651, 0.65, 0.81, 0.65, 7.7, 0.0028, 6.0, 0.955};
+}  // namespace
+
+bool build_group_sums(const dd_plan &p, bool batch, GroupTables *t) {
   const double kModel = 0.74, kCus = 256;
   const int bits = p.desc.dtype == DD_U4 ? 4 : p.desc.dtype == DD_U16 ? 16 : 8;
-  const bool best_staged = !is_direct(p.fwd) && p.fwd.waves == 8;
+  const bool best_staged = !is_direct(p.def_fwd) && p.def_fwd.waves == 8;
   const double rate = bits == 4 ? 80.0 : bits == 16 ? (best_staged ? 47.0 : 27.0) : best_staged ? 64.0 : 53.0;
   const int64_t tile = bits == 16 ? kGrpWin : 2 * kGrpWin;
   const int64_t n_blk = (p.desc.n_dm + group_rows(bits) - 1) / group_rows(bits), tiles = (p.n_out + tile - 1) / tile;
   const double groups = ceil((double)n_blk * (double)tiles / kCus);
   const double others = ceil((double)((p.desc.n_dm + 31) / 32) * (double)((p.n_out + 511) / 512) / (2 * kCus));
-  // the group kernel's rounds at its mean cost per block against the others' rounds, and
-  // (a beam of a batch) all its tiles against the plan's additions
-  const double round_limit = 0.9 * others * (2.0 * 32 * 512) * p.desc.n_chan / rate / (groups * kModel) * (double)n_blk;
-  const double batch_limit = 0.9 * (double)p.desc.n_dm * (double)p.n_out * p.desc.n_chan / rate / kModel / (double)tiles;
-  if (!build_group_tables(p.shift.data(), p.desc.n_dm, p.desc.n_chan, bits, p.in_pitch_bytes, &p.gtab,
-                          std::max(round_limit, batch_limit)) ||
-      p.gtab.data.size() * 4 > table_bytes(p)) {
-    p.gtab = GroupTables();
-    return;
-  }
-  struct Model {
-    double start, op, overlap, tail;  // group sums: us of a workgroup, and per instruction; several rounds
-    int rows;
-    double samples;                   // the other kernel's workgroup, two of which share a CU,
-    double own_start, own_chan, alone, own_overlap, own_tail;  // its us, per channel (share of it where alone on its CU)
-    double batch_start, batch_op, batch_own_start, batch_own_chan;  // the same among many beams
-  };
-  const Model m = bits == 8   ? Model{8.64, 0.00331, 0.665, 1.13, 32, 512, 5.84, 0.229, 0.64, 0.79, 0.72, 7.1, 0.003, 5.8, 0.206}
-                  : bits == 4 ? Model{8.95, 0.00347, 0.687, 1.30, 16, 1008, 9.45, 0.243, 0.82, 0.68, 0.85, 9.0, 0.00286, 7.0, 0.18}
-                              : Model{11.4, 0.00378, 0.864, 0.75, 32, 1024, 7.96, 0.651, 0.65, 0.81, 0.65, 7.7, 0.0028, 6.0, 0.955};
+  // a beam of a batch: all its tiles against the plan's additions; a plan: the group kernel's rounds
+  // at its mean cost per block against the others' rounds
+  const double limit =
+      batch ? 0.9 * (double)p.desc.n_dm * (double)p.n_out * p.desc.n_chan / rate / kModel / (double)tiles
+            : 0.9 * others * (2.0 * 32 * 512) * p.desc.n_chan / rate / (groups * kModel) * (double)n_blk;
+  const GroupModel m = bits == 8 ? kGroup8 : bits == 4 ? kGroup4 : kGroup16;
   const double slow = bits == 4 || best_staged ? 1.0 : bits == 8 ? 1.2 : 1.7;  // staged shapes of 16 waves, direct reads
-  const double wgs = (double)n_blk * (double)tiles, mean_work = p.gtab.work / (double)n_blk;
+  const double rounds = (double)n_blk * (double)tiles / kCus;
   const double own_wgs = ceil((double)p.desc.n_dm / m.rows) * ceil((double)p.n_out / m.samples);
   const double own_rounds = own_wgs / (2 * kCus), own_wg = m.own_start + m.own_chan * slow * p.desc.n_chan;
-  const double sums_us = launch_us(m.start + m.op * p.gtab.max_work, m.start + m.op * mean_work, wgs / kCus, m.overlap, m.tail);
-  const double own_us = own_rounds <= 0.5 ? m.own_start + m.alone * m.own_chan * slow * p.desc.n_chan
-                                          : launch_us(own_wg, own_wg, own_rounds, m.own_overlap, m.own_tail);
-  p.gtab.use = p.gtab.cost <= round_limit && sums_us < (bits == 4 ? 0.95 : 1.0) * own_us;
-  // a beam of a batch (220 plans as batches of themselves): 2 of 106 8-bit and 10 of 49 4-bit ones
-  // were up to 1.57 times as slow by group sums without this line, 1 and 2 with it
-  p.gtab.batch = p.gtab.cost <= batch_limit && (m.batch_start + m.batch_op * mean_work) * wgs / kCus <
-                                                   0.95 * (m.batch_own_start + m.batch_own_chan * slow * p.desc.n_chan) * own_rounds;
-  if (!p.gtab.use && !p.gtab.batch) p.gtab = GroupTables();
+  // the most instructions per block that pay: of the largest block in a single round, else (and in
+  // a batch) of all on average
+  double max_work;
+  if (batch) {
+    const double own = 0.95 * (m.batch_own_start + m.batch_own_chan * slow * p.desc.n_chan) * own_rounds;
+    max_work = (own / rounds - m.batch_start) / m.batch_op;
+  } else {
+    const double own = (bits == 4 ? 0.95 : 1.0) *
+                       (own_rounds <= 0.5 ? m.own_start + m.alone * m.own_chan * slow * p.desc.n_chan
+                                          : launch_us(own_wg, own_wg, own_rounds, m.own_overlap, m.own_tail));
+    max_work = ((rounds <= 1 ? own : own / (m.overlap * (rounds + m.tail))) - m.start) / m.op;
+  }
+  if (max_work <= 0) return false;
+  const GroupTables *g = &p.gtab;
+  if (p.gtab.data.empty()) {
+    if (!build_group_tables(p.shift.data(), p.desc.n_dm, p.desc.n_chan, bits, p.in_pitch_bytes, t, limit, max_work) ||
+        t->data.size() * 4 > p.def_table_bytes) {
+      *t = GroupTables();
+      return false;
+    }
+    g = t;
+  }
+  const bool pays = g->cost <= limit && (rounds <= 1 && !batch ? g->max_work : g->work / (double)n_blk) < max_work;
+  if (!pays) *t = GroupTables();
+  return pays;
 }
 
 // Whether a direction of a float plan runs by quad sums (quad_f32.hip) instead of its
@@ -504,7 +544,7 @@ static void choose_quads(dd_plan &p, int dir) {
   }
   QuadTables q;
   if (!rows || !build_quad_tables(sh, rows, &q) ||
-      q.data.size() * 4 > up256(t.offs.size() * 2) + up256(t.sbase.size() * 4))  // (they take those tables' place)
+      q.data.size() * 4 > up256(t.offs_count * 2) + up256(t.sbase_count * 4))  // (they take those tables' place)
     return;
   if (t.per_wave == 2) {
     const double start = rows == 64 ? 8.30 : 6.78, rec = rows == 64 ? 0.307 : 0.42, quad = rows == 64 ? 0.255 : 0.071;
@@ -527,14 +567,25 @@ static void choose_quads(dd_plan &p, int dir) {
 dd_status choose_forward_tiles(dd_plan &p) {
   dd_status st = choose_shapes(p);
   if (st != DD_OK) return st;
-  choose_group_sums(p);
-  if (p.desc.dtype == DD_F32)
-    for (int dir = 0; dir < 2; ++dir) choose_quads(p, dir);
-  if (p.desc.dtype != DD_F32 && !p.gtab.use) {
-    const bool batch = p.gtab.batch;
-    st = set_tiles(p, 0, p.fwd.shape, p.fwd.order);  // fill its tables
-    p.gtab.batch = batch;
+  p.def_fwd = p.fwd;
+  p.def_table_bytes = table_bytes(p);
+  // the tables of shared sums, or those of the shapes that they do not replace
+  if (p.desc.dtype == DD_F32) {
+    for (int dir = 0; dir < 2 && st == DD_OK; ++dir) {
+      choose_quads(p, dir);
+      const FloatTables &t = dir ? p.ftab_adj : p.ftab_fwd;
+      if (!p.qtab[dir].use) st = set_tiles(p, dir, t.shape, t.order);
+    }
+  } else {
+    GroupTables t;
+    if (build_group_sums(p, false, &t)) {
+      p.gtab = std::move(t);
+      p.gtab.use = true;
+    } else {
+      st = set_tiles(p, 0, p.fwd.shape, p.fwd.order);
+    }
   }
+  p.chosen = false;
   return st;
 }
 
@@ -550,9 +601,9 @@ TableLayout table_layout(const dd_plan &p) {
   const FloatTables *tabs[2] = {&p.ftab_fwd, &p.ftab_adj};
   for (int k = 0; k < 2; ++k) {
     L.f_offs[k] = off;
-    off += up256(tabs[k]->offs.size() * 2);
+    off += up256(tabs[k]->offs_count * 2);
     L.f_sbase[k] = off;
-    off += up256(tabs[k]->sbase.size() * 4);
+    off += up256(tabs[k]->sbase_count * 4);
   }
   return L;
 }
@@ -561,8 +612,8 @@ size_t table_bytes(const dd_plan &p) {
   if (p.desc.dtype != DD_F32 && is_direct(p.fwd)) return up256(p.shift.size() * sizeof(int32_t));
   if (p.desc.dtype != DD_F32)
     return up256(p.itab.offs_words * sizeof(uint32_t)) + up256(p.itab.sbase_words * sizeof(int32_t));
-  return up256(p.ftab_fwd.offs.size() * 2) + up256(p.ftab_fwd.sbase.size() * 4) + up256(p.ftab_adj.offs.size() * 2) +
-         up256(p.ftab_adj.sbase.size() * 4);
+  return up256(p.ftab_fwd.offs_count * 2) + up256(p.ftab_fwd.sbase_count * 4) + up256(p.ftab_adj.offs_count * 2) +
+         up256(p.ftab_adj.sbase_count * 4);
 }
 
 // Table sizes follow the layouts of build_int_tables / build_float_tables

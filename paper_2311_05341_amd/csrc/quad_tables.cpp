@@ -88,7 +88,12 @@ void order_patterns(Quad *q, int rows) {
 }
 
 struct Task {
-  int quad, p0, p1, chunk;
+  int run, chunk;
+};
+
+// A run of a quad's patterns [p0, p1): its records, first operation block.
+struct Run {
+  int quad, p0, p1;
   size_t recs, op0;
 };
 
@@ -97,31 +102,37 @@ struct Op {
   int32_t start;
 };
 
-// Append the operation blocks that build patterns [p0, p1) of quad k; returns how many.
-size_t task_ops(const Quad &q, int k, int p0, int p1, int n_rows, std::vector<uint32_t> *out) {
-  std::vector<Op> ops;
+// How many operation blocks build patterns [p0, p1): four rows, then each change of a row.
+size_t run_blocks(const Quad &q, int p0, int p1) {
+  int ops = 4;
+  for (int p = p0 + 1; p < p1; ++p) ops += changes(q.pat[p - 1], q.pat[p]);
+  return (size_t)(ops + kQuadOps - 1) / kQuadOps;
+}
+
+// Append these operation blocks, of quad k.
+void run_ops(const Quad &q, int k, int p0, int p1, int n_rows, std::vector<uint32_t> *out) {
+  Op ops[4 + 3 * kMaxOutputs];
+  size_t n_ops = 0;
   for (int p = p0; p < p1; ++p) {
     const int32_t *r = q.pat[p].r;
-    if (p == p0) ops.push_back({0, 0});
+    if (p == p0) ops[n_ops++] = {0, 0};
     for (uint32_t c = 1; c < 4; ++c)
-      if (p == p0 || r[c - 1] != q.pat[p - 1].r[c - 1]) ops.push_back({c, r[c - 1]});
-    ops.back().kind |= kQuadWrite;
+      if (p == p0 || r[c - 1] != q.pat[p - 1].r[c - 1]) ops[n_ops++] = {c, r[c - 1]};
+    ops[n_ops - 1].kind |= kQuadWrite;
   }
-  size_t n = 0;
-  for (size_t o = 0; o < ops.size(); o += kQuadOps, ++n) {
+  for (size_t o = 0; o < n_ops; o += kQuadOps) {
     int32_t least = INT32_MAX;
-    for (size_t e = o; e < std::min(o + kQuadOps, ops.size()); ++e) least = std::min(least, ops[e].start);
+    for (size_t e = o; e < std::min(o + kQuadOps, n_ops); ++e) least = std::min(least, ops[e].start);
     uint32_t w[kQuadOpWords] = {(uint32_t)k << 15 | (uint32_t)q.words, 0, (uint32_t)(q.base + least), 0, 0};
     for (size_t e = 0; e < kQuadOps; ++e) {  // spare operations repeat the last window
-      const bool spare = o + e >= ops.size();
-      const Op &op = ops[spare ? ops.size() - 1 : o + e];
+      const bool spare = o + e >= n_ops;
+      const Op &op = ops[spare ? n_ops - 1 : o + e];
       w[1] |= (spare ? op.kind & 3 : op.kind) << (4 * e);
       if (4 * k + (int)(op.kind & 3) >= n_rows) w[1] |= kQuadNone << (4 * e);
       w[3 + e / 2] |= (uint32_t)(op.start - least) << (16 * (e % 2));
     }
     out->insert(out->end(), w, w + kQuadOpWords);
   }
-  return n;
 }
 
 struct Block {
@@ -148,44 +159,56 @@ void build_block(const QuadShifts &sh, int b, int rows, int nqp, uint16_t *sums,
       B.hi = std::max<int64_t>(B.hi, (int64_t)q.base + r.second + q.chunks(rows) * 64 * quad_lane_words(rows));
     }
   }
+  std::vector<Run> runs, best_runs;
+  std::vector<Task> todo, best;
+  std::vector<int> wave, best_wave;
+  size_t best_load = 0, best_simd = 0;
   for (int i = 0; i < nq;) {
     const uint32_t set = (B.steps.size() / kQuadStepWords & 1) * kQuadSetBytes;
     int j = i, bytes = 0;
     while (j < nq && j < i + kQuadStep && bytes + quads[j].bytes() <= kQuadSetBytes) bytes += quads[j++].bytes();
     // Tasks: each chunk of each quad, its patterns in as many runs as leave the busiest
     // wave the fewest records; the longest first to the wave with the fewest.
-    std::vector<Task> todo, best;
-    std::vector<int> wave, best_wave;
-    std::vector<uint32_t> ops, best_ops;
-    const size_t op0 = B.ops.size() / kQuadOpWords;
-    size_t best_load = SIZE_MAX, best_simd = 0;
-    for (int split = 1; split <= 4; ++split) {
+    best_load = SIZE_MAX;
+    bool more = true;  // a quad has patterns left for another split
+    for (int split = 1; more && split <= 4; ++split) {
+      more = false;
+      runs.clear();
       todo.clear();
-      ops.clear();
+      wave.clear();
       for (int k = i; k < j; ++k) {
         const int n = std::min(split, quads[k].n_pat);
+        more |= quads[k].n_pat > split;
         for (int s = 0; s < n; ++s) {
           const int p0 = quads[k].n_pat * s / n, p1 = quads[k].n_pat * (s + 1) / n;
-          const size_t at = op0 + ops.size() / kQuadOpWords, recs = task_ops(quads[k], k, p0, p1, sh.n_rows, &ops);
-          for (int c = 0; c < quads[k].chunks(rows); ++c) todo.push_back({k, p0, p1, c, recs, at});
+          for (int c = 0; c < quads[k].chunks(rows); ++c) todo.push_back({(int)runs.size(), c});
+          runs.push_back({k, p0, p1, run_blocks(quads[k], p0, p1), 0});
         }
       }
-      std::stable_sort(todo.begin(), todo.end(), [](const Task &x, const Task &y) { return x.recs > y.recs; });
+      std::stable_sort(todo.begin(), todo.end(),
+                       [&](const Task &x, const Task &y) { return runs[x.run].recs > runs[y.run].recs; });
       size_t load[kQuadWaves] = {}, simd[4] = {}, total = 0;
-      wave.clear();
       for (const Task &x : todo) {
         const int w = (int)(std::min_element(load, load + kQuadWaves) - load);
-        load[w] += x.recs;
-        simd[w & 3] += x.recs;
-        total += x.recs;
+        load[w] += runs[x.run].recs;
+        simd[w & 3] += runs[x.run].recs;
+        total += runs[x.run].recs;
         wave.push_back(w);
       }
       const size_t v = kQuadWaves * *std::max_element(load, load + kQuadWaves) + total;
-      if (v < best_load)
-        best_load = v, best_simd = *std::max_element(simd, simd + 4), best = todo, best_wave = wave, best_ops = ops;
+      if (v < best_load) {
+        best_load = v;
+        best_simd = *std::max_element(simd, simd + 4);
+        best.swap(todo);
+        best_wave.swap(wave);
+        best_runs.swap(runs);
+      }
     }
     B.records += (double)best_simd;
-    B.ops.insert(B.ops.end(), best_ops.begin(), best_ops.end());
+    for (Run &r : best_runs) {
+      r.op0 = B.ops.size() / kQuadOpWords;
+      run_ops(quads[r.quad], r.quad, r.p0, r.p1, sh.n_rows, &B.ops);
+    }
     uint32_t slot[kQuadStep], at = set / 4;
     for (int k = i; k < j; ++k) {
       const Quad &q = quads[k];
@@ -202,14 +225,14 @@ void build_block(const QuadShifts &sh, int b, int rows, int nqp, uint16_t *sums,
       const size_t mark = rec.size();
       for (size_t x = 0; x < best.size(); ++x) {
         if (best_wave[x] != w) continue;
-        const Task &y = best[x];
+        const Run &y = best_runs[best[x].run];
         const Quad &q = quads[y.quad];
-        const int chunk = 64 * quad_lane_words(rows) * y.chunk;
+        const int chunk = 64 * quad_lane_words(rows) * best[x].chunk;
         uint32_t dst = slot[y.quad - i] + (uint32_t)(y.p0 * q.words + chunk);
         for (size_t k = 0; k < y.recs; ++k) {
           const size_t o = y.op0 + k;
           rec.push_back((uint32_t)o);
-          rec.push_back(dst << 16 | (uint32_t)y.chunk);
+          rec.push_back(dst << 16 | (uint32_t)best[x].chunk);
           for (int e = 0; e < kQuadOps; ++e)
             if (B.ops[o * kQuadOpWords + 1] >> (4 * e) & kQuadWrite) dst += (uint32_t)q.words;
         }
@@ -248,7 +271,7 @@ bool build_quad_tables(const QuadShifts &sh, int rows, QuadTables *t) {
   try {
     std::vector<Block> blocks(n_blk);
     std::vector<uint16_t> sums((size_t)n_blk * kQuadWaves * nqp * per_wave, 0);
-    const int nthr = (int)std::min<int64_t>({kMaxParts, n_blk, std::max<int64_t>(1, (int64_t)n_blk * nq / 512),
+    const int nthr = (int)std::min<int64_t>({kMaxParts, n_blk, std::max<int64_t>(1, (int64_t)n_blk * nq / 64),
                                              std::max(1u, std::thread::hardware_concurrency())});
     uint8_t failed[kMaxParts] = {};
     run_parts(nthr, [&](int k) {

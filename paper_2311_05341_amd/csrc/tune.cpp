@@ -161,7 +161,7 @@ dd_status dd_plan_autotune(dd_plan *p, int32_t dir, const void *src, float *dst,
   int orig_shape, orig_order;
   current_tiles(*p, dir, &orig_shape, &orig_order);
   // set_tiles leaves the group and quad tables, not their use
-  const bool orig_use = p->gtab.use, orig_batch = p->gtab.batch, orig_quads = p->qtab[dir].use;
+  const bool orig_use = p->gtab.use, orig_chosen = p->chosen, orig_quads = p->qtab[dir].use;
   p->bound = false;
   const int64_t out_len = dir == 0 ? p->n_out : p->desc.n_samp;
   // Timed span: an eighth of the job (so that the input streamed per output
@@ -236,7 +236,7 @@ dd_status dd_plan_autotune(dd_plan *p, int32_t dir, const void *src, float *dst,
     (void)hipStreamSynchronize(st);  // no upload may still read host tables that set_tiles replaces
     set_tiles(*p, dir, orig_shape, orig_order);
     p->gtab.use = orig_use;
-    p->gtab.batch = orig_batch;
+    p->chosen = orig_chosen;
     p->qtab[dir].use = orig_quads;
     p->bound = false;
     return fail(status, msg);
@@ -252,7 +252,7 @@ dd_status dd_plan_autotune(dd_plan *p, int32_t dir, const void *src, float *dst,
   status = set_tiles(*p, dir, best_shape, best_order);
   if (status == DD_OK && best_shape == orig_shape && best_order == orig_order) {
     p->gtab.use = orig_use;
-    p->gtab.batch = orig_batch;
+    p->chosen = orig_chosen;
     p->qtab[dir].use = orig_quads;
   }
   if (status == DD_OK) status = upload_tables(*p, ws, stream);

@@ -63,3 +63,17 @@ def test_float_default_is_the_faster_kernel(dd, row):
     t = p.tiles(d)
     p.set_tiles(d, t["shape"], t["order"])  # that direction only
     assert not p.shares_sums(d) and p.shares_sums(1 - d) == other
+
+
+@pytest.mark.parametrize("dtype", ["u8", "u4", "u16", "f32"])
+@pytest.mark.parametrize("n_dm", [1, 33, 300])
+def test_workspace_is_that_of_the_default_shapes(dd, dtype, n_dm):
+    """Tables that shared sums take the place of are sized without being filled in."""
+    p = _plan(dd, dtype, 512, 40000, n_dm, 0.0, 0.25, 1500.0, 128.0)
+    dirs = (0, 1) if dtype == "f32" else (0,)
+    assert any(p.shares_sums(d) for d in dirs) or n_dm == 1
+    want = p.info.dev_table_bytes
+    for d in dirs:
+        t = p.tiles(d)
+        p.set_tiles(d, t["shape"], t["order"])
+        assert p.info.dev_table_bytes == want and p.info.tune_ws_bytes >= want
