@@ -251,8 +251,10 @@ dd_status dd_execute_adjoint(const dd_plan *plan, const float *d_y, int64_t y_pi
  *   dd_plan_query, 16-byte aligned) receives each candidate's tables; on
  *   success the plan is bound to d_ws with the winner's tables.  If the
  *   environment variable DD_TUNE_CACHE names a file, the winner is appended to
- *   it (one text line per plan and direction) and later dd_plan_create calls
- *   for an identical plan description apply it.  *report may be NULL.
+ *   it (one text line per plan and direction: its shape and order, and whether
+ *   it is the shape's own kernel or shared sums) and later dd_plan_create calls
+ *   for an identical plan description apply it.  A line of a library without shared
+ *   sums is ignored for a direction that runs by them.  *report may be NULL.
  *   Errors: DD_ERR_ARG, DD_ERR_ALIGN, DD_ERR_DTYPE, DD_ERR_HIP (plan unbound then).
  */
 dd_status dd_plan_shape_count(const dd_plan *plan, int32_t *n);

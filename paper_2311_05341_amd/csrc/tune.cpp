@@ -33,6 +33,10 @@ static void current_tiles(const dd_plan &p, int dir, int *shape, int *order) {
   }
 }
 
+static bool shares_sums(const dd_plan &p, int dir) {
+  return p.desc.dtype == DD_F32 ? p.qtab[dir].use : dir == 0 && p.gtab.use;
+}
+
 // FNV-1a over a byte range (identifies an explicit frequency table).
 static uint64_t fnv1a(const void *data, size_t n, uint64_t h = 1469598103934665603ull) {
   const uint8_t *b = (const uint8_t *)data;
@@ -53,9 +57,12 @@ static std::string cache_key(const dd_plan &p, int dir) {
   return buf;
 }
 
-// Cache line: "<tag> <key> <shape> <order> <ns> <per_wave> <waves> <row_block> <ms>".
+// Cache line: "<tag> <key> <shape> <order> <ns> <per_wave> <waves> <row_block> <ms> <sums>".
 // The shape's parameters are stored too, so a line written by a library with
-// a different list of compiled shapes is ignored rather than misapplied.
+// a different list of compiled shapes is ignored rather than misapplied.  sums: 1 if
+// shared sums were the fastest, 0 if the shape's own kernel was.  A line that ends before
+// it comes from a library without shared sums: it was not compared with them, and says
+// nothing about a direction that runs by them.
 void apply_tune_cache(dd_plan &p) {
   const char *path = getenv("DD_TUNE_CACHE");
   if (!path || !*path) return;
@@ -63,33 +70,32 @@ void apply_tune_cache(dd_plan &p) {
   FILE *f = fopen(path, "r");
   if (!f) return;
   const int dirs = p.desc.dtype == DD_F32 ? 2 : 1;
-  int want_shape[2] = {-1, -1}, want_order[2] = {0, 0};
+  int want_shape[2] = {-1, -1}, want_order[2] = {0, 0}, want_sums[2] = {0, 0};
   std::string keys[2];
   for (int dir = 0; dir < dirs; ++dir) keys[dir] = cache_key(p, dir);
   char line[1024];
   while (fgets(line, sizeof line, f)) {
     char tag[32], key[600];
-    int shape, order, k[4];
+    int shape, order, k[4], sums = -1;
     double ms;
-    if (sscanf(line, "%31s %599s %d %d %d %d %d %d %lf", tag, key, &shape, &order, &k[0], &k[1], &k[2], &k[3], &ms) != 9)
+    if (sscanf(line, "%31s %599s %d %d %d %d %d %d %lf %d", tag, key, &shape, &order, &k[0], &k[1], &k[2], &k[3], &ms,
+               &sums) < 9)
       continue;
     if (strcmp(tag, kCacheTag) != 0) continue;
     for (int dir = 0; dir < dirs; ++dir) {
       if (keys[dir] != key || shape < 0 || shape >= num_shapes(p)) continue;
+      if (sums != 0 && (sums == 1) != shares_sums(p, dir)) continue;
       const int *s = shape_params(p, shape);
       if (s[0] != k[0] || s[1] != k[1] || s[2] != k[2] || s[3] != k[3]) continue;
       want_shape[dir] = shape;  // the last matching line wins
       want_order[dir] = order;
+      want_sums[dir] = sums == 1;
     }
   }
   fclose(f);
   for (int dir = 0; dir < dirs; ++dir)
-    if (want_shape[dir] >= 0) {
-      // the default choice keeps its group sums; another one is set (the default stays on failure)
-      int shape, order;
-      current_tiles(p, dir, &shape, &order);
-      if (want_shape[dir] != shape || want_order[dir] != order) set_tiles(p, dir, want_shape[dir], want_order[dir]);
-    }
+    if (want_shape[dir] >= 0 && !want_sums[dir])
+      set_tiles(p, dir, want_shape[dir], want_order[dir]);  // keeps the default on failure, as do shared sums
 }
 
 static void append_tune_cache(const dd_plan &p, int dir, int shape, int order, double ms) {
@@ -99,8 +105,8 @@ static void append_tune_cache(const dd_plan &p, int dir, int shape, int order, d
   FILE *f = fopen(path, "a");
   if (!f) return;
   const int *s = shape_params(p, shape);
-  fprintf(f, "%s %s %d %d %d %d %d %d %.6f\n", kCacheTag, cache_key(p, dir).c_str(), shape, order, s[0], s[1], s[2],
-          s[3], ms);
+  fprintf(f, "%s %s %d %d %d %d %d %d %.6f %d\n", kCacheTag, cache_key(p, dir).c_str(), shape, order, s[0], s[1], s[2],
+          s[3], ms, (int)shares_sums(p, dir));
   fclose(f);
 }
 
@@ -118,7 +124,7 @@ dd_status dd_plan_shape_count(const dd_plan *p, int32_t *n) {
 
 int32_t dd_plan_shares_sums(const dd_plan *p, int32_t dir) {
   if (!p || (dir != 0 && dir != 1)) return 0;
-  return p->desc.dtype == DD_F32 ? p->qtab[dir].use : dir == 0 && p->gtab.use;
+  return shares_sums(*p, dir);
 }
 
 dd_status dd_plan_get_tiles(const dd_plan *p, int32_t dir, dd_tiles *t) {

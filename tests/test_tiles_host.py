@@ -179,3 +179,42 @@ def test_16bit_default_takes_the_phase_load_shape(dd):
         first = p.tiles(0)
         break
     assert first is not None and first["row_block"] <= 4 and key(first) != (16, 4, 8, 4)
+
+
+@pytest.mark.parametrize("dtype,code", [("u8", 1), ("f32", 3)])
+def test_tune_cache_tells_shared_sums_from_shapes(dd, tmp_path, monkeypatch, dtype, code):
+    """Lines end with the kernel that was the fastest; one that does not say was not compared with
+    shared sums, and does not take a plan off them."""
+    cfg = dict(dtype=dtype, n_chan=1024, n_samp=65536, f_high=1500.0, chan_bw=300.0 / 1024, t_samp=128e-6, dm_start=0.0,
+               dm_step=0.25, n_dm=500)
+    p0 = _plan(dd, cfg)
+    assert p0.shares_sums(0)
+    t = p0.tiles(0)
+    params = "%d %d %d %d" % (t["ns"], t["per_wave"], t["waves"], t["row_block"])
+    key = _cache_key(cfg, code, p0.in_pitch_bytes, 0)
+    path = tmp_path / "tune.txt"
+    monkeypatch.setenv("DD_TUNE_CACHE", str(path))
+    other = (t["order"] + 1) % 4
+
+    def made(*lines):
+        path.write_text("".join("dd-tune-v2 %s %d %d %s 1.0%s\n" % (key, t["shape"], o, params, end) for o, end in lines))
+        p = _plan(dd, cfg)
+        return p.shares_sums(0), p.tiles(0)["shape"], p.tiles(0)["order"]
+
+    default = (True, t["shape"], t["order"])
+    assert made((other, "")) == default and made((t["order"], "")) == default
+    assert made((other, " 0")) == (False, t["shape"], other)
+    assert made((t["order"], " 0")) == (False, t["shape"], t["order"])
+    assert made((t["order"], " 1")) == default
+    assert made((other, " 0"), (t["order"], " 1")) == default  # the last line wins
+    assert made((t["order"], " 1"), (other, " 0")) == (False, t["shape"], other)
+    assert made((other, " 0"), (other, "")) == (False, t["shape"], other)
+    small = dict(cfg, n_chan=16, n_dm=4)  # too small for shared sums: any line counts, but one of theirs
+    q0 = _plan(dd, small)
+    assert not q0.shares_sums(0)
+    cfg, key = small, _cache_key(small, code, q0.in_pitch_bytes, 0)
+    t = q0.tiles(0)
+    params = "%d %d %d %d" % (t["ns"], t["per_wave"], t["waves"], t["row_block"])
+    other = (t["order"] + 1) % 4
+    assert made((other, "")) == made((other, " 0")) == (False, t["shape"], other)
+    assert made((other, " 1")) == (False, t["shape"], t["order"])
