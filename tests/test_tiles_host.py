@@ -209,7 +209,7 @@ def test_tune_cache_tells_shared_sums_from_shapes(dd, tmp_path, monkeypatch, dty
     assert made((other, " 0"), (t["order"], " 1")) == default  # the last line wins
     assert made((t["order"], " 1"), (other, " 0")) == (False, t["shape"], other)
     assert made((other, " 0"), (other, "")) == (False, t["shape"], other)
-    small = dict(cfg, n_chan=16, n_dm=4)  # too small for shared sums: any line counts, but one of theirs
+    small = dict(cfg, n_chan=1)  # one channel has no sums to share: any line counts, but one of theirs
     q0 = _plan(dd, small)
     assert not q0.shares_sums(0)
     cfg, key = small, _cache_key(small, code, q0.in_pitch_bytes, 0)
