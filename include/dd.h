@@ -236,7 +236,8 @@ dd_status dd_execute_adjoint(const dd_plan *plan, const float *d_y, int64_t y_pi
  *   workgroup order `order` (0 to 3).  DD_ERR_RANGE (plan unchanged) if the shape
  *   cannot stage the plan's delay spread.  On success the plan is unbound:
  *   query dev_table_bytes again and call dd_plan_bind before executing.
- * dd_plan_autotune: time every (shape, order) that holds the plan's spread and
+ * dd_plan_autotune: time every (shape, order) that holds the plan's spread, and shared
+ *   sums where they are the direction's default (also after tiles were chosen), and
  *   keep the fastest (the current choice stays unless another is at least 2%
  *   faster).  Each candidate runs on the caller's buffers over the first
  *   timed_out_samples output samples of every row (all of them for small plans;
@@ -297,7 +298,7 @@ dd_status dd_plan_autotune(dd_plan *plan, int32_t direction, const void *d_src, 
  *   the beams' plans: staged or direct-read; DD_ERR_RANGE, batch unchanged, if a beam cannot
  *   be staged with it); unbinds the batch, which keeps its workspace size.
  * dd_batch_autotune: with the arguments of dd_batch_bind, time the current assignment, every
- *   beam at its default shape, and every staged shape with at least 32 DM rows per workgroup and
+ *   beam at its default shape (with shared sums wherever they pay, and without), and every staged shape with at least 32 DM rows per workgroup and
  *   every direct-read shape for all beams, each on the whole batch (one warm-up replay, one timed replay with HIP events on
  *   `stream`); keep the fastest (the current one stays unless another is at least 2% faster) and
  *   leave the batch bound with it.  Outputs are overwritten.  Synchronises `stream`.  *report may

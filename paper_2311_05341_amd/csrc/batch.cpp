@@ -460,8 +460,8 @@ dd_status dd_batch_autotune(dd_batch *b, const void *const *d_in, float *const *
     *ms = t;
     return DD_OK;
   };
-  // Candidates: the current assignment, every beam at its default (and there without group sums), and
-  // every staged shape with at least 32 DM rows per workgroup, and every
+  // Candidates: the current assignment, every beam at its default (there with group sums wherever they
+  // pay, and without), and every staged shape with at least 32 DM rows per workgroup, and every
   // direct-read shape, shared by all beams (smaller staged ones only pay where
   // a beam's default had to fall back to them).
   const std::vector<char> none(b->plans.size(), 0);
@@ -469,11 +469,15 @@ dd_status dd_batch_autotune(dd_batch *b, const void *const *d_in, float *const *
   cands.push_back(orig);
   const Assignment defaults = default_assignment(b);
   if (!(defaults == orig)) cands.push_back(defaults);
-  if (defaults.sums != none) cands.push_back({defaults.shapes, none});
+  Assignment sums = defaults;  // (a plan's tiles chosen explicitly keep its beam's default off them)
+  for (size_t i = 0; i < b->plans.size(); ++i) sums.sums[i] = sums_pay(b, i);
+  if (!(sums == orig) && !(sums == defaults)) cands.push_back(sums);
+  const Assignment plain = {defaults.shapes, none};
+  if (!(plain == orig) && !(plain == defaults)) cands.push_back(plain);
   for (int s = 0; s < num_batch_shapes(); ++s) {
     if (!direct_shape(s) && kIntShapes[s][1] * kIntShapes[s][2] < 32) continue;
     const Assignment all = {std::vector<int>(b->plans.size(), s), none};
-    if (!(all == orig) && !(all == defaults)) cands.push_back(all);
+    if (!(all == orig) && !(all == defaults) && !(all == plain)) cands.push_back(all);
   }
   double default_ms = 0.0, best_ms = 0.0;
   size_t best = 0;

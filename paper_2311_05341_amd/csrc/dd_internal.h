@@ -87,7 +87,8 @@ struct dd_plan {
   dd::IntTables itab;          // integer plans: staged forward kernel's tables (sizes only while gtab is in use)
   dd::GroupTables gtab;        // integer plans that run by group sums by default: their tables
   dd::TileCfg def_fwd;         // default forward tile shape,
-  size_t def_table_bytes = 0;  // and the default shapes' table bytes
+  size_t def_table_bytes = 0;  // the default shapes' table bytes
+  int def_shape[2] = {}, def_order[2] = {};  // and, by direction, the default shape and order
   bool chosen = false;         // integer plans: tiles chosen explicitly (no group sums in a batch)
   dd::FloatTables ftab_fwd;    // float plans: forward kernel tables
   dd::FloatTables ftab_adj;    // float plans: adjoint kernel tables

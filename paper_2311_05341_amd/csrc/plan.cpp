@@ -569,6 +569,10 @@ dd_status choose_forward_tiles(dd_plan &p) {
   if (st != DD_OK) return st;
   p.def_fwd = p.fwd;
   p.def_table_bytes = table_bytes(p);
+  p.def_shape[0] = p.fwd.shape;
+  p.def_order[0] = p.fwd.order;
+  p.def_shape[1] = p.ftab_adj.shape;
+  p.def_order[1] = p.ftab_adj.order;
   // the tables of shared sums, or those of the shapes that they do not replace
   if (p.desc.dtype == DD_F32) {
     for (int dir = 0; dir < 2 && st == DD_OK; ++dir) {

@@ -37,6 +37,31 @@ static bool shares_sums(const dd_plan &p, int dir) {
   return p.desc.dtype == DD_F32 ? p.qtab[dir].use : dir == 0 && p.gtab.use;
 }
 
+// What a direction runs: a shape's own kernel, or shared sums (with the shape and order whose
+// workspace they use).
+struct Choice {
+  int shape = 0, order = 0;
+  bool sums = false;
+  bool operator==(const Choice &o) const { return shape == o.shape && order == o.order && sums == o.sums; }
+};
+
+// The choice of shared sums, where the plan holds their tables (it does where they were its default).
+static bool sums_choice(const dd_plan &p, int dir, Choice *c) {
+  const bool f32 = p.desc.dtype == DD_F32;
+  if (f32 ? p.qtab[dir].data.empty() : p.gtab.data.empty()) return false;
+  *c = {p.def_shape[dir], p.def_order[dir], true};
+  return true;
+}
+
+static dd_status apply(dd_plan *p, int dir, const Choice &c) {
+  const dd_status st = set_tiles(*p, dir, c.shape, c.order);
+  if (st == DD_OK && c.sums) {
+    (p->desc.dtype == DD_F32 ? p->qtab[dir].use : p->gtab.use) = true;
+    if (dir == 0) p->chosen = false;
+  }
+  return st;
+}
+
 // FNV-1a over a byte range (identifies an explicit frequency table).
 static uint64_t fnv1a(const void *data, size_t n, uint64_t h = 1469598103934665603ull) {
   const uint8_t *b = (const uint8_t *)data;
@@ -164,10 +189,10 @@ dd_status dd_plan_autotune(dd_plan *p, int32_t dir, const void *src, float *dst,
   int dev = -1;
   if (p->bound && hipGetDevice(&dev) == hipSuccess && dev != p->device) p->bound = false;
 
-  int orig_shape, orig_order;
-  current_tiles(*p, dir, &orig_shape, &orig_order);
-  // set_tiles leaves the group and quad tables, not their use
-  const bool orig_use = p->gtab.use, orig_chosen = p->chosen, orig_quads = p->qtab[dir].use;
+  Choice orig;
+  current_tiles(*p, dir, &orig.shape, &orig.order);
+  orig.sums = shares_sums(*p, dir);
+  const bool orig_chosen = p->chosen;
   p->bound = false;
   const int64_t out_len = dir == 0 ? p->n_out : p->desc.n_samp;
   // Timed span: an eighth of the job (so that the input streamed per output
@@ -210,40 +235,40 @@ dd_status dd_plan_autotune(dd_plan *p, int32_t dir, const void *src, float *dst,
 
   dd_status status = DD_OK;
   double default_ms = 0.0, best_ms = 0.0;
-  int best_shape = orig_shape, best_order = orig_order, tried = 0;
+  Choice best = orig;
+  int tried = 0;
   status = time_current(&default_ms);
   if (status == DD_OK) {
     best_ms = default_ms;
     tried = 1;
-    for (int s = 0; s < num_shapes(*p) && status == DD_OK; ++s)
-      for (int o = 0; o < kNumOrders && status == DD_OK; ++o) {
-        if (s == orig_shape && o == orig_order) continue;
-        const dd_status ts = set_tiles(*p, dir, s, o);
-        if (ts == DD_ERR_RANGE) continue;  // this shape cannot stage the plan's spread
-        if (ts != DD_OK) {
-          status = ts;
-          break;
-        }
-        double ms = 0.0;
-        status = time_current(&ms);
-        if (status != DD_OK) break;
-        ++tried;
-        if (ms < best_ms) {
-          best_ms = ms;
-          best_shape = s;
-          best_order = o;
-        }
+    auto try_choice = [&](const Choice &c) {
+      if (c == orig) return;
+      status = apply(p, dir, c);
+      if (status == DD_ERR_RANGE) {  // this shape cannot stage the plan's spread
+        status = DD_OK;
+        return;
       }
+      double ms = 0.0;
+      if (status == DD_OK) status = time_current(&ms);
+      if (status != DD_OK) return;
+      ++tried;
+      if (ms < best_ms) {
+        best_ms = ms;
+        best = c;
+      }
+    };
+    Choice sums;
+    if (sums_choice(*p, dir, &sums)) try_choice(sums);
+    for (int s = 0; s < num_shapes(*p) && status == DD_OK; ++s)
+      for (int o = 0; o < kNumOrders && status == DD_OK; ++o) try_choice({s, o, false});
   }
   (void)hipEventDestroy(e0);
   (void)hipEventDestroy(e1);
   if (status != DD_OK) {
     const std::string msg = dd_last_error();
     (void)hipStreamSynchronize(st);  // no upload may still read host tables that set_tiles replaces
-    set_tiles(*p, dir, orig_shape, orig_order);
-    p->gtab.use = orig_use;
+    (void)apply(p, dir, orig);
     p->chosen = orig_chosen;
-    p->qtab[dir].use = orig_quads;
     p->bound = false;
     return fail(status, msg);
   }
@@ -251,16 +276,11 @@ dd_status dd_plan_autotune(dd_plan *p, int32_t dir, const void *src, float *dst,
   // three workgroup orders measure within 1% of each other on the tuning span and
   // rank differently on the whole job.
   if (best_ms > 0.98 * default_ms) {
-    best_shape = orig_shape;
-    best_order = orig_order;
+    best = orig;
     best_ms = default_ms;
   }
-  status = set_tiles(*p, dir, best_shape, best_order);
-  if (status == DD_OK && best_shape == orig_shape && best_order == orig_order) {
-    p->gtab.use = orig_use;
-    p->chosen = orig_chosen;
-    p->qtab[dir].use = orig_quads;
-  }
+  status = apply(p, dir, best);
+  if (status == DD_OK && best == orig) p->chosen = orig_chosen;
   if (status == DD_OK) status = upload_tables(*p, ws, stream);
   if (status == DD_OK) {
     const hipError_t se = hipStreamSynchronize(st);
@@ -270,7 +290,7 @@ dd_status dd_plan_autotune(dd_plan *p, int32_t dir, const void *src, float *dst,
     p->bound = false;
     return status;
   }
-  append_tune_cache(*p, dir, best_shape, best_order, best_ms);
+  append_tune_cache(*p, dir, best.shape, best.order, best_ms);
   if (rep) {
     memset(rep, 0, sizeof(*rep));
     rep->n_tried = tried;

@@ -234,3 +234,48 @@ def test_shortest_input_every_shape(dd, dtype):
         g = g.cpu().numpy().astype(np.float64)
         assert (np.abs(g - gw) <= 1e-5 * ga).all(), (s_, o)
         assert (g[ga == 0] == 0).all(), (s_, o)
+
+
+@pytest.mark.parametrize("dtype,direction", [("u8", 0), ("u16", 0), ("f32", 0), ("f32", 1)])
+def test_autotune_returns_to_shared_sums(dd, tmp_path, monkeypatch, dtype, direction):
+    """A plan taken off its shared sums by an explicit choice is tuned back to them where they are the
+    fastest (here by a factor of two), the cache records it, and the result stays bitwise the same."""
+    cache = tmp_path / "tune.txt"
+    monkeypatch.setenv("DD_TUNE_CACHE", str(cache))
+    cfg = dict(dtype=dtype, n_chan=1024, n_samp=40000, f_high=1500.0, chan_bw=300.0 / 1024, t_samp=256e-6, dm_start=0.0,
+               dm_step=0.1, n_dm=512)
+    plan = plan_for(dd, cfg)
+    assert plan.shares_sums(direction)
+    default = plan.tiles(direction)
+    g = torch.Generator(device="cuda")
+    g.manual_seed(3)
+    if dtype == "f32":
+        x = torch.randn((1024, 40000), device="cuda", generator=g)
+    else:
+        x = torch.randint(0, 256, (1024, 40000 * (2 if dtype == "u16" else 1)), dtype=torch.uint8, device="cuda", generator=g)
+        x = x.view(torch.uint16) if dtype == "u16" else x
+    y = torch.randn((512, plan.out_pitch), device="cuda", generator=g)
+    src = y if direction else x
+    dst = torch.empty((1024, 40000) if direction else (512, plan.out_pitch), device="cuda")
+
+    def run():
+        return (plan.adjoint(y)[:, :40000] if direction else plan.forward(x)[:, : plan.n_out]).clone()
+
+    want = run()
+    for shape in range(plan.n_shapes):
+        try:
+            plan.set_tiles(direction, shape, 0)
+            break
+        except dd.DDError as e:
+            assert e.name == "DD_ERR_RANGE"
+    assert not plan.shares_sums(direction) and torch.equal(run(), want)
+    rep = plan.autotune(src, dst, direction=direction)
+    print(dtype, direction, rep, flush=True)
+    assert plan.shares_sums(direction) and plan.tiles(direction) == default and rep["best"] == default
+    assert rep["best_ms"] < 0.8 * rep["default_ms"]
+    assert torch.equal(run(), want)
+    assert cache.read_text().split()[-1] == "1"
+    again = plan_for(dd, cfg)
+    assert again.shares_sums(direction) and again.tiles(direction) == default
+    rep = plan.autotune(src, dst, direction=direction)  # now the current choice, and still the fastest
+    assert plan.shares_sums(direction) and torch.equal(run(), want)
