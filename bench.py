@@ -456,12 +456,20 @@ def setup_batch48(dd, torch, synth, n_chunks=BATCH_CHUNKS, log=log):
 
 
 def batch_shapes(batch):
-    """Tile shapes a batch's beams run: {shape index: number of beams}."""
+    """What a batch's beams run: {shape index, or "shared sums": number of beams}."""
     counts = {}
     for b in range(len(batch.plans)):
-        s = batch.beam_tiles(b)["shape"]
+        s = "shared sums" if batch.shares_sums(b) else str(batch.beam_tiles(b)["shape"])
         counts[s] = counts.get(s, 0) + 1
-    return {str(k): v for k, v in sorted(counts.items())}
+    return dict(sorted(counts.items()))
+
+
+def batch_kernels(batch):
+    """The kernels a batch launches."""
+    names = {"fwd_group_batched_kernel" if batch.shares_sums(b) else
+             "fwd_direct_batched_kernel" if batch.beam_tiles(b)["row_block"] == 0 else "fwd_int_batched_kernel"
+             for b in range(len(batch.plans))}
+    return " + ".join(sorted(names))
 
 
 def timed_events(torch, fn, steps, warmup):
@@ -552,11 +560,13 @@ def bench_batch48(args, dd, torch, synth):
     stream = torch.cuda.current_stream()
     tune = None
     if not args.no_autotune:
-        # the batch autotuner on the first chunk's batch; the other chunks take its shape
+        # the batch autotuner on the first chunk's batch; the other chunks take its shape, if it is a
+        # common one of all beams
         t = time.perf_counter()
         tune = batches[0][1].autotune()
-        for _, bt in batches[1:]:
-            bt.set_tiles(tune["best"]["shape"])
+        if len(batch_shapes(batches[0][1])) == 1 and not batches[0][1].shares_sums(0):
+            for _, bt in batches[1:]:
+                bt.set_tiles(tune["best"]["shape"])
         torch.cuda.synchronize()
         tune["seconds"] = time.perf_counter() - t
         log("batch autotune: %s" % tune)
@@ -603,6 +613,9 @@ def bench_batch48(args, dd, torch, synth):
     kernel_ms = float(np.sum(launch_ms)) / args.steps
     achieved = adds / (kernel_ms * 1e-3) / 1e12
     beam_seconds = sum(b["n_samp"] * b["t_samp"] for b in beams)
+    # a batch of several kernels, or of shared sums, has no price per sample-add
+    plain_form = all(batch_kernels(bt) == "fwd_int_batched_kernel" for _, bt in batches)
+    peak = VALU_PEAK_TOPS if plain_form else None
     rec = {
         "metric": "Tadds/s (48 beams, batched)",
         "value": value,
@@ -625,11 +638,14 @@ def bench_batch48(args, dd, torch, synth):
                         "calls_per_step": sum(len(c) for c in chunkers)},
         "batched_over_plain": ms_plain / ms_batched,
         "x_realtime_beams": beam_seconds / (ms_batched * 1e-3),
-        "roofline": {"bound": "alu", "achieved": achieved, "peak": None, "unit": "Tadds/s",
-                     "frac": None, "traffic": None, "kernel": "fwd_group_batched_kernel and others",
-                     "kernel_ms": kernel_ms, "instruction_form": SHARED_FORM, "peak_instruction_form": None,
-                     "frac_instruction_form": None},
-        "lds_roofline": None,
+        "roofline": {"bound": "alu", "achieved": achieved, "peak": peak, "unit": "Tadds/s",
+                     "frac": achieved / peak if peak else None, "traffic": None,
+                     "kernel": batch_kernels(batches[0][1]), "kernel_ms": kernel_ms,
+                     "instruction_form": INT_FORM if peak else SHARED_FORM,
+                     "peak_instruction_form": 2 * peak if peak else None,
+                     "frac_instruction_form": achieved / (2 * peak) if peak else None},
+        "lds_roofline": {"achieved": achieved, "peak": LDS_PEAK_TBS, "unit": "TB/s", "frac": achieved / LDS_PEAK_TBS,
+                         "bytes_per_add": 1} if plain_form else None,
         "batch_tiles": batches[0][1].tiles(),
         "beams_per_shape": batch_shapes(batches[0][1]),
         "batch_autotune": tune,
@@ -683,9 +699,7 @@ def bench_batch_set(args, dd, torch, synth):
     torch.cuda.synchronize()
     same = all(torch.equal(g, o[:, : p.n_out]) for g, o, p in zip(got, outputs, plans))
     direct = all(p.tiles(0)["row_block"] == 0 for p in plans)
-    # the plans' own calls tell which beams share sums well; a beam of a batch may do so where
-    # its plan alone does not, so a mixed batch is priced by no one form either
-    shared = any(p.shares_sums(0) for p in plans)
+    shared = any(batch.shares_sums(b) for b in range(len(plans)))  # then no one form prices the batch
     form, per_op, lds_b = (SHARED_FORM, None, 0) if shared else accumulate_form(dtype, plans[0].tiles(0))
     achieved = adds / (b_ms * 1e-3) / 1e12
     rec = {
@@ -713,9 +727,7 @@ def bench_batch_set(args, dd, torch, synth):
         "batched_equals_plain": same,
         "roofline": {"bound": "alu", "achieved": achieved, "peak": None if shared else VALU_PEAK_TOPS, "unit": "Tadds/s",
                      "frac": None if shared else achieved / VALU_PEAK_TOPS, "traffic": None,
-                     "kernel": ("fwd_group_batched_kernel and others" if shared else
-                                "fwd_direct_batched_kernel" if direct else "fwd_int_batched_kernel"),
-                     "kernel_ms": b_ms, "kernel_ms_median": b_med, "instruction_form": form,
+                     "kernel": batch_kernels(batch), "kernel_ms": b_ms, "kernel_ms_median": b_med, "instruction_form": form,
                      "peak_instruction_form": per_op * VALU_PEAK_TOPS if per_op else None,
                      "frac_instruction_form": achieved / (per_op * VALU_PEAK_TOPS) if per_op else None},
         "lds_roofline": None if not lds_b else {"achieved": achieved * lds_b, "peak": LDS_PEAK_TBS, "unit": "TB/s",

@@ -294,6 +294,10 @@ dd_status dd_plan_autotune(dd_plan *plan, int32_t direction, const void *d_src, 
  * dd_batch_get_tiles: the shape every beam runs (order is always 0: work items are claimed
  *   dynamically), or shape = -1 and all other fields 0 when the beams run different shapes.
  * dd_batch_get_beam_tiles: the shape beam `beam` (0..n-1, the order of dd_batch_create) runs.
+ *   (In both, a beam that runs by shared sums counts with its plan's shape.)
+ * dd_batch_shares_sums: 1 if beam `beam` runs by shared sums, else 0 (also for a null batch or
+ *   no such beam).  By default a beam does where that is faster among many beams, whether or
+ *   not its plan's own calls do, unless the plan's tiles were chosen explicitly.
  * dd_batch_set_tiles: put every beam on compiled shape `shape` (below dd_plan_shape_count of
  *   the beams' plans: staged or direct-read; DD_ERR_RANGE, batch unchanged, if a beam cannot
  *   be staged with it); unbinds the batch, which keeps its workspace size.
@@ -312,6 +316,7 @@ dd_status dd_batch_bind(dd_batch *batch, const void *const *d_in, float *const *
 dd_status dd_execute_batched(dd_batch *batch, void *stream);
 dd_status dd_batch_get_tiles(const dd_batch *batch, dd_tiles *tiles);
 dd_status dd_batch_get_beam_tiles(const dd_batch *batch, int32_t beam, dd_tiles *tiles);
+int32_t dd_batch_shares_sums(const dd_batch *batch, int32_t beam);
 dd_status dd_batch_set_tiles(dd_batch *batch, int32_t shape);
 dd_status dd_batch_autotune(dd_batch *batch, const void *const *d_in, float *const *d_out, const int64_t *out_pitch,
                             void *d_workspace, size_t bytes, void *stream, dd_tune_report *report);

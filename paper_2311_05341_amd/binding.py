@@ -99,6 +99,8 @@ _lib.dd_batch_get_beam_tiles.argtypes = [_vp, _i32, ctypes.POINTER(Tiles)]
 _lib.dd_batch_get_beam_tiles.restype = _i32
 _lib.dd_batch_set_tiles.argtypes = [_vp, _i32]
 _lib.dd_batch_set_tiles.restype = _i32
+_lib.dd_batch_shares_sums.argtypes = [_vp, _i32]
+_lib.dd_batch_shares_sums.restype = _i32
 _lib.dd_batch_autotune.argtypes = [_vp, ctypes.POINTER(_vp), ctypes.POINTER(_vp), ctypes.POINTER(_i64), _vp, _sz, _vp,
                                    ctypes.POINTER(TuneReport)]
 _lib.dd_batch_autotune.restype = _i32
@@ -420,14 +422,18 @@ class Batch:
         _check(_lib.dd_batch_get_beam_tiles(self._h, int(beam), ctypes.byref(t)), "dd_batch_get_beam_tiles")
         return t.as_dict()
 
+    def shares_sums(self, beam) -> bool:
+        """Whether beam `beam` runs by shared sums instead of its shape's kernel."""
+        return bool(_lib.dd_batch_shares_sums(self._h, int(beam)))
+
     def set_tiles(self, shape, stream=None):
         """Put every beam on compiled shape `shape` (staged or direct-read) and re-bind."""
         _check(_lib.dd_batch_set_tiles(self._h, int(shape)), "dd_batch_set_tiles")
         self.bind(stream)
 
     def autotune(self, stream=None) -> dict:
-        """Time the per-beam default shapes and the shared staged and direct-read shapes on the whole
-        batch and keep the fastest (dd_batch_autotune); outputs are overwritten."""
+        """Time the per-beam defaults (with and without shared sums) and the common staged and
+        direct-read shapes on the whole batch and keep the fastest (dd_batch_autotune); outputs are overwritten."""
         ins, outs, pitches = self._bind_args()
         rep = TuneReport()
         _check(_lib.dd_batch_autotune(self._h, ins, outs, pitches, self.workspace.data_ptr(), self.workspace.numel(),

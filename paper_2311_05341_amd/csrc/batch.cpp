@@ -423,6 +423,10 @@ dd_status dd_batch_get_beam_tiles(const dd_batch *b, int32_t beam, dd_tiles *t) 
   return DD_OK;
 }
 
+int32_t dd_batch_shares_sums(const dd_batch *b, int32_t beam) {
+  return b && beam >= 0 && (size_t)beam < b->sums.size() && b->sums[beam];
+}
+
 dd_status dd_batch_set_tiles(dd_batch *b, int32_t shape) {
   if (!b) return fail(DD_ERR_ARG, "null batch");
   if (shape < 0 || shape >= num_batch_shapes()) return fail(DD_ERR_ARG, "no such tile shape");
