@@ -6,9 +6,12 @@ import pytest
 import torch
 
 import oracle
-from helpers import plan_for
+from helpers import plan_for, sample_rows
 
 pytestmark = pytest.mark.gpu
+
+EPS = 2.0 ** -24
+
 
 @pytest.fixture(scope="module")
 def dd():
@@ -26,6 +29,85 @@ def _input(dtype, n_chan, n_samp, seed):
     x = np.full((n_chan, (n + unit - 1) // unit * unit), np.iinfo(elem).max, dtype=elem)
     x[:, :n] = rng.integers(0, np.iinfo(elem).max + 1, (n_chan, n), dtype=elem)
     return x
+
+
+def _check_int(dd, dtype, n_chan, n_samp, n_dm, start, step, freqs=None, shared=True):
+    bw = 0.0 if freqs is not None else 300.0 / n_chan
+    s = oracle.shift_table(n_chan, 1500.0, bw, 64e-6, start, step, n_dm, freqs=freqs)
+    x = _input(dtype, n_chan, n_samp, 7)
+    plan = dd.Plan(n_chan, n_samp, dtype, 1500.0, bw, 64e-6, start, step, n_dm, chan_freq=freqs,
+                   in_pitch_bytes=x.strides[0])
+    assert plan.shares_sums(0) == shared
+    picks = sample_rows(n_dm, every=max(1, n_dm // 12))
+    print("group %s n_chan=%d n_samp=%d n_dm=%d step=%g" % (dtype, n_chan, n_samp, n_dm, step), flush=True)
+    want = oracle.forward(x, dtype, n_samp, s, rows=picks)
+    xd = torch.from_numpy(x).cuda()
+    out = torch.full((plan.n_dm, plan.out_pitch + 8), -7.0, dtype=torch.float32, device="cuda")
+    got = plan.forward(xd, out=out).clone()
+    assert np.array_equal(got[picks].cpu().numpy(), want)
+    assert bool((out[:, plan.n_out:] == -7.0).all())
+    t = plan.tiles(0)
+    plan.set_tiles(0, t["shape"], t["order"])
+    assert not plan.shares_sums(0) and torch.equal(plan.forward(xd), got)
+
+
+# (channels, samples, trials, dm_start, dm_step, encodings that run by group sums): less than one
+# time tile, a ragged one, no delay, a partial last group, DM blocks with a tail, pattern rows of
+# five and seven chunks (seven in 16 bits from 64 rows)
+GROUP = [(1024, 3000, 130, 0.0, 0.1, "u8 u4 u16"), (257, 1026, 40, 0.0, 0.0, "u8 u4 u16"), (600, 9000, 96, 0.0, 0.1, "u8 u4 u16"),
+         (1001, 1030, 40, 0.0, 0.02, "u8 u4 u16"), (1024, 9000, 64, 0.0, 0.25, "u8 u4 u16"),
+         (4096, 4000, 64, 0.0, 1.0, "u8 u4 u16"), (8192, 4000, 33, 0.0, 2.0, "u8 u4"), (512, 32770, 97, 10.0, 0.25, "u4 u16")]
+
+
+@pytest.mark.parametrize("dtype", ["u8", "u4", "u16"])
+@pytest.mark.parametrize("case", GROUP)
+def test_group_sums(dd, case, dtype):
+    _check_int(dd, dtype, *case[:5], shared=dtype in case[5].split())
+
+
+@pytest.mark.parametrize("dtype", ["u8", "u4", "u16"])
+@pytest.mark.parametrize("near", [4, 16])
+def test_group_sums_of_unordered_channels(dd, dtype, near):
+    """Channels shuffled among their neighbours: delays that fall with the channel, so that windows
+    start before their group's and the tile's first sample."""
+    n_chan = 1024
+    order = np.random.default_rng(3).permuted(np.arange(n_chan).reshape(-1, near), axis=1).ravel()
+    _check_int(dd, dtype, n_chan, 12000, 96, 0.0, 0.05, freqs=1500.0 - order * (300.0 / n_chan))
+
+
+# rows that end one, two and three into a quad, with blocks of 64 and of 32 outputs, and (last) more than
+# 512 workgroups forward
+QUAD = [(1021, 9000, 130, 0.1), (514, 9000, 66, 0.25), (255, 20011, 129, 0.25), (65, 40000, 515, 0.1)]
+
+
+@pytest.mark.parametrize("case", QUAD)
+def test_quad_sums_and_what_lies_past_the_last_row(dd, case):
+    """The rows past the last of a quad are zeros, whatever lies there in memory: rows of NaN."""
+    n_chan, n_samp, n_dm, step = case
+    cfg = dict(dtype="f32", n_chan=n_chan, n_samp=n_samp, f_high=1500.0, chan_bw=300.0 / n_chan, t_samp=256e-6,
+               dm_start=0.0, dm_step=step, n_dm=n_dm)
+    pitch = (n_samp + 3) // 4 * 4
+    plan = plan_for(dd, cfg, in_pitch_bytes=4 * pitch)
+    assert plan.shares_sums(0) and plan.shares_sums(1)
+    s = oracle.shift_table(n_chan, 1500.0, 300.0 / n_chan, 256e-6, 0.0, step, n_dm)
+    rng = np.random.default_rng(n_chan)
+    x = np.full((n_chan + 4, pitch), np.nan, dtype=np.float32)
+    x[:n_chan, :n_samp] = rng.standard_normal((n_chan, n_samp))
+    y = np.full((n_dm + 4, plan.n_out), np.nan, dtype=np.float32)
+    y[:n_dm] = rng.standard_normal((n_dm, plan.n_out))
+    xd, yd = torch.from_numpy(x).cuda(), torch.from_numpy(y).cuda()
+    print("quads n_chan=%d n_samp=%d n_dm=%d" % (n_chan, n_samp, n_dm), flush=True)
+    got, grad = plan.forward(xd[:n_chan]).clone(), plan.adjoint(yd[:n_dm])[:, :n_samp].clone()
+    want, ab = oracle.forward_f32(np.ascontiguousarray(x[:n_chan, :n_samp]), n_samp, s)
+    assert np.all(np.abs(got.cpu().numpy().astype(np.float64) - want) <= (n_chan + 32) * EPS * ab + 1e-30)
+    wantg = oracle.adjoint(y[:n_dm], n_chan, n_samp, s)
+    abg = oracle.adjoint(np.abs(y[:n_dm]), n_chan, n_samp, s)
+    assert np.all(np.abs(grad.cpu().numpy().astype(np.float64) - wantg) <= (n_dm + 32) * EPS * abg + 1e-30)
+    for d in (0, 1):
+        t = plan.tiles(d)
+        plan.set_tiles(d, t["shape"], t["order"])
+        assert not plan.shares_sums(d)
+    assert torch.equal(plan.forward(xd[:n_chan]), got) and torch.equal(plan.adjoint(yd[:n_dm])[:, :n_samp], grad)
 
 
 @pytest.mark.parametrize("dtype", ["u8", "u4", "u16"])
@@ -69,3 +151,24 @@ def test_beams_by_shared_sums_and_by_their_shape(dd, dtype):
     print(dtype, rep, [batch.shares_sums(b) for b in range(5)], flush=True)
     assert batch.shares_sums(0) and batch.shares_sums(2)  # also the beam whose tiles were chosen
     check()
+
+
+@pytest.mark.parametrize("dtype", ["u8", "u4", "u16"])
+def test_replayed_group_sums(dd, dtype):
+    """Captured group sums replay with fresh inputs."""
+    cfg = dict(dtype=dtype, n_chan=1024, n_samp=9000, f_high=1500.0, chan_bw=300.0 / 1024, t_samp=64e-6, dm_start=0.0,
+               dm_step=0.1, n_dm=64)
+    x = _input(dtype, 1024, 9000, 9)
+    plan = plan_for(dd, cfg, in_pitch_bytes=x.strides[0])
+    assert plan.shares_sums(0)
+    xd = torch.from_numpy(x).cuda()
+    out = torch.empty((plan.n_dm, plan.out_pitch), dtype=torch.float32, device="cuda")
+    plan.forward(xd, out=out)
+    g = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(g):
+        plan.forward(xd, out=out)
+    for k in range(3):
+        xd.copy_(torch.from_numpy(np.roll(x, k + 1, axis=0)).cuda())
+        g.replay()
+        torch.cuda.synchronize()
+        assert torch.equal(out[:, : plan.n_out], plan.forward(xd))
