@@ -438,32 +438,41 @@ static double launch_us(double longest, double mean, double rounds, double overl
 // channels or workgroups, and refuses 128 ch x 32768 x 256 DMs of step 1 (42 us against 36)
 // by far more than that.
 //
-// From the tables: a workgroup of group sums takes a start of 9 us (16-bit: 11) and about
-// 8 clocks per building instruction of its busiest SIMD, step by step; one of the other
-// kernels a start and a time per channel, less where a CU has only one of them.  Constants
-// fitted to 1160 plans (32-4096 ch, 16-1500 DMs of step 0.02-2, 2000-300000 outputs at
-// 1200-1550 MHz), timed both ways: group sums to 7-10%, the others to 5-9%.  Without this
-// model 128 of 593 8-bit plans of that set ran by group sums that are up to 1.86 times as
-// slow as their shape (200 ch x 82109 x 116 DMs: 98 against 78 us), 19 of 259 4-bit and 5 of 241
-// 16-bit ones up to 1.31 and 1.39; with it 5, none and 1, at most 1.07, and 21 that would gain 2%
-// or more (one 22%, the others up to 17%) run their shape.  On the two plans above, 4-bit 8192 ch x
-// 2^18 x 500 and 16-bit the same, group sums against the other kernels: 353 / 820, 1.09 /
-// 1.78, 13.1 / 22.4 and 21.7 / 37.7 ms.
+// From the tables: a workgroup of group sums takes a start of 9 us (16-bit: 12) and about
+// 9 clocks per building instruction of its busiest SIMD, step by step; one of the other
+// kernels a start and a time per channel, less where a CU has only one of them; both less
+// where few run.  Constants fitted to 1160 plans (32-4096 ch, 16-1500 DMs of step 0.02-2,
+// 2000-300000 outputs at 1200-1550 MHz), timed both ways: group sums to 6-9%, the others to
+// 5-8%.  Without this model 128 of 593 8-bit plans of that set ran by group sums that are up
+// to 1.86 times as slow as their shape (200 ch x 82109 x 116 DMs: 98 against 78 us), 19 of 259
+// 4-bit and 5 of 241 16-bit ones up to 1.31 and 1.39; with it 5, 1 and 1, at most 1.07, and
+// 11 that would gain 2% or more (one 22%) run their shape.  Of 700 other plans 50 were slower
+// by group sums without it; with it 7, at most 1.10, and 3 that would gain 2 to 4% run their shape.
+// On the two plans above, 4-bit 8192 ch x 2^18 x 500 and 16-bit the same, group sums against
+// the other kernels: 353 / 820, 1.09 / 1.78, 13.1 / 22.4 and 21.7 / 37.7 ms.
 //
 // A beam of a batch: the same two models without rounds, for many workgroups in flight (220
 // plans as batches of themselves: 2 of 106 8-bit and 10 of 49 4-bit ones were up to 1.57 times as
 // slow by group sums without the second model, 1 and 2 with it).
 namespace {
 struct GroupModel {
-  double start, op, overlap, tail;  // group sums: us of a workgroup, and per instruction; several rounds
+  // group sums: us of a workgroup and per instruction with all CUs busy, how much less with few;
+  // several rounds
+  double start, op, idle, overlap, tail;
+  // the other kernel's workgroup, two of which share a CU; its us, and per channel
   int rows;
-  double samples;                   // the other kernel's workgroup, two of which share a CU,
-  double own_start, own_chan, alone, own_overlap, own_tail;  // its us, per channel (share of it where alone on its CU)
+  double samples, own_start, own_chan;
+  // shares of the time per channel: one on every CU, how much less with few; the start of a second one
+  double alone, own_idle, second, own_overlap, own_tail;
+  double margin;  // of the other kernel's time that group sums may take
   double batch_start, batch_op, batch_own_start, batch_own_chan;  // the same among many beams
 };
-constexpr GroupModel kGroup8 = {8.64, 0.00331, 0.665, 1.13, 32, 512, 5.84, 0.229, 0.64, 0.79, 0.72, 7.1, 0.003, 5.8, 0.206};
-constexpr GroupModel kGroup4 = {8.95, 0.00347, 0.687, 1.30, 16, 1008, 9.45, 0.243, 0.82, 0.68, 0.85, 9.0, 0.00286, 7.0, 0.18};
-constexpr GroupModel kGroup16 = {11.4, 0.00378, 0.864, 0.75, 32, 1024, 7.96, 0.651, 0.65, 0.81, 0.65, 7.7, 0.0028, 6.0, 0.955};
+constexpr GroupModel kGroup8 = {8.91, 0.00357, 0.119, 0.62, 1.13, 32, 512, 5.83, 0.2267, 0.715, 0.207, 1.02, 0.795, 0.724,
+                                1.01, 7.1, 0.003, 5.8, 0.206};
+constexpr GroupModel kGroup4 = {9.29, 0.00379, 0.140, 0.635, 1.30, 16, 1008, 9.71, 0.2482, 0.934, 0.418, 0.951, 0.663,
+                                0.852, 0.97, 9.0, 0.00286, 7.0, 0.18};
+constexpr GroupModel kGroup16 = {11.96, 0.00413, 0.149, 0.796, 0.754, 32, 1024, 7.96, 0.6722, 0.668, 0.122, 0.947, 0.783,
+                                 0.647, 1.0, 7.7, 0.0028, 6.0, 0.955};
 }  // namespace
 
 bool build_group_sums(const dd_plan &p, bool batch, GroupTables *t) {
@@ -492,10 +501,12 @@ bool build_group_sums(const dd_plan &p, bool batch, GroupTables *t) {
     const double own = 0.95 * (m.batch_own_start + m.batch_own_chan * slow * p.desc.n_chan) * own_rounds;
     max_work = (own / rounds - m.batch_start) / m.batch_op;
   } else {
-    const double own = (bits == 4 ? 0.95 : 1.0) *
-                       (own_rounds <= 0.5 ? m.own_start + m.alone * m.own_chan * slow * p.desc.n_chan
-                                          : launch_us(own_wg, own_wg, own_rounds, m.own_overlap, m.own_tail));
-    max_work = ((rounds <= 1 ? own : own / (m.overlap * (rounds + m.tail))) - m.start) / m.op;
+    const double share = own_rounds <= 0.5 ? m.alone + m.own_idle * (own_rounds - 0.5)
+                                           : m.second + (1.0 - m.second) * 2.0 * (std::min(own_rounds, 1.0) - 0.5);
+    const double own = m.margin * (own_rounds <= 1 ? m.own_start + m.own_chan * slow * p.desc.n_chan * share
+                                                   : launch_us(own_wg, own_wg, own_rounds, m.own_overlap, m.own_tail));
+    const double op = m.op * (1.0 - m.idle * std::max(0.0, 1.0 - rounds));
+    max_work = ((rounds <= 1 ? own : own / (m.overlap * (rounds + m.tail))) - m.start) / op;
   }
   if (max_work <= 0) return false;
   const GroupTables *g = &p.gtab;
