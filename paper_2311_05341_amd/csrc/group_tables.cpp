@@ -432,29 +432,42 @@ bool build_group_tables(const int32_t *shift, int n_dm, int n_chan, int bits, in
   try {
     std::vector<Block> blocks(n_blk);
     const int64_t work = (int64_t)n_blk * n_chan;
-    if (max_cost > 0) {  // plans that are far from it: the costs of two blocks tell
-      Block &mid = blocks[(n_blk - 1) / 2], &last = blocks[n_blk - 1];
-      build_block(in, (n_blk - 1) / 2, true, &mid);
-      if (mid.ok && n_blk > 1) build_block(in, n_blk - 1, true, &last);
-      if (!mid.ok || !last.ok || 0.5 * n_blk * (mid.cost + last.cost) > (n_blk > 2 ? 1.2 : 1.0) * max_cost) return false;
-    }
-    if (max_work > 0) {  // and the instructions of one
-      build_block(in, (n_blk - 1) / 2, false, &blocks[(n_blk - 1) / 2]);
-      if (!blocks[(n_blk - 1) / 2].ok || blocks[(n_blk - 1) / 2].work > 1.3 * max_work) return false;
-    }
-    const int nthr = (int)std::min<int64_t>({kMaxParts, n_blk, std::max<int64_t>(1, work / 1024),
+    const int nthr = (int)std::min<int64_t>({kMaxParts, n_blk, std::max<int64_t>(1, work / 512),
                                              std::max(1u, std::thread::hardware_concurrency())});
-    uint8_t failed[kMaxParts] = {};
-    run_parts(nthr, [&](int k) {
-      try {
-        for (int b = k; b < n_blk; b += nthr)
-          if (!blocks[b].n_steps) build_block(in, b, false, &blocks[b]);
-      } catch (const std::bad_alloc &) {
-        failed[k] = 1;
+    // Blocks `first`, `first` + step, ... as run by up to nthr threads; false on bad_alloc.
+    auto build = [&](int first, int step, bool cost_only) {
+      uint8_t failed[kMaxParts] = {};
+      const int count = (n_blk - first + step - 1) / step;
+      const int n = (int)std::min<int64_t>({nthr, count, std::max<int64_t>(1, (int64_t)count * n_chan / 512)});
+      run_parts(n, [&](int k) {
+        try {
+          for (int b = first + k * step; b < n_blk; b += n * step)
+            if (!blocks[b].n_steps) build_block(in, b, cost_only, &blocks[b]);
+        } catch (const std::bad_alloc &) {
+          failed[k] = 1;
+        }
+      });
+      for (uint8_t f : failed)
+        if (f) return false;
+      return true;
+    };
+    if (max_cost > 0) {  // plans that are far from it: the costs of all blocks, or of two where that takes longer, tell
+      const int mid = (n_blk - 1) / 2, step = n_blk <= nthr ? 1 : n_blk - 1 - mid;
+      const int first = n_blk <= nthr ? 0 : mid;
+      if (!build(first, step, true)) return false;
+      double cost = 0;
+      for (int b = first; b < n_blk; b += step) {
+        if (!blocks[b].ok) return false;
+        cost += blocks[b].cost;
       }
-    });
-    for (uint8_t f : failed)
-      if (f) return false;
+      if (n_blk <= nthr ? cost > max_cost : 0.5 * n_blk * cost > 1.2 * max_cost) return false;
+    }
+    if (max_work > 0 && n_blk > nthr) {  // and the instructions of one
+      Block &mid = blocks[(n_blk - 1) / 2];
+      build_block(in, (n_blk - 1) / 2, false, &mid);
+      if (!mid.ok || mid.work > 1.3 * max_work) return false;
+    }
+    if (!build(0, 1, false)) return false;
     size_t recs = 0, ops = kGrpBlockWords, sums = 0;
     t->head.lo = 0;  // the idle operation block loads the tile's own samples of channel 0
     t->head.hi = kGrpChunk + 12;
