@@ -42,7 +42,7 @@ struct dd_batch {
   std::vector<int> shape;         // per beam (original index): its shape
   std::vector<char> sums;         // per beam: it runs by group sums (beams at their default shape)
   std::vector<IntTables> tables;  // per beam (original index), for its shape (empty for direct-read and group sums)
-  std::vector<signed char> pay;   // per beam: whether group sums pay (-1: not looked at)
+  std::vector<signed char> pay;   // per beam: a SumsPay (-1: not looked at)
   std::vector<std::shared_ptr<const GroupTables>> gtabs;  // per beam: their table where its plan holds none
   std::vector<int> order;         // beams in decreasing per-item cost
   std::vector<BatchGroup> groups;
@@ -191,34 +191,44 @@ static int default_shape(const dd_plan &p) {
   return kNumIntShapes + (p.desc.dtype == DD_U4 ? 1 : 0);
 }
 
-// Whether beam i runs by group sums unless its plan's tiles were chosen explicitly; found out
-// once, with the table where its plan holds none.
-static bool sums_pay(dd_batch *b, size_t i) {
-  if (b->pay[i] >= 0) return b->pay[i] > 0;
+// Whether group sums pay for beam i; found out once, with the table where its plan holds none.
+static SumsPay sums_pay(dd_batch *b, size_t i) {
+  if (b->pay[i] >= 0) return (SumsPay)b->pay[i];
   const dd_plan *p = b->plans[i];
   const size_t first = std::find(b->plans.begin(), b->plans.end(), p) - b->plans.begin();
   if (first < i) {
     b->pay[i] = sums_pay(b, first);
     b->gtabs[i] = b->gtabs[first];
   } else {
+    b->pay[i] = kSumsLose;
     try {
       auto t = std::make_shared<GroupTables>();
-      b->pay[i] = build_group_sums(*p, true, t.get());
+      const SumsPay pay = build_group_sums(*p, true, t.get());
       b->gtabs[i] = std::move(t);
+      b->pay[i] = pay;
     } catch (const std::bad_alloc &) {
-      b->pay[i] = 0;
     }
   }
-  return b->pay[i] > 0;
+  return (SumsPay)b->pay[i];
+}
+
+// The beams that run by group sums, of all or of those whose plans' tiles were not chosen
+// explicitly: those that pay, and next to them those that nearly do.
+static std::vector<char> beams_by_sums(dd_batch *b, bool all) {
+  const size_t n = b->plans.size();
+  std::vector<char> on(n, 0);
+  bool any = false;
+  for (size_t i = 0; i < n; ++i)
+    if (all || !b->plans[i]->chosen) any |= sums_pay(b, i) == kSumsPay;
+  for (size_t i = 0; i < n && any; ++i) on[i] = (all || !b->plans[i]->chosen) && sums_pay(b, i) != kSumsLose;
+  return on;
 }
 
 // Every beam at its plan's default.
 static Assignment default_assignment(dd_batch *b) {
   Assignment as;
-  for (size_t i = 0; i < b->plans.size(); ++i) {
-    as.shapes.push_back(default_shape(*b->plans[i]));
-    as.sums.push_back(!b->plans[i]->chosen && sums_pay(b, i));
-  }
+  for (const dd_plan *p : b->plans) as.shapes.push_back(default_shape(*p));
+  as.sums = beams_by_sums(b, false);
   return as;
 }
 
@@ -473,8 +483,7 @@ dd_status dd_batch_autotune(dd_batch *b, const void *const *d_in, float *const *
   cands.push_back(orig);
   const Assignment defaults = default_assignment(b);
   if (!(defaults == orig)) cands.push_back(defaults);
-  Assignment sums = defaults;  // (a plan's tiles chosen explicitly keep its beam's default off them)
-  for (size_t i = 0; i < b->plans.size(); ++i) sums.sums[i] = sums_pay(b, i);
+  const Assignment sums = {defaults.shapes, beams_by_sums(b, true)};
   if (!(sums == orig) && !(sums == defaults)) cands.push_back(sums);
   const Assignment plain = {defaults.shapes, none};
   if (!(plain == orig) && !(plain == defaults)) cands.push_back(plain);

@@ -112,9 +112,11 @@ dd_status choose_forward_tiles(dd_plan &p);
 // shape's kernel (gtab.use, qtab[direction].use are cleared, chosen is set).
 // With fill false the staged tables are only sized.
 dd_status set_tiles(dd_plan &p, int direction, int shape, int order, bool fill = true);
-// Whether the plan (batch: as a beam of a batch), with its default tiles, runs by group sums: the
-// tables are then the plan's own, if it holds them, else *t.
-bool build_group_sums(const dd_plan &p, bool batch, GroupTables *t);
+// Whether the plan (batch: as a beam of a batch), with its default tiles, is faster by group
+// sums (a beam's times within a tenth: near): the tables are then the plan's own, if it holds
+// them, else *t.
+enum SumsPay { kSumsLose, kSumsNear, kSumsPay };
+SumsPay build_group_sums(const dd_plan &p, bool batch, GroupTables *t);
 int num_shapes(const dd_plan &p);
 size_t table_bytes(const dd_plan &p);
 // Byte offsets of the plan's current tables inside a table workspace of

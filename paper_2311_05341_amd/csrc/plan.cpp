@@ -451,9 +451,13 @@ static double launch_us(double longest, double mean, double rounds, double overl
 // On the two plans above, 4-bit 8192 ch x 2^18 x 500 and 16-bit the same, group sums against
 // the other kernels: 353 / 820, 1.09 / 1.78, 13.1 / 22.4 and 21.7 / 37.7 ms.
 //
-// A beam of a batch: the same two models without rounds, for many workgroups in flight (220
-// plans as batches of themselves: 2 of 106 8-bit and 10 of 49 4-bit ones were up to 1.57 times as
-// slow by group sums without the second model, 1 and 2 with it).
+// A beam of a batch: the same two models without rounds, for many workgroups in flight, fitted
+// to 330 plans (128-1024 ch, 64-512 DMs) in batches of themselves (group sums to 7%, the
+// others to 2-4%).  There 8 of 157 4-bit beams were up to 1.26 times as slow by group sums; with
+// the second model two (1.04 and 1.20).  Next to beams that gain by group sums, up to a tenth is
+// given to them, since the two kernels fill each other's waits: eight 4-bit batches of 9-30
+// beams took 1 to 5% longer with the line at equal times less 3%, and the same at equal
+// times and at 5%, 10%, 20% and more above.
 namespace {
 struct GroupModel {
   // group sums: us of a workgroup and per instruction with all CUs busy, how much less with few;
@@ -468,14 +472,14 @@ struct GroupModel {
   double batch_start, batch_op, batch_own_start, batch_own_chan;  // the same among many beams
 };
 constexpr GroupModel kGroup8 = {8.91, 0.00357, 0.119, 0.62, 1.13, 32, 512, 5.83, 0.2267, 0.715, 0.207, 1.02, 0.795, 0.724,
-                                1.01, 7.1, 0.003, 5.8, 0.206};
+                                1.01, 4.43, 0.00256, 4.04, 0.1967};
 constexpr GroupModel kGroup4 = {9.29, 0.00379, 0.140, 0.635, 1.30, 16, 1008, 9.71, 0.2482, 0.934, 0.418, 0.951, 0.663,
-                                0.852, 0.97, 9.0, 0.00286, 7.0, 0.18};
+                                0.852, 0.97, 5.52, 0.00279, 5.45, 0.1676};
 constexpr GroupModel kGroup16 = {11.96, 0.00413, 0.149, 0.796, 0.754, 32, 1024, 7.96, 0.6722, 0.668, 0.122, 0.947, 0.783,
-                                 0.647, 1.0, 7.7, 0.0028, 6.0, 0.955};
+                                 0.647, 1.0, 8.04, 0.0035, 6.28, 0.9156};
 }  // namespace
 
-bool build_group_sums(const dd_plan &p, bool batch, GroupTables *t) {
+SumsPay build_group_sums(const dd_plan &p, bool batch, GroupTables *t) {
   const double kModel = 0.74, kCus = 256;
   const int bits = p.desc.dtype == DD_U4 ? 4 : p.desc.dtype == DD_U16 ? 16 : 8;
   const bool best_staged = !is_direct(p.def_fwd) && p.def_fwd.waves == 8;
@@ -496,10 +500,11 @@ bool build_group_sums(const dd_plan &p, bool batch, GroupTables *t) {
   const double own_rounds = own_wgs / (2 * kCus), own_wg = m.own_start + m.own_chan * slow * p.desc.n_chan;
   // the most instructions per block that pay: of the largest block in a single round, else (and in
   // a batch) of all on average
-  double max_work;
+  double max_work, near_work = 0;
   if (batch) {
-    const double own = 0.95 * (m.batch_own_start + m.batch_own_chan * slow * p.desc.n_chan) * own_rounds;
+    const double own = (m.batch_own_start + m.batch_own_chan * slow * p.desc.n_chan) * own_rounds;
     max_work = (own / rounds - m.batch_start) / m.batch_op;
+    near_work = (1.1 * own / rounds - m.batch_start) / m.batch_op;
   } else {
     const double share = own_rounds <= 0.5 ? m.alone + m.own_idle * (own_rounds - 0.5)
                                            : m.second + (1.0 - m.second) * 2.0 * (std::min(own_rounds, 1.0) - 0.5);
@@ -508,19 +513,22 @@ bool build_group_sums(const dd_plan &p, bool batch, GroupTables *t) {
     const double op = m.op * (1.0 - m.idle * std::max(0.0, 1.0 - rounds));
     max_work = ((rounds <= 1 ? own : own / (m.overlap * (rounds + m.tail))) - m.start) / op;
   }
-  if (max_work <= 0) return false;
+  near_work = std::max(near_work, max_work);
+  if (near_work <= 0) return kSumsLose;
   const GroupTables *g = &p.gtab;
   if (p.gtab.data.empty()) {
-    if (!build_group_tables(p.shift.data(), p.desc.n_dm, p.desc.n_chan, bits, p.in_pitch_bytes, t, limit, max_work) ||
+    if (!build_group_tables(p.shift.data(), p.desc.n_dm, p.desc.n_chan, bits, p.in_pitch_bytes, t, limit, near_work) ||
         t->data.size() * 4 > p.def_table_bytes) {
       *t = GroupTables();
-      return false;
+      return kSumsLose;
     }
     g = t;
   }
-  const bool pays = g->cost <= limit && (rounds <= 1 && !batch ? g->max_work : g->work / (double)n_blk) < max_work;
-  if (!pays) *t = GroupTables();
-  return pays;
+  const double work = rounds <= 1 && !batch ? g->max_work : g->work / (double)n_blk;
+  if (g->cost <= limit && work < max_work) return kSumsPay;
+  if (g->cost <= limit && work < near_work) return kSumsNear;
+  *t = GroupTables();
+  return kSumsLose;
 }
 
 // Whether a direction of a float plan runs by quad sums (quad_f32.hip) instead of its
@@ -593,7 +601,7 @@ dd_status choose_forward_tiles(dd_plan &p) {
     }
   } else {
     GroupTables t;
-    if (build_group_sums(p, false, &t)) {
+    if (build_group_sums(p, false, &t) == kSumsPay) {
       p.gtab = std::move(t);
       p.gtab.use = true;
     } else {

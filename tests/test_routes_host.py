@@ -77,3 +77,30 @@ def test_workspace_is_that_of_the_default_shapes(dd, dtype, n_dm):
         t = p.tiles(d)
         p.set_tiles(d, t["shape"], t["order"])
         assert p.info.dev_table_bytes == want and p.info.tune_ws_bytes >= want
+
+
+def test_beams_near_the_line_follow_the_batch(dd):
+    """A 4-bit beam that group sums slow down a little (12.7 against 11.7 us in a batch of itself) runs
+    by them next to one that they speed up (the two kernels fill each other's waits), else not;
+    and never after its plan's tiles were chosen."""
+    import ctypes
+
+    lib = ctypes.CDLL(dd.LIB_PATH)
+    lib.dd_batch_create.argtypes = [ctypes.POINTER(ctypes.c_void_p), ctypes.c_int32, ctypes.POINTER(ctypes.c_void_p)]
+    lib.dd_batch_shares_sums.argtypes = [ctypes.c_void_p, ctypes.c_int32]
+    lib.dd_batch_destroy.argtypes = [ctypes.c_void_p]
+
+    def shares(*plans):
+        h = ctypes.c_void_p()
+        assert lib.dd_batch_create((ctypes.c_void_p * len(plans))(*[p._h for p in plans]), len(plans), ctypes.byref(h)) == 0
+        got = [lib.dd_batch_shares_sums(h, i) for i in range(len(plans))]
+        lib.dd_batch_destroy(h)
+        return got
+
+    near = _plan(dd, "u4", 128, 42994, 73, 0.0, 0.5, 1500.0, 256.0)
+    gains = _plan(dd, "u4", 1024, 40000, 300, 0.0, 0.1, 1500.0, 64.0)
+    loses = _plan(dd, "u4", 64, 16384, 10, 0.0, 21.0, 1500.0, 64.0)
+    assert shares(near, near) == [0, 0] and shares(near, gains) == [1, 1] and shares(gains, loses, near) == [1, 0, 1]
+    t = gains.tiles(0)
+    gains.set_tiles(0, t["shape"], t["order"])
+    assert shares(near, gains) == [0, 0]
