@@ -746,6 +746,15 @@ def bench_batch_set(args, dd, torch, synth):
         sys.exit("batched outputs differ from the plain calls")
 
 
+def run_as(plan, tiles):
+    """Puts an integer plan on the tiles of a survey's range and returns its kernel's name.  Set
+    only where they differ: setting tiles, the default ones too, takes a plan off shared sums."""
+    if tiles != plan.tiles(0):
+        plan.set_tiles(0, tiles["shape"], tiles["order"])
+    return ("fwd_group_kernel" if plan.shares_sums(0) else
+            "fwd_int_kernel" if tiles["row_block"] else "fwd_direct_kernel")
+
+
 def bench_survey(args, dd, torch, synth):
     """Multi-range DM plan (binning + one transform per range) over one 8-bit filterbank.
 
@@ -801,7 +810,9 @@ def bench_survey(args, dd, torch, synth):
 
     # Per-kernel breakdown: the same kernels launched one by one (binning into
     # buffers of the survey's layout, each range through a plan with the survey's
-    # tile choice), each timed with HIP events on the current stream.
+    # tile choice), each timed with HIP events on the current stream.  The survey does not tell
+    # whether tuning took a range off shared sums to its default tiles: such a range is timed by
+    # shared sums here, and the parts then add up to less than the step.
     def timed(fn, reps):
         fn()
         e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
@@ -833,11 +844,11 @@ def bench_survey(args, dd, torch, synth):
         p = dd.Plan(n_chan, ri["n_samp"], ri["dtype"], cfg["f_high"], cfg["chan_bw"], ri["t_samp"], start, step,
                     n_dm, in_pitch_bytes=src.stride(0) * src.element_size())
         tl = sv.tiles(r)
-        p.set_tiles(0, tl["shape"], tl["order"])
+        kernel = run_as(p, tl)
         ms = timed(lambda: p.forward(src, out=outs[r]), max(1, args.steps // 2))
         a = float(n_dm) * ri["n_out"] * n_chan
         parts.append({"range": r, "dm_start": start, "dm_step": step, "n_dm": n_dm, "bin": b, "input": ri["dtype"],
-                      "n_out": ri["n_out"], "ms": ms, "Tadds_s": a / ms / 1e9, "tiles": tl})
+                      "n_out": ri["n_out"], "ms": ms, "Tadds_s": a / ms / 1e9, "tiles": tl, "kernel": kernel})
         del p
     dom = max(parts, key=lambda q: q["ms"])
     log("survey parts: %s; bins: %s; corner turn: %s" % (parts, bins, turn))
@@ -850,7 +861,7 @@ def bench_survey(args, dd, torch, synth):
                    "adds_per_step": adds, "input_layout": "time-major spectra" if tm else "channel-major rows"},
         "x_realtime": n_samp * t_samp / (ms_step * 1e-3),
         "roofline": {"bound": "alu", "achieved": dom["Tadds_s"], "peak": None, "unit": "Tadds/s",
-                     "frac": None, "traffic": None, "kernel": "fwd_group_kernel or the range's shape",
+                     "frac": None, "traffic": None, "kernel": dom["kernel"],
                      "range": dom["range"], "kernel_ms": dom["ms"]},
         "parts": parts, "binning": bins, "corner_turn": turn, "autotune_s": tune_s,
         "sum_of_parts_ms": sum(q["ms"] for q in parts) + sum(q["ms"] for q in bins) + (turn["ms"] if turn else 0.0),

@@ -82,3 +82,30 @@ def test_wide_beam_batches_read_directly():
             p = dd.Plan(c["n_chan"], c["n_samp"], dtype, c["f_high"], c["chan_bw"], c["t_samp"], c["dm_start"],
                         c["dm_step"], c["n_dm"], bind=False)
             assert p.tiles(0)["row_block"] == 0, (dtype, c)
+
+
+def test_survey_ranges_are_timed_on_the_kernel_they_run():
+    """A range whose tiles are its plan's own stays on shared sums; other tiles are set and name
+    their shape's kernel."""
+    import paper_2311_05341_amd as dd
+    b = _bench()
+    plan = dd.Plan(1024, 65536, "u8", 1500.0, 0.29, 6.4e-05, 0.0, 0.1, 512, bind=False)
+    assert plan.shares_sums(0)
+    assert b.run_as(plan, plan.tiles(0)) == "fwd_group_kernel" and plan.shares_sums(0)
+
+    class Staged:
+        """A plan as far as run_as uses one; set_tiles of a real plan loads its tables on a GPU."""
+        now = dict(plan.tiles(0))
+
+        def tiles(self, direction):
+            return self.now
+
+        def set_tiles(self, direction, shape, order):
+            self.now = dict(self.now, shape=shape, order=order)
+
+        def shares_sums(self, direction):
+            return False
+    staged = Staged()
+    want = dict(plan.tiles(0), order=1 - plan.tiles(0)["order"] % 2)
+    assert b.run_as(staged, want) == "fwd_int_kernel" and staged.now == want
+    assert b.run_as(staged, dict(want, row_block=0)) == "fwd_direct_kernel"
