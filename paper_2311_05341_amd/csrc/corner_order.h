@@ -12,13 +12,14 @@ namespace dd {
 //
 // Runs against the order by time tiles, us:
 // * Float rows of whole lines are read a little faster in order (1024 ch x 100000: 166 / 158).
-// * A multiple of 8 channel tiles (one 8 of wider samples aside): the order by time tiles, too, keeps a channel
-//   tile on its XCD, and runs pay only for turns far larger than the caches (8-bit 4096 ch
-//   x 436460: 739 / 1041, 8192 x 40002: 151 / 173); below, 8 XCDs each with a time tile of
-//   their own cost up to 15% (float 16384 x 5000: 155 / 138, 16-bit 16384 x 5000: 72 / 65,
-//   4-bit 16384 x 8300: 40 / 35, 8-bit 32768 x 1994: 28 / 25).  The line is at 1.7e8 samples
-//   for all types, over rows of whole lines of 8 or 16 bits at 1.4 GB read and written (8-bit
-//   4096 ch x 136192: 1.07 times, x 253562: 0.92; 4-bit 2048 x 166912: 0.91).  Spectra that do not end on a line pay in any case.
+// * A multiple of 8 channel tiles (but for just 8 of samples wider than 4 bits): the order by
+//   time tiles, too, keeps a channel tile on its XCD, and runs pay only for turns far larger
+//   than the caches (8-bit 4096 ch x 436460: 739 / 1041, 8192 x 40002: 151 / 173); below, 8
+//   XCDs each with a time tile of their own cost up to 15% (float 16384 x 5000: 155 / 138,
+//   16-bit 16384 x 5000: 72 / 65, 4-bit 16384 x 8300: 40 / 35, 8-bit 32768 x 1994: 28 / 25).
+//   The line is at 1.7e8 samples for all types, over rows of whole lines of 8 or 16 bits at
+//   1.4 GB read and written (8-bit 4096 ch x 136192: 1.07 times, x 253562: 0.92; 4-bit 2048 x
+//   166912: 0.91).  Spectra that do not end on a line pay in any case.
 // * One channel tile over rows of whole lines: only its spectra can share lines (4-bit 257 ch x
 //   231424: 23 / 31, 16-bit 128 x 200000: 16 / 14, 8-bit 64 x 2152448: 63 / 55); large ones of
 //   at least half a tile gain a little (8-bit 256 x 2294784: 225 / 240).  Short 4-bit ones do

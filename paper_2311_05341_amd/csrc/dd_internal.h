@@ -182,11 +182,11 @@ inline int launch_forward(const dd_plan &p, const void *tables, const void *d_in
 }
 int launch_forward_f32(const dd_plan &p, const void *tables, const void *d_in, float *d_out, int64_t out_pitch,
                        void *stream, int64_t out_limit = 0);
-// Float tile shapes compiled into the library: (ns, per_wave, waves, row_block).
 // Quad sums (quad_f32.hip): out[n_outputs][out_pitch], samples 0..out_len-1, from the rows x
 // of row_len floats.
 int launch_quad(const QuadTables &q, const void *tables, const float *x, int64_t row_pitch, int n_rows, int64_t row_len,
                 float *out, int64_t out_pitch, int n_outputs, int64_t out_len, void *stream);
+// Float tile shapes compiled into the library: (ns, per_wave, waves, row_block).
 extern const int kF32Shapes[][4];
 extern const int kNumF32Shapes;
 // Integer tile shapes compiled into the library: (ns, dm_per_wave, waves,

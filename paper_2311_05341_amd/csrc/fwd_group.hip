@@ -2,11 +2,10 @@
 // group_tables.h).
 //
 // A workgroup owns 32 (16-bit input: 64) DM rows x one time tile and runs through groups of
-// neighbouring channels.  Per group, the builder waves compute the partial sums
-// of its few delay patterns over the tile's window into LDS, and the summing
-// waves add to every DM row the window of the pattern it follows, at the row's
-// own offset: one LDS read and one add per row, word and group, where a kernel
-// that sums channel by channel does one per channel.
+// neighbouring channels.  Per group, its waves compute the partial sums of the group's few
+// delay patterns over the tile's window into LDS, and each adds to its own DM rows the window
+// of the pattern a row follows, at the row's own offset: one LDS read and one add per row,
+// word and group, where a kernel that sums channel by channel does one per channel.
 //
 // LDS words: 8- and 4-bit input packs two 16-bit partial sums per word, the
 // samples k and k + kGrpWin of the tile, so that a window at any offset starts

@@ -11,14 +11,16 @@
 //
 // The floor is LDS: one word read per four rows, output and sample, where the kernels that
 // stage rows read one per row (they run at 80% of it).  Bound by instruction issue and the
-// barriers: on 1024 ch x 2^17 x 1024 DMs (6 patterns of 770 words per quad) LDS is 45% busy,
-// vector units 45%.  Forward and adjoint of that plan: 17.0 ms by staged rows, 8.8 by quad
-// sums; 1024 ch x 131900 x 512 DMs of step 0.1: 9.6 and 3.3.  On the way there: windows
-// loaded when a pattern needs them, one pattern after another: 10.9; a stream loaded ahead
-// with a bounded descriptor per operation: 13.4, without where the block's windows lie
-// inside their rows: 10.8; rows taken over by one asm branch instead of the compiler's
-// copies: 9.5; 256 words of a pattern per record instead of 192: 9.0.  8 waves of 128
-// outputs' registers each (384 or 576 words per record): 12.8 and 13.4; 32 outputs: 11.2.
+// barriers: on 1024 ch x 2^17 x 1024 DMs (6.2 patterns of 770 words per quad on average, 3.6
+// quads a step, whose busiest wave has 1.4 times the mean of records) LDS is 47% busy,
+// vector units 45% (adjoint: both 43%).  Forward and adjoint of that plan: 17.0 ms by
+// staged rows, 8.8 by quad sums; 1024 ch x 131900 x 512 DMs of step 0.1: 9.6 and 3.3.  On the
+// way there: windows loaded when a pattern needs them, one pattern after another: 10.9; a
+// stream loaded ahead with a bounded descriptor per operation: 13.4, without where the
+// block's windows lie inside their rows: 10.8; rows taken over by one asm branch instead of
+// the compiler's copies: 9.5; 256 words of a pattern per record instead of 192: 9.0.  8 waves
+// of 128 outputs' registers each (384 or 576 words per record): 12.8 and 13.4; 32 outputs:
+// 11.2.
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 

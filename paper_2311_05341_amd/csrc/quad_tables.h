@@ -6,8 +6,8 @@
 //   P_r(t + sh(o, k)) = sum_c X(k + c, t + sh(o, k) + r_c),  r_c = sh(o, k + c) - sh(o, k),
 // and the outputs of a block share few delay patterns r (neighbouring outputs differ by
 // much less than a sample of delay between neighbouring rows).  So each pattern's sums
-// are computed once, over the words that its outputs read, and every output adds one
-// word per quad and sample: the same additions in the same order as row by row.
+// are computed once, over the range of words that the block's outputs read, and every output
+// adds one word per quad and sample: the same additions in the same order as row by row.
 #pragma once
 
 #include <stdint.h>
